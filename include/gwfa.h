@@ -437,7 +437,8 @@ int gwfa_label_entries(int32_t n_vtx, const uint8_t *seq, const int64_t *seq_off
  * [6] MLP evaluations, [7] entries dropped by pruning, [8] scores run,
  * [9]..[12] device wall-clock ticks (100 MHz) summed over queries spent in
  * the expansion+extension pass, the crossing rounds, the crossing merge and
- * the pruning pass, [13]..[15] reserved.  out16 receives 16 values. */
+ * the pruning pass (scores of pruned runs with at most 64 entries: all but the
+ * crossing rounds under [9]), [13]..[15] reserved.  out16 receives 16 values. */
 int gwfa_stats(gwfa_ctx *ctx, int64_t *out16, int32_t reset);
 
 #ifdef __cplusplus

@@ -279,6 +279,20 @@ __device__ __forceinline__ int64_t lab_base(int4 lab) {
     return (int64_t)(((uint64_t)(uint32_t)lab.y << 32) | (uint32_t)lab.x);
 }
 
+// LDS lists of the narrow path (narrow_scores): the list being expanded (slots
+// 2 .. n+1, two sentinels on each side), the list being built and the crossing
+// candidates.  Entries carry their vertex's label base and length.
+struct Narrow {
+    static constexpr int N = 64;       // entries of a list: one per lane of the wave
+    static constexpr int C = 128;      // crossing candidates kept here, the rest in the arena
+    int4 ie[N + 4];
+    int4 oe[N];
+    int64_t ib[N + 4], ob[N];
+    int32_t iw[N + 4], it[N + 4], il[N + 4];
+    int32_t ow[N], ot[N], ol[N];
+    int32_t cu[C], ck[C], cw[C], ct[C];
+};
+
 // Workgroup LDS, sized for the workgroup (merge keys, the staged batch) and
 // the mode (the network's weights only where it runs).
 template <int BLOCK, int MODE>
@@ -307,22 +321,55 @@ struct Shared {
     ull mlp;
     ull tick[4];      // wall-clock ticks per phase (thread 0)
     int32_t scan[16];
-    ull skeys[XS];
-    int32_t sidx[XS];
-    int32_t xcnt[XS];       // merge: main-list entries below each crossing entry
     ull samp[nsamp(BLOCK)]; // sort keys of list entries 0, SAMP, 2 SAMP, ... written by the expansion
-    // expansion: the entries of one batch of the source list at slots 2 ..
-    // BLOCK+1 plus two neighbours on each side (slots 0, 1, BLOCK+2, BLOCK+3)
-    int32_t nbv[NB], nbk[NB], nbo[NB], nbd[NB], nbw[NB], nbt[NB];
-    // crossing rounds: claimed diagonals (vertex, diagonal, page, label length,
-    // predecessor's trace index, label base) and candidates (target, diagonal,
-    // trace index of the crossing diagonal)
-    int32_t xsv[XC + 1], xsk[XC + 1], xsd[XC + 1], xsl[XC + 1], xst[XC + 1];
-    int64_t xsb[XC + 1];
-    int32_t csu[CS + 1], csk[CS + 1], cst[CS + 1];
+    // what the narrow path is called with and what it hands back (narrow_scores)
+    int32_t nr_code, nr_s, nr_n, nr_n1, nr_round, nr_vmx, nr_list, nr_r;
+    uint32_t nr_mask;
+    int64_t nr_work, nr_arena;
+    // The narrow path's lists share the storage of the wide path's arrays: a
+    // score runs on one of the two.
+    union {
+        struct {
+            ull skeys[XS];
+            int32_t sidx[XS];
+            int32_t xcnt[XS];       // merge: main-list entries below each crossing entry
+            // expansion: the entries of one batch of the source list at slots 2 ..
+            // BLOCK+1 plus two neighbours on each side (slots 0, 1, BLOCK+2, BLOCK+3)
+            int32_t nbv[NB], nbk[NB], nbo[NB], nbd[NB], nbw[NB], nbt[NB];
+            // crossing rounds: claimed diagonals (vertex, diagonal, page, label length,
+            // predecessor's trace index, label base) and candidates (target, diagonal,
+            // trace index of the crossing diagonal)
+            int32_t xsv[XC + 1], xsk[XC + 1], xsd[XC + 1], xsl[XC + 1], xst[XC + 1];
+            int64_t xsb[XC + 1];
+            int32_t csu[CS + 1], csk[CS + 1], cst[CS + 1];
+        };
+        Narrow nw;
+    };
     alignas(16) uint16_t mlpw[MODE >= 2 ? 4808 : 8];   // pruning network (bfloat16), loaded once per launch
     float mscale[8];        // feature scales
 };
+
+// The workgroup's LDS: one variable per instantiation, named through this
+// function by the kernel and by the narrow path (a function of its own).
+template <int BLOCK, int MODE>
+__device__ __forceinline__ Shared<BLOCK, MODE>& lds() {
+    __shared__ Shared<BLOCK, MODE> S;
+    return S;
+}
+
+// The launch arguments as the kernel received them, in constant memory.
+typedef const __attribute__((address_space(4))) KArgs* KernArg;
+__device__ __forceinline__ KernArg kernarg() { return (KernArg)__builtin_amdgcn_kernarg_segment_ptr(); }
+// The same through a pointer the compiler cannot follow: what is read through
+// it is loaded (scalar cache) where it is used.  Read directly, every argument
+// and every pointer made from one stays in scalar registers for the whole
+// kernel, and with about 250 such values the compiler moves them to and from
+// vector lanes in every inner loop.
+__device__ __forceinline__ const KArgs& fresh_args() {
+    KernArg p = kernarg();
+    asm volatile("" : "+s"(p));
+    return *(const KArgs*)p;
+}
 
 // Per-query view of the arena and of the read.
 struct Q {
@@ -342,6 +389,48 @@ struct Q {
     uint32_t gen;
     bool tb, track;   // traced walks; walk lengths and lags tracked (pruning, dumps)
 };
+
+// The arena's parts and the launch's read store, from (fresh) arguments.
+__device__ __forceinline__ void bind_q(Q& q, const KArgs& A, char* arena) {
+    q.rd = A.rd;
+    q.dir = reinterpret_cast<ull*>(arena + A.o_dir);
+    q.pages = reinterpret_cast<Page*>(arena + A.o_pages);
+    q.mkey = reinterpret_cast<ull*>(arena + A.o_mkey);
+    q.Tv = reinterpret_cast<int32_t*>(arena + A.o_tv);
+    q.Tt = reinterpret_cast<int32_t*>(arena + A.o_tt);
+    q.tb = A.traceback != 0;
+}
+// View of query r in a workgroup's arena (mask and gen are set per attempt).
+// The query's parameters are the same in every lane: readfirstlane keeps them
+// in scalar registers (and tests on them branches of the whole wave).
+template <int MODE>
+__device__ __forceinline__ Q make_q(const KArgs& A, char* arena, int r) {
+    Q q;
+    q.q0 = uniform64(A.rd_off[r]);
+    q.qlen = __builtin_amdgcn_readfirstlane((int32_t)(A.rd_off[r + 1] - q.q0));
+    q.vs = __builtin_amdgcn_readfirstlane(A.v_start[r]);
+    q.ve = __builtin_amdgcn_readfirstlane(A.v_end ? A.v_end[r] : A.end_vertex);
+    q.j0 = __builtin_amdgcn_readfirstlane(A.v_off ? A.v_off[r] : 0);
+    q.j1 = __builtin_amdgcn_readfirstlane(A.v_off_hi ? A.v_off_hi[r] : q.j0);
+    q.ilo = max(0, q.qlen - A.end_free);
+    q.wfree = A.walk_free != 0;
+    bind_q(q, A, arena);
+    q.track = MODE >= 1;   // the launch picks MODE >= 1 when pruning or dumping
+    q.mask = 0;
+    q.gen = 0;
+    return q;
+}
+// List j (0 or 1) of an arena: entry words, W, t, and the crossing diagonals'
+// labels (9 words per entry of list_cap entries).
+__device__ __forceinline__ Lists list_of(const KArgs& A, char* arena, int j) {
+    const int64_t lcap = A.list_cap;
+    int32_t* p = reinterpret_cast<int32_t*>(arena + A.o_lists) + (int64_t)j * 9 * lcap;
+    Lists x;
+    x.e = reinterpret_cast<int4*>(p);
+    x.w = p + 4 * lcap; x.t = p + 5 * lcap; x.l = p + 6 * lcap;
+    x.b = reinterpret_cast<int64_t*>(p + 7 * lcap);
+    return x;
+}
 
 template <class SH>
 __device__ __forceinline__ int32_t trace_push_from(const Q& q, SH& S, int32_t v, int32_t tprev, ull probe);
@@ -578,63 +667,535 @@ __device__ __forceinline__ void entry_features(float* f, int32_t s, int32_t i, i
     f[7] = log1pf((float)(qlen - i));
 }
 
+// ---------------------------------------------------------------------------
+// Narrow wavefronts: scores whose lists have at most 64 entries are run by one
+// wave on lists in LDS, with no barrier and one memory round trip per score
+// (records, windows and out-edge records together) where the wide path takes
+// about eight (list, labels, records, stores drained before each barrier,
+// list again for the merge and the pruning).  Pruned runs and short reads
+// stay here: a score of Algorithm 4 on the 1 Mb DAG has 5 entries, and its
+// wide cost is round trips and about 1,500 instructions per wave, whatever
+// the number of lanes at work.  Each lane takes one output diagonal (three
+// slots of 21 source entries per step) instead of one source with three
+// outputs, so the windows, records and extension are written once.
+// Bound now by the round trip and by issue (16 waves per CU): 2.2 us a score
+// alone, 3.1 us with 10 waves on the CU, against 4.6 and 7.7 us on the wide
+// path.  20,000 reads of 10 kb on the 1 Mb DAG, Algorithm 4 (64 lanes): 15.9 ->
+// 6.5 ms; 8,009 reads on the 10 Mb graph, learned: 92.3 -> 57.8 ms.
+// Entered at 48 entries or fewer: from 49 on the next list usually exceeds 64
+// and the score would be started here only to be handed over.
+// ---------------------------------------------------------------------------
+constexpr int NARROW_IN = 48;   // lists entering the narrow path; it leaves above Narrow::N
+// how the narrow path left
+constexpr int NR_WIDE = 0;      // (not run)
+constexpr int NR_ROUNDS = 1;    // score nr_s outgrew it: nr_n entries in list 0, S.ncand candidates left to claim
+constexpr int NR_END = 2;       // the query is done, status nr_n
+constexpr int NR_FLAGS = 3;     // capacity exceeded, flags nr_n
+
+__device__ __forceinline__ int lanes_below(ull m) {   // set bits of m below this lane
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+__device__ __forceinline__ int64_t readlane64(int64_t x, int l) {
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)(uint64_t)x, l);
+    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)((uint64_t)x >> 32), l);
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+// LDS written by some lanes of the wave is read by others: the DS operations
+// of a wave execute in order, so only the compiler has to keep the order.
+__device__ __forceinline__ void wave_lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
+// Continues the exact-match runs of the lanes with `more` (at query base qp,
+// label base sp, at most rem bases): the whole wave compares one lane's run,
+// 2,048 bases per memory round trip (a run between two errors of an accurate
+// read is hundreds of bases; one lane alone compares 128 per round trip).
+__device__ __forceinline__ int32_t wave_extend(const KArgs& A, const Q& q, bool more, int64_t qp, int64_t sp,
+                                               int32_t rem, uint32_t& chunks) {
+    ull need = __ballot(more);
+    const int lane = __lane_id();
+    int32_t ext = 0;
+    while (need) {
+        const int l = __builtin_ctzll(need);
+        need &= need - 1;
+        const int64_t uq = readlane64(qp, l), us = readlane64(sp, l);
+        const int32_t ur = __builtin_amdgcn_readlane(rem, l);
+        int32_t e = 0;
+        uint32_t w = 0;
+        for (;;) {
+            const int32_t off = e + 32 * lane;
+            const bool in = off < ur;
+            const int32_t o = in ? off : 0;
+            const ull x = win32(q.rd, uq + o) ^ win32(A.seg, us + o);
+            const int32_t rl = min(32, ur - off);
+            const int32_t m = min(x ? (int32_t)(__clzll((long long)x) >> 1) : 32, rl);
+            const ull bad = __ballot(in && m < rl);
+            if (bad) {
+                const int f = __builtin_ctzll(bad);
+                e += 32 * f + __builtin_amdgcn_readlane(m, f);
+                w += f + 1;
+                break;
+            }
+            const int32_t g = min(ur - e, 2048);
+            e += g;
+            w += (uint32_t)(g + 31) >> 5;
+            if (e >= ur) break;
+        }
+        if (lane == l) { ext = e; chunks += w; }
+    }
+    return ext;
+}
+
+// Runs scores from S.nr_s on as long as the lists stay narrow; called by the
+// 64 lanes of wave 0.  List nr_list (nr_n entries, read through the merge's
+// bitmap when nr_vmx) is the source of score s > 0, or holds the start
+// entries (s = 0).  What is left for the wide path goes to list 0.  A
+// function of its own: inlined, its scalars and the wide loop's do not fit
+// the scalar registers together and the wide loop spills vector registers.
+template <int BLOCK, int MODE>
+__device__ __attribute__((noinline)) void narrow_scores(int64_t karg) {
+    using SH = Shared<BLOCK, MODE>;
+    SH& S = lds<BLOCK, MODE>();
+    const KArgs& A = *(const KArgs*)(KernArg)uniform64(karg);
+    char* const arena = (char*)uniform64(S.nr_arena);
+    Q q = make_q<MODE>(A, arena, __builtin_amdgcn_readfirstlane(S.nr_r));
+    q.mask = __builtin_amdgcn_readfirstlane(S.nr_mask);
+    q.gen = __builtin_amdgcn_readfirstlane(S.gen);
+    const int32_t half = (int32_t)((q.mask + 1) >> 1);
+    int32_t s = __builtin_amdgcn_readfirstlane(S.nr_s), n = __builtin_amdgcn_readfirstlane(S.nr_n);
+    const int32_t vmx = __builtin_amdgcn_readfirstlane(S.nr_vmx);
+    const uint32_t* vm_bits = reinterpret_cast<uint32_t*>(S.skeys);
+    const int32_t* vm_pre = reinterpret_cast<int32_t*>(S.skeys) + SH::XS;
+    const Lists L0 = list_of(A, arena, 0), Ls = list_of(A, arena, __builtin_amdgcn_readfirstlane(S.nr_list));
+    int32_t* cu = reinterpret_cast<int32_t*>(arena + A.o_cand);
+    int32_t *ck = cu + A.cand_cap, *cW = cu + 2 * (int64_t)A.cand_cap, *ct = cu + 3 * (int64_t)A.cand_cap;
+    uint32_t chunks = 0;
+    constexpr bool LEARN = MODE >= 2;
+    constexpr int SRC = 21;             // sources per step (three output slots each)
+    Narrow& L = S.nw;
+    const int lane = __lane_id();
+    const int li = lane / 3, lj = lane - 3 * li;
+    const int4* __restrict__ vinfo = A.vinfo;
+    const ull t_in = wall_clock64();
+    ull t_rounds = 0;
+    int64_t work = 0;
+    int32_t adm = 0, cross = 0, dropped = 0, evals = 0;
+    int code = NR_WIDE, val = 0, round = 0;
+    int32_t n1 = 0, ntot = 0, nc = 0;
+    int2 lmax = make_int2(0, 0);
+    // ---- the list from memory
+    {
+        int4 e = make_int4(-1, 0, 0, 0);
+        int32_t w = 0, t = -1, l = 0;
+        int64_t b = 0;
+        if (lane < n) {
+            const int32_t p = vmx ? vm_phys_bm(vm_bits, vm_pre, S.sidx, lane) : lane;
+            e = Ls.e[p];
+            if (q.track) w = Ls.w[p];
+            if (q.tb) t = Ls.t[p];
+            const int4 lab = A.vlab[e.x];
+            l = lab.z;
+            b = lab_base(lab);
+        }
+        wave_lds_order();   // the bitmap (same storage) is read before the lists are written
+        if (s == 0) {
+            L.oe[lane] = e; L.ow[lane] = 0; L.ot[lane] = t; L.ol[lane] = l; L.ob[lane] = b;
+        } else {
+            L.ie[lane + 2] = e; L.iw[lane + 2] = w; L.it[lane + 2] = t; L.il[lane + 2] = l; L.ib[lane + 2] = b;
+        }
+        if (lane < 2) {
+            L.ie[lane] = make_int4(-1, 0, 0, 0);
+            L.ie[lane + 66] = make_int4(-1, 0, 0, 0);
+        }
+        wave_lds_order();
+    }
+    for (;;) {
+        n1 = 0;
+        nc = 0;
+        lmax = make_int2(0, 0);
+        if (s > 0) {
+            if (lane == 0) { S.found = 0; S.iend = -1; S.endkey = ~0ull; }
+            // ========== EXPAND + EXTEND ==========
+            for (int32_t c0 = 0; c0 < n; c0 += SRC) {
+                const bool src = lane < 3 * SRC && c0 + li < n;
+                const int32_t si = min(c0 + li, n - 1) + 2;
+                const int4 em2 = L.ie[si - 2], em1 = L.ie[si - 1], e0 = L.ie[si], ep1 = L.ie[si + 1], ep2 = L.ie[si + 2];
+                const int32_t v = e0.x, k = e0.y;
+                const int32_t Lv = L.il[si];
+                const int64_t sb = L.ib[si];
+                const bool pm1 = em1.x == v && em1.y == k - 1;
+                const bool pm2 = pm1 ? (em2.x == v && em2.y == k - 2) : (em1.x == v && em1.y == k - 2);
+                const bool pp1 = ep1.x == v && ep1.y == k + 1;
+                const int4 ez = pp1 ? ep2 : ep1;
+                const bool pp2 = ez.x == v && ez.y == k + 2;
+                // output diagonal kk; its sources: kk-1 (insertion), kk (mismatch), kk+1 (deletion)
+                const int32_t kk = k - 1 + lj;
+                const bool own = src && (lj == 2 || (!pm1 && (lj == 1 || !pm2)));
+                const bool hasB = lj == 1 || (lj == 2 && pp1);
+                const bool hasC = lj == 0 || (lj == 1 ? pp1 : pp2);
+                const int bi = lj == 1 ? si : si + 1;
+                const int ci = lj == 0 ? si : (lj == 1 || !pp1 ? si + 1 : si + 2);
+                const int32_t oB = lj == 1 ? e0.z : ep1.z, dB = lj == 1 ? e0.w : ep1.w;
+                const int32_t oC = lj == 0 ? e0.z : (lj == 1 ? ep1.z : ez.z);
+                const int32_t W0 = q.track ? L.iw[si] : 0, WB = q.track ? L.iw[bi] : 0, WC = q.track ? L.iw[ci] : 0;
+                const int32_t t0 = q.tb ? L.it[si] : -1, tB = q.tb ? L.it[bi] : -1, tC = q.tb ? L.it[ci] : -1;
+                int32_t bo = -1, bw = -1, bt = -1;
+                if (lj == 2 && k + e0.z < q.qlen) { bo = e0.z; bw = W0; bt = t0; }
+                if (hasB && kk + oB < q.qlen && oB < Lv && (oB + 1 > bo || (oB + 1 == bo && WB + 1 > bw))) {
+                    bo = oB + 1; bw = WB + 1; bt = tB;
+                }
+                if (hasC && oC < Lv && (oC + 1 > bo || (oC + 1 == bo && WC + 1 > bw))) {
+                    bo = oC + 1; bw = WC + 1; bt = tC;
+                }
+                const bool cand = own && bo > (hasB ? oB : -1);
+                const bool chk = cand && !hasB;      // the diagonal's record decides
+                int pg = hasB ? dB : e0.w;
+                if (chk && (kk >> 5) != (k >> 5)) pg = dir_insert(q.dir, q.mask, dkey(v, kk >> 5), &S.dirn);
+                // record, out-edge record and windows in one round of loads
+                const int32_t m = cand ? min(q.qlen - (kk + bo), Lv - bo) : 0;
+                const ull rw = q.pages[chk && pg >= 0 ? pg : 0].R[kk & 31];
+                const int4 vi = vinfo[v];
+                const int64_t qp = q.q0 + (m > 0 ? kk + bo : 0), sp = sb + (m > 0 ? bo : 0);
+                const ull x = win32(q.rd, qp) ^ win32(A.seg, sp);
+                const bool rec = chk && pg >= 0 && rgen(rw) == q.gen;
+                const bool ov = cand && !(rec && bo <= rval(rw));
+                int32_t lx = 0;
+                if (ov && m > 0) {
+                    ++chunks;
+                    lx = min(x ? (int32_t)(__clzll((long long)x) >> 1) : 32, m);
+                }
+                lx += wave_extend(A, q, lx == 32 && m > 32, qp + 32, sp + 32, m - 32, chunks);
+                const ull om = __ballot(ov);
+                const int32_t p = n1 + lanes_below(om);
+                n1 += __popcll(om);
+                int ncr = 0;
+                const int32_t o = bo + lx, W = bw + lx;
+                if (ov) {
+                    if (pg < 0) {
+                        atomicOr(&S.flags, F_GROW);
+                    } else {
+                        ncr = record_entry(q, S, v, kk, o, W, pg, chk && !rec, Lv, o == Lv ? vi.y : 0, lmax);
+                        const int4 e = make_int4(v, kk, o, pg);
+                        if (p < Narrow::N) {
+                            L.oe[p] = e; L.ol[p] = Lv; L.ob[p] = sb;
+                            if (q.track) L.ow[p] = W;
+                            if (q.tb) L.ot[p] = bt;
+                        } else {   // more than a narrow list: it goes on in the wide path
+                            L0.e[p] = e;
+                            if (q.track) L0.w[p] = W;
+                            if (q.tb) L0.t[p] = bt;
+                            if ((p & (SAMP - 1)) == 0) S.samp[p / SAMP] = skey(v, kk);
+                        }
+                    }
+                }
+                if (__ballot(ncr != 0)) {
+                    int tot;
+                    const int c = nc + wave_excl_scan(ncr, tot);
+                    nc += __builtin_amdgcn_readfirstlane(tot);
+                    for (int j = 0; j < ncr; ++j) {
+                        const int32_t u = j == 0 ? vi.z : (j == 1 ? vi.w : A.out_dst[vi.x + j]);
+                        if (c + j < Narrow::C) {
+                            L.cu[c + j] = u; L.ck[c + j] = kk + Lv; L.ct[c + j] = bt;
+                            if (q.track) L.cw[c + j] = W;
+                        } else if (c + j < A.cand_cap) {
+                            cu[c + j] = u; ck[c + j] = kk + Lv; cW[c + j] = W; ct[c + j] = bt;
+                        } else {
+                            atomicOr(&S.flags, F_LIST);
+                        }
+                    }
+                }
+            }
+            adm += n1;
+        }
+        wave_lds_order();
+        // ========== crossings, in rounds ==========
+        int32_t xlo = n1, xhi = s == 0 ? n : n1;
+        const int32_t preset = s == 0 ? n : 0;   // the start entries have their trace records
+        bool timed = false;
+        ull tr = 0;
+        for (round = 0;; ++round) {
+            if (xlo < xhi) {
+                // extend the entries created by the previous round (or the starts)
+                const int32_t idx = xlo + lane;
+                const bool act = idx < xhi;
+                const int32_t ix = act ? idx : xlo;
+                const int4 e = L.oe[ix];
+                const int32_t Lv = L.ol[ix];
+                const int64_t sb = L.ob[ix];
+                const int32_t W0 = q.track ? L.ow[ix] : 0;
+                int32_t t = q.tb ? L.ot[ix] : -1;
+                const int32_t v = e.x, k = e.y, o0 = e.z;
+                const bool push = q.tb && act && idx >= preset;
+                const int32_t m = act ? min(q.qlen - (k + o0), Lv - o0) : 0;
+                const int4 vi = vinfo[v];
+                const ull probe = __hip_atomic_load(&q.mkey[push ? (dhash(dkey(v, t)) & q.mask) : 0], __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_AGENT);
+                const int64_t qp = q.q0 + (m > 0 ? k + o0 : 0), sp = sb + (m > 0 ? o0 : 0);
+                const ull x = win32(q.rd, qp) ^ win32(A.seg, sp);
+                int32_t lx = 0;
+                if (m > 0) {
+                    ++chunks;
+                    lx = min(x ? (int32_t)(__clzll((long long)x) >> 1) : 32, m);
+                }
+                lx += wave_extend(A, q, lx == 32 && m > 32, qp + 32, sp + 32, m - 32, chunks);
+                const int32_t o = o0 + lx, W = W0 + lx;
+                int ncr = 0;
+                if (act) {
+                    ncr = record_entry(q, S, v, k, o, W, e.w, true, Lv, o == Lv ? vi.y : 0, lmax);
+                    if (push) t = trace_push_from(q, S, v, t, probe);
+                    L.oe[idx].z = o;
+                    if (q.track) L.ow[idx] = W;
+                    if (q.tb) L.ot[idx] = t;
+                }
+                if (__ballot(ncr != 0)) {
+                    int tot;
+                    const int c = nc + wave_excl_scan(ncr, tot);
+                    nc += __builtin_amdgcn_readfirstlane(tot);
+                    for (int j = 0; j < ncr; ++j) {
+                        const int32_t u = j == 0 ? vi.z : (j == 1 ? vi.w : A.out_dst[vi.x + j]);
+                        if (c + j < Narrow::C) {
+                            L.cu[c + j] = u; L.ck[c + j] = k + Lv; L.ct[c + j] = t;
+                            if (q.track) L.cw[c + j] = W;
+                        } else if (c + j < A.cand_cap) {
+                            cu[c + j] = u; ck[c + j] = k + Lv; cW[c + j] = W; ct[c + j] = t;
+                        } else {
+                            atomicOr(&S.flags, F_LIST);
+                        }
+                    }
+                }
+                wave_lds_order();
+            }
+            const int f1 = __builtin_amdgcn_readfirstlane(S.flags | ((S.dirn > half || S.mn > half) ? F_GROW : 0));
+            if (f1) { code = NR_FLAGS; val = f1; break; }
+            if (xhi + nc > Narrow::N) { code = NR_ROUNDS; break; }   // may outgrow the narrow lists
+            if (nc == 0) break;
+            if (!timed) { timed = true; tr = wall_clock64(); }
+            // claim never-seen diagonals.  One wave holds every candidate, so equal
+            // ones meet here and no atomic is needed: the lowest lane takes the
+            // diagonal, with the largest W among them, and the extension of the
+            // next pass writes its record.
+            const bool act = lane < nc;
+            const int ci = act ? lane : 0;
+            const int32_t u = L.cu[ci], kc = L.ck[ci], tc = q.tb ? L.ct[ci] : -1;
+            int32_t wc = q.track ? L.cw[ci] : 0;
+            const ull key = dkey(u, kc >> 5);
+            const uint32_t h = dhash(key) & q.mask;
+            const ull dprobe = __hip_atomic_load(&q.dir[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const int4 lab = A.vlab[u];
+            const ull wh = __hip_atomic_load(&q.pages[h].R[kc & 31], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            int ds = -1;
+            bool fresh = false;
+            if (act) {
+                ds = dir_settle(q.dir, q.mask, key, h, dprobe, &S.dirn);
+                if (ds < 0) {
+                    atomicOr(&S.flags, F_GROW);
+                } else {
+                    const ull w = ds == (int)h ? wh : __hip_atomic_load(&q.pages[ds].R[kc & 31], __ATOMIC_RELAXED,
+                                                                        __HIP_MEMORY_SCOPE_AGENT);
+                    fresh = rgen(w) != q.gen;
+                }
+            }
+            ull todo = __ballot(fresh), lead = 0;
+            while (todo) {
+                const int f = __builtin_ctzll(todo);
+                const ull same = __ballot(fresh && u == __builtin_amdgcn_readlane(u, f) &&
+                                          kc == __builtin_amdgcn_readlane(kc, f));
+                lead |= 1ull << f;
+                todo &= ~same;
+                if (q.track && (same & (same - 1))) {
+                    int32_t wm = (same >> lane) & 1 ? wc : 0;
+                    for (int j = 32; j >= 1; j >>= 1) wm = max(wm, __shfl_xor(wm, j, 64));
+                    if (lane == f) wc = wm;
+                }
+            }
+            if ((lead >> lane) & 1) {
+                const int32_t p = xhi + lanes_below(lead);
+                L.oe[p] = make_int4(u, kc, 0, ds);
+                L.ol[p] = lab.z; L.ob[p] = lab_base(lab);
+                if (q.track) L.ow[p] = wc;
+                if (q.tb) L.ot[p] = tc;
+            }
+            wave_lds_order();
+            const int f2 = __builtin_amdgcn_readfirstlane(S.flags | (S.dirn > half ? F_GROW : 0));
+            if (f2) { code = NR_FLAGS; val = f2; break; }
+            xlo = xhi;
+            xhi += __popcll(lead);
+            cross += xhi - xlo;
+            nc = 0;
+        }
+        if (timed) t_rounds += wall_clock64() - tr;
+        ntot = xhi;
+        if (code != NR_WIDE) break;
+        work += ntot;
+        int32_t amax = 0, imax = 0;
+        if (q.track) {
+            for (int m = 32; m >= 1; m >>= 1) {
+                lmax.x = max(lmax.x, __shfl_xor(lmax.x, m, 64));
+                lmax.y = max(lmax.y, __shfl_xor(lmax.y, m, 64));
+            }
+            amax = __builtin_amdgcn_readfirstlane(lmax.x);
+            imax = __builtin_amdgcn_readfirstlane(lmax.y);
+        }
+        // this lane's entry of the score's list: outputs first, then crossing entries
+        const bool ent = lane < ntot;
+        const int li2 = ent ? lane : 0;
+        const int4 e = L.oe[li2];
+        const int32_t eW = q.track ? L.ow[li2] : 0, eT = q.tb ? L.ot[li2] : -1, eL = L.ol[li2];
+        const int64_t eB = L.ob[li2];
+        // ========== end test ==========
+        if (__builtin_amdgcn_readfirstlane(S.found)) {
+            int32_t iend = q.qlen;
+            if (q.ilo < q.qlen) {
+                iend = __builtin_amdgcn_readfirstlane(S.iend);
+                if (ent && e.y + e.z == iend && ends_walk(q, e.x, e.z, eL))
+                    atomicMin(&S.endkey, ((ull)(uint32_t)e.x << 32) | (uint32_t)e.z);
+                wave_lds_order();
+            }
+            if (q.tb) {
+                const int32_t ev = (int32_t)(S.endkey >> 32), eo = (int32_t)(S.endkey & 0xffffffffull);
+                if (lane == 0) S.tend = -1;
+                wave_lds_order();
+                if (ent && e.x == ev && e.z == eo && e.y + eo == iend) S.tend = eT;
+            }
+            code = NR_END; val = GWFA_ST_OK;
+            break;
+        }
+        if (A.max_score >= 0 && s >= A.max_score) { code = NR_END; val = GWFA_ST_MAX_SCORE; break; }
+        if (ntot == 0) { code = NR_END; val = q.ve >= 0 ? GWFA_ST_UNREACHABLE : GWFA_ST_MAX_SCORE; break; }
+        if (q.ve < 0 && s > q.qlen + 1) { code = NR_END; val = GWFA_ST_MAX_SCORE; break; }
+        // ========== merge of the crossing entries, and Algorithm 4 ==========
+        {
+            bool keep = ent;
+            if (MODE == 1 && A.prune == GWFA_PRUNE_HEURISTIC && amax > A.a_diff) {
+                keep = ent && amax - (e.y + e.z + eW) < A.a_diff;
+                const ull dm = __ballot(ent && !keep);
+                if (ent && !keep) q.pages[e.w].R[e.y & 31] = mkR(q.gen, e.z);   // the record stays
+                dropped += __popcll(dm);
+            }
+            const ull km = __ballot(keep);
+            const ull lowm = n1 >= 64 ? ~0ull : (1ull << n1) - 1;
+            const ull mo = km & lowm;
+            ull mc = km & ~lowm;
+            const ull key = skey(e.x, e.y);
+            int32_t pos = lanes_below(mo);        // kept outputs before this one (crossing entries: set below)
+            if (mc) {
+                const bool crossing = lane >= n1;
+                int32_t cnt = 0, outs = 0;
+                while (mc) {
+                    const int f = __builtin_ctzll(mc);
+                    mc &= mc - 1;
+                    const ull kf = (ull)readlane64((int64_t)key, f);
+                    cnt += kf < key ? 1 : 0;
+                    const int32_t b = __popcll(__ballot(key < kf) & mo);
+                    if (lane == f) outs = b;
+                }
+                pos = (crossing ? outs : pos) + cnt;
+            }
+            n = __popcll(km);
+            wave_lds_order();
+            if (keep) {
+                L.ie[pos + 2] = e; L.il[pos + 2] = eL; L.ib[pos + 2] = eB;
+                if (q.track) L.iw[pos + 2] = eW;
+                if (q.tb) L.it[pos + 2] = eT;
+            }
+            if (lane < 2) L.ie[n + 2 + lane] = make_int4(-1, 0, 0, 0);
+            wave_lds_order();
+        }
+        // ========== learned keep/drop ==========
+        if (LEARN && A.prune == GWFA_PRUNE_LEARNED && n >= A.mlp_gate && (s % A.mlp_period) == 0) {
+            const bool live = lane < n;
+            const int ix = (live ? lane : 0) + 2;
+            const int4 c = L.ie[ix];
+            const int32_t cw2 = L.iw[ix], cl = L.il[ix], c_t = q.tb ? L.it[ix] : -1;
+            const int64_t cb = L.ib[ix];
+            const int32_t i = c.y + c.z;
+            float f[8];
+            entry_features(f, s, i, cw2, c.z, cl, vinfo[c.x].y, amax, imax, q.qlen);
+            const float z = mlp_logit_wave(f, S.mscale, S.mlpw);
+            const bool keep = live && (z >= A.keep_threshold || i + cw2 == amax);   // the furthest diagonal stays
+            if (live && !keep) q.pages[c.w].R[c.y & 31] = mkR(q.gen, c.z);
+            const ull km = __ballot(keep);
+            evals += n;
+            dropped += n - __popcll(km);
+            n = __popcll(km);
+            const int32_t pos = lanes_below(km);
+            wave_lds_order();
+            if (keep) {
+                L.ie[pos + 2] = c; L.iw[pos + 2] = cw2; L.il[pos + 2] = cl; L.ib[pos + 2] = cb;
+                if (q.tb) L.it[pos + 2] = c_t;
+            }
+            if (lane < 2) L.ie[n + 2 + lane] = make_int4(-1, 0, 0, 0);
+            wave_lds_order();
+        }
+        ++s;
+    }
+    // ========== what is left for the wide path ==========
+    if (code == NR_ROUNDS) {
+        if (q.track) {
+            for (int m = 32; m >= 1; m >>= 1) {
+                lmax.x = max(lmax.x, __shfl_xor(lmax.x, m, 64));
+                lmax.y = max(lmax.y, __shfl_xor(lmax.y, m, 64));
+            }
+        }
+        if (lane < min(ntot, Narrow::N)) {
+            const int4 e = L.oe[lane];
+            L0.e[lane] = e;
+            if (q.track) L0.w[lane] = L.ow[lane];
+            if (q.tb) L0.t[lane] = L.ot[lane];
+            if (lane < n1 && (lane & (SAMP - 1)) == 0) S.samp[lane / SAMP] = skey(e.x, e.y);
+        }
+        // the candidates to where the wide path looks for them
+        int32_t u2[2], k2[2], w2[2], t2[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int c = lane + 64 * j;
+            u2[j] = L.cu[c]; k2[j] = L.ck[c]; w2[j] = q.track ? L.cw[c] : 0; t2[j] = L.ct[c];
+        }
+        wave_lds_order();
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int c = lane + 64 * j;
+            if (c < nc) put_cand(S, A, cu, ck, cW, ct, c, u2[j], k2[j], w2[j], t2[j]);
+        }
+        for (int c = Narrow::C + lane; c < min(nc, (int)SH::CS); c += 64) {
+            S.csu[c] = cu[c]; S.csk[c] = ck[c]; S.cst[c] = ct[c];
+        }
+        if (lane == 0) {
+            S.ncand = nc; S.n_out = ntot; S.nr_n1 = n1; S.nr_round = round;
+            S.amax = lmax.x; S.imax = lmax.y;
+        }
+        val = ntot;
+    }
+    for (int j = 32; j >= 1; j >>= 1) chunks += __shfl_xor(chunks, j, 64);
+    if (lane == 0) {
+        S.chunks += (ull)chunks;
+        S.nr_code = code; S.nr_s = s; S.nr_n = val; S.nr_work = work;
+        S.adm += (ull)adm; S.cross += (ull)cross; S.dropped += dropped;
+        if (LEARN) S.mlp += (ull)evals;
+        const ull t_out = wall_clock64();
+        S.tick[0] += t_out - t_in - t_rounds;
+        S.tick[1] += t_rounds;
+    }
+}
+
 // MODE 0: exact; 1: walk lengths tracked (Algorithm 4); 2: trace dump (and
 // the learned keep/drop); 3: learned keep/drop without the dump.  Each mode
 // is its own instantiation so that the registers of what it does not use
 // are not allocated.
 template <int BLOCK, int MODE>
-__device__ void align_read(const KArgs& A, char* __restrict__ arena, int r, Shared<BLOCK, MODE>& S) {
+__device__ void align_read(const KArgs& Ak, char* __restrict__ arena, int r, Shared<BLOCK, MODE>& S) {
     using SH = Shared<BLOCK, MODE>;
     constexpr bool LEARN = MODE >= 2;
     constexpr bool DUMP = MODE == 2;
+    constexpr bool NARROW = MODE == 1 || MODE == 3;   // pruned runs: small wavefronts throughout
     const int tid = threadIdx.x;
-    Q q;
-    q.rd = A.rd;
-    // The query's parameters are the same in every lane: readfirstlane keeps
-    // them in scalar registers (and the test below a branch of the whole wave).
-    q.q0 = uniform64(A.rd_off[r]);
-    q.qlen = __builtin_amdgcn_readfirstlane((int32_t)(A.rd_off[r + 1] - q.q0));
-    q.vs = __builtin_amdgcn_readfirstlane(A.v_start[r]);
-    q.ve = __builtin_amdgcn_readfirstlane(A.v_end ? A.v_end[r] : A.end_vertex);
-    q.j0 = __builtin_amdgcn_readfirstlane(A.v_off ? A.v_off[r] : 0);
-    q.j1 = __builtin_amdgcn_readfirstlane(A.v_off_hi ? A.v_off_hi[r] : q.j0);
-    q.ilo = max(0, q.qlen - A.end_free);
-    q.wfree = A.walk_free != 0;
-    gwfa_result* out = A.res + r;
+    // arguments: see fresh_args; the exact instantiations have room for them
+    auto args = [&]() -> const KArgs& { return NARROW ? fresh_args() : Ak; };
     const int64_t t_begin = (int64_t)wall_clock64();
-    const int64_t* __restrict__ seg_off = A.seg_off;
     // Every query here passed the screen pass (k_screen): its start vertex,
     // start window and end vertex are in range.
-    const int32_t* __restrict__ out_dst = A.out_dst;
-    const int4* __restrict__ vinfo = A.vinfo;
-    q.dir = reinterpret_cast<ull*>(arena + A.o_dir);
-    q.pages = reinterpret_cast<Page*>(arena + A.o_pages);
-    q.mkey = reinterpret_cast<ull*>(arena + A.o_mkey);
-    q.Tv = reinterpret_cast<int32_t*>(arena + A.o_tv);
-    q.Tt = reinterpret_cast<int32_t*>(arena + A.o_tt);
-    q.tb = A.traceback != 0;
-    q.track = MODE >= 1;   // the launch picks MODE >= 1 when pruning or dumping
-    uint32_t* hdr = reinterpret_cast<uint32_t*>(arena + A.o_hdr);
-    int32_t* const lbase = reinterpret_cast<int32_t*>(arena + A.o_lists);
-    const int64_t lcap = A.list_cap;
-    // list j (0 or 1): entry words, W, t, and the crossing diagonals' labels
-    // (9 words per entry of list_cap entries)
-    auto LL = [&](int j) -> Lists {
-        int32_t* p = lbase + (int64_t)j * 9 * lcap;
-        Lists x;
-        x.e = reinterpret_cast<int4*>(p);
-        x.w = p + 4 * lcap; x.t = p + 5 * lcap; x.l = p + 6 * lcap;
-        x.b = reinterpret_cast<int64_t*>(p + 7 * lcap);
-        return x;
-    };
-    int32_t* cbase = reinterpret_cast<int32_t*>(arena + A.o_cand);
-    const int64_t cc = A.cand_cap;
-    int32_t *cu = cbase, *ck = cbase + cc, *cW = cbase + 2 * cc, *ct = cbase + 3 * cc;
-    ull* gkeys = reinterpret_cast<ull*>(arena + A.o_sort);
-    int32_t* gidx = reinterpret_cast<int32_t*>(gkeys + A.sort_cap);
-
+    Q q = make_q<MODE>(args(), arena, r);
     int cap_log2 = 8;
     {
+        const KArgs& A = args();
         const int64_t want = ((int64_t)q.qlen / 32 + 1) * A.dir_factor;
         while (cap_log2 < A.dir_log2_max && ((int64_t)1 << cap_log2) < want) ++cap_log2;
     }
@@ -651,12 +1212,16 @@ __device__ void align_read(const KArgs& A, char* __restrict__ arena, int r, Shar
     for (;;) {   // attempts with a growing directory
         const uint32_t mask = (1u << cap_log2) - 1;
         const int32_t half = (int32_t)((mask + 1) >> 1);
+        const KArgs& A0 = args();
+        const int32_t dir_log2_max = A0.dir_log2_max;
+        bind_q(q, A0, arena);
         q.mask = mask;
         for (uint32_t i = tid; i <= mask; i += BLOCK) {
             q.dir[i] = 0;
             if (q.tb) q.mkey[i] = 0;
         }
         if (tid == 0) {
+            uint32_t* hdr = reinterpret_cast<uint32_t*>(arena + A0.o_hdr);
             const uint32_t g = hdr[0] + 1;
             hdr[0] = g;
             S.gen = g;
@@ -672,10 +1237,10 @@ __device__ void align_read(const KArgs& A, char* __restrict__ arena, int r, Shar
         // (vs, -1 - j), so the traced walk tells where it started.
         {
             const int32_t nst = q.j1 - q.j0 + 1;
-            const Lists L0 = LL(0);
-            const int64_t sb0 = seg_off[q.vs];
-            const int32_t lv0 = (int32_t)(seg_off[q.vs + 1] - sb0);
-            for (int32_t t = tid; t < min(nst, (int32_t)A.list_cap); t += BLOCK) {
+            const Lists L0 = list_of(A0, arena, 0);
+            const int64_t sb0 = A0.seg_off[q.vs];
+            const int32_t lv0 = (int32_t)(A0.seg_off[q.vs + 1] - sb0);
+            for (int32_t t = tid; t < min(nst, (int32_t)A0.list_cap); t += BLOCK) {
                 const int32_t j = q.j1 - t;
                 const int ds = dir_insert(q.dir, mask, dkey(q.vs, (-j) >> 5), &S.dirn);
                 if (ds < 0) atomicOr(&S.flags, F_GROW);
@@ -685,8 +1250,8 @@ __device__ void align_read(const KArgs& A, char* __restrict__ arena, int r, Shar
                 L0.b[t] = sb0; L0.l[t] = lv0;
             }
             if (tid == 0) {
-                S.n_out = min(nst, (int32_t)A.list_cap);
-                if (nst > A.list_cap) atomicOr(&S.flags, F_LIST);
+                S.n_out = min(nst, (int32_t)A0.list_cap);
+                if (nst > A0.list_cap) atomicOr(&S.flags, F_LIST);
             }
         }
         __syncthreads();
@@ -704,12 +1269,51 @@ __device__ void align_read(const KArgs& A, char* __restrict__ arena, int r, Shar
         chunks = 0;
         for (;; ++s) {
             if (f0) break;
+            // ========== narrow wavefronts: wave 0 alone, on LDS lists ==========
+            bool outgrown = false;    // the narrow path left this score to the crossing rounds below
+            if (NARROW && (s > 0 ? n_cur : n_start) <= NARROW_IN) {
+                if (tid == 0) {
+                    S.nr_s = s; S.nr_n = s > 0 ? n_cur : n_start; S.nr_vmx = vmx; S.nr_list = s > 0 ? cur : 0;
+                    S.nr_r = r; S.nr_mask = mask; S.nr_arena = (int64_t)(uintptr_t)arena;
+                }
+                __syncthreads();      // the list is complete before wave 0 reads it
+                if (tid < 64) narrow_scores<BLOCK, MODE>((int64_t)(uintptr_t)kernarg());
+                __syncthreads();
+                const int nr = __builtin_amdgcn_readfirstlane(S.nr_code);
+                const int32_t val = __builtin_amdgcn_readfirstlane(S.nr_n);
+                s = __builtin_amdgcn_readfirstlane(S.nr_s);
+                work += uniform64(S.nr_work);
+                vmx = 0;
+                if (nr == NR_FLAGS) { rflags = val; break; }
+                if (nr == NR_END) {
+                    status = val;
+                    if (val == GWFA_ST_OK && q.ilo < q.qlen) clip = q.qlen - __builtin_amdgcn_readfirstlane(S.iend);
+                    break;
+                }
+                outgrown = true;
+                cur = 1;              // list 0 is under construction
+                n_cur = val;
+            }
+            const KArgs& A = args();
+            bind_q(q, A, arena);
+            // read here for the loops below: the compiler does not move a load from
+            // these arguments out of a branch
+            const int4* __restrict__ vinfo = A.vinfo;
+            const int4* __restrict__ vlab = A.vlab;
+            const ull* __restrict__ seg = A.seg;
+            const int32_t list_cap = A.list_cap;
+            auto LL = [&](int j) -> Lists { return list_of(A, arena, j); };
+            int32_t* const cu = reinterpret_cast<int32_t*>(arena + A.o_cand);
+            const int64_t cc = A.cand_cap;
+            int32_t *const ck = cu + cc, *const cW = cu + 2 * cc, *const ct = cu + 3 * cc;
             const int nb = 1 - cur;
             const Lists Ld = LL(nb);
             int32_t n1 = 0;           // diagonals produced by the expansion
             int2 lmax = make_int2(0, 0);   // this lane's largest a = i + W~ and i of the score (tracked modes)
             ull tk = wall_clock64();
-            if (s > 0) {
+            if (outgrown) {
+                n1 = __builtin_amdgcn_readfirstlane(S.nr_n1);
+            } else if (s > 0) {
                 if (tid == 0) { S.found = 0; S.iend = -1; S.endkey = ~0ull; S.amax = 0; S.imax = 0; }
                 __syncthreads();
                 // ========== EXPAND (Algorithm 3) + EXTEND of what it admits ==========
@@ -757,7 +1361,7 @@ __device__ void align_read(const KArgs& A, char* __restrict__ arena, int r, Shar
                     // the label of v (its length bounds the candidates, its base places
                     // their windows), requested before the exchange of neighbours,
                     // which hides its latency
-                    const int4 lab = A.vlab[valid ? v : 0];   // unconditional: its wait can move to the first use
+                    const int4 lab = vlab[valid ? v : 0];   // unconditional: its wait can move to the first use
                     // the neighbours at merged positions idx-2 .. idx+2 come from LDS:
                     // every lane stages its entry, threads 0-3 the two positions on
                     // each side of the batch
@@ -858,9 +1462,9 @@ __device__ void align_read(const KArgs& A, char* __restrict__ arena, int r, Shar
                     const ull rw0l = q.pages[(rec0 && pg0 >= 0) ? pg0 : 0].R[(k - 1) & 31];
                     const ull rw2l = q.pages[(rec2 && pg2 >= 0) ? pg2 : 0].R[(k + 1) & 31];
                     const int4 vil = vinfo[valid ? v : 0];
-                    const ull x0l = win32(q.rd, m0 > 0 ? q.q0 + k - 1 + c0 : q.q0) ^ win32(A.seg, m0 > 0 ? sb + c0 : 0);
-                    const ull x1l = win32(q.rd, m1 > 0 ? q.q0 + k + c1 : q.q0) ^ win32(A.seg, m1 > 0 ? sb + c1 : 0);
-                    const ull x2l = win32(q.rd, m2 > 0 ? q.q0 + k + 1 + c2 : q.q0) ^ win32(A.seg, m2 > 0 ? sb + c2 : 0);
+                    const ull x0l = win32(q.rd, m0 > 0 ? q.q0 + k - 1 + c0 : q.q0) ^ win32(seg, m0 > 0 ? sb + c0 : 0);
+                    const ull x1l = win32(q.rd, m1 > 0 ? q.q0 + k + c1 : q.q0) ^ win32(seg, m1 > 0 ? sb + c1 : 0);
+                    const ull x2l = win32(q.rd, m2 > 0 ? q.q0 + k + 1 + c2 : q.q0) ^ win32(seg, m2 > 0 ? sb + c2 : 0);
                     const ull rw0 = (rec0 && pg0 >= 0) ? rw0l : 0ull;
                     const ull rw2 = (rec2 && pg2 >= 0) ? rw2l : 0ull;
                     const int4 vi = valid ? vil : make_int4(0, 0, -1, -1);
@@ -897,7 +1501,7 @@ __device__ void align_read(const KArgs& A, char* __restrict__ arena, int r, Shar
                             const int32_t mj = (j == 0) ? m0 : ((j == 1) ? m1 : m2);
                             if (lj == 32 && mj > 32) {
                                 const int32_t oj = (j == 0) ? oo0 : ((j == 1) ? oo1 : oo2);
-                                const int32_t r = 32 + lcp<false>(q.rd, q.q0 + k - 1 + j + oj + 32, ((q.q0 + q.qlen) >> 5) + 1, A.seg,
+                                const int32_t r = 32 + lcp<false>(q.rd, q.q0 + k - 1 + j + oj + 32, ((q.q0 + q.qlen) >> 5) + 1, seg,
                                                            sb + oj + 32, ((sb + Lv) >> 5) + 1, mj - 32, chunks);
                                 if (j == 0) lx0 = r; else if (j == 1) lx1 = r; else lx2 = r;
                             }
@@ -925,7 +1529,7 @@ __device__ void align_read(const KArgs& A, char* __restrict__ arena, int r, Shar
                             const int32_t p = outbase + pos + slot;
                             ++slot;
                             if (d < 0) d = dir_insert(q.dir, mask, dkey(v, kj >> 5), &S.dirn);
-                            if (p >= A.list_cap) {
+                            if (p >= list_cap) {
                                 atomicOr(&S.flags, F_LIST);
                             } else if (d < 0) {
                                 atomicOr(&S.flags, F_GROW);
@@ -959,16 +1563,17 @@ __device__ void align_read(const KArgs& A, char* __restrict__ arena, int r, Shar
                     }
                     outbase += total;
                 }
-                n1 = min(outbase, A.list_cap);
+                n1 = min(outbase, list_cap);
                 if (adm) atomicAdd(&S.adm, (ull)adm);
                 if (tid == 0) S.n_out = n1;
             }
             if (tid == 0) { const ull t2 = wall_clock64(); S.tick[0] += t2 - tk; tk = t2; }
             // ========== crossings (Algorithm 2, same score, cost 0), in rounds ==========
             int32_t xlo = n1, xhi = (s == 0) ? n_start : n1;
+            if (outgrown) xlo = xhi = n_cur;   // extended already; their candidates are next
             const int32_t preset_hi = (s == 0) ? n_start : 0;   // the start entries have their W and t
             bool restart = false;
-            for (int round = 0;; ++round) {
+            for (int round = outgrown ? __builtin_amdgcn_readfirstlane(S.nr_round) : 0;; ++round) {
                 // (1) extend the diagonals created by the previous round
                 for (int32_t base = xlo; base < xhi; base += BLOCK) {
                     const int32_t idx = base + tid;
@@ -1045,7 +1650,7 @@ __device__ void align_read(const KArgs& A, char* __restrict__ arena, int r, Shar
                         const ull key = dkey(u, kc >> 5);
                         const uint32_t h = dhash(key) & mask;
                         const ull probe = __hip_atomic_load(&q.dir[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        const int4 lab = A.vlab[u];
+                        const int4 lab = vlab[u];
                         const ull wh = __hip_atomic_load(&q.pages[h].R[kc & 31], __ATOMIC_RELAXED,
                                                          __HIP_MEMORY_SCOPE_AGENT);
                         csb = lab_base(lab);
@@ -1071,7 +1676,7 @@ __device__ void align_read(const KArgs& A, char* __restrict__ arena, int r, Shar
                     }
                     const int pos = wave_alloc(claim, &S.n_out);
                     if (claim) {
-                        if (pos < A.list_cap) {
+                        if (pos < list_cap) {
                             Ld.e[pos] = make_int4(u, kc, 0, ds);
                             Ld.l[pos] = cLv; Ld.b[pos] = csb;
                             if (q.track) Ld.w[pos] = wc;
@@ -1123,7 +1728,7 @@ __device__ void align_read(const KArgs& A, char* __restrict__ arena, int r, Shar
                     for (int32_t idx = tid; idx < ntot; idx += BLOCK) {
                         const int4 e = Ld.e[idx];
                         const int32_t v = e.x, o = e.z;
-                        if (e.y + o == iend && ends_walk(q, v, o, A.vlab[v].z))
+                        if (e.y + o == iend && ends_walk(q, v, o, vlab[v].z))
                             atomicMin(&S.endkey, ((ull)(uint32_t)v << 32) | (uint32_t)o);
                     }
                     __syncthreads();
@@ -1220,6 +1825,8 @@ __device__ void align_read(const KArgs& A, char* __restrict__ arena, int r, Shar
                     int N = 1;
                     while (N < m) N <<= 1;
                     if (N > A.sort_cap) { rflags = F_LIST; break; }
+                    ull* const gkeys = reinterpret_cast<ull*>(arena + A.o_sort);
+                    int32_t* const gidx = reinterpret_cast<int32_t*>(gkeys + A.sort_cap);
                     for (int i = tid; i < N; i += BLOCK) {
                         ull key = ~0ull;
                         if (i < m) {
@@ -1298,7 +1905,7 @@ __device__ void align_read(const KArgs& A, char* __restrict__ arena, int r, Shar
                         const int4 e = Ls.e[ph];
                         v = e.x; k = e.y; o = e.z; dp = e.w; W = Ls.w[ph];
                         i = k + o;
-                        const int32_t Lv = A.vlab[v].z;
+                        const int32_t Lv = vlab[v].z;
                         entry_features(f, s, i, W, o, Lv, vinfo[v].y, amax, imax, q.qlen);
                         rec = (DUMP && A.dump) ? 1 : 0;
                         keep = 1;
@@ -1352,8 +1959,8 @@ __device__ void align_read(const KArgs& A, char* __restrict__ arena, int r, Shar
         if (status >= 0 || !(rflags)) break;
         // capacity exceeded: grow the directory if possible, else give up
         __syncthreads();
-        if ((rflags & F_GROW) && !(rflags & F_LIST) && cap_log2 < A.dir_log2_max) {
-            cap_log2 = min(cap_log2 + 2, A.dir_log2_max);
+        if ((rflags & F_GROW) && !(rflags & F_LIST) && cap_log2 < dir_log2_max) {
+            cap_log2 = min(cap_log2 + 2, dir_log2_max);
             continue;
         }
         status = GWFA_ST_ARENA;
@@ -1363,6 +1970,9 @@ __device__ void align_read(const KArgs& A, char* __restrict__ arena, int r, Shar
     __syncthreads();
     // ========== results and walk (Algorithm 6) ==========
     if (tid == 0) {
+        const KArgs& A = args();
+        bind_q(q, A, arena);
+        gwfa_result* const out = A.res + r;
         out->t_begin = t_begin;
         out->t_end = (int64_t)wall_clock64();
         out->status = status;
@@ -1419,7 +2029,7 @@ __device__ void align_read(const KArgs& A, char* __restrict__ arena, int r, Shar
 template <int BLOCK, int MODE>
 __global__ __launch_bounds__(BLOCK, MODE == 2 ? 2 : (BLOCK >= 512 ? (MODE == 0 ? 4 : 1) : (MODE == 3 ? 3 : 4))) void k_align(KArgs A) {
     constexpr bool LEARN = MODE >= 2;
-    __shared__ Shared<BLOCK, MODE> S;
+    Shared<BLOCK, MODE>& S = lds<BLOCK, MODE>();
     char* arena = A.arena + (int64_t)blockIdx.x * A.arena_stride;
     if constexpr (LEARN) {
         if (A.prune == GWFA_PRUNE_LEARNED) {
