@@ -227,8 +227,8 @@ int gwfa_ctx_create(int device, void* hip_stream, gwfa_ctx** out) {
               hipMalloc((void**)&c->d_cursor, sizeof(unsigned long long)) == hipSuccess &&
               hipMalloc((void**)&c->d_retry_count, sizeof(int32_t)) == hipSuccess &&
               hipMalloc((void**)&c->d_valid_n, sizeof(int32_t)) == hipSuccess &&
-              hipMalloc((void**)&c->d_stats, 16 * sizeof(unsigned long long)) == hipSuccess;
-    if (ok) ok = hipMemset(c->d_stats, 0, 16 * sizeof(unsigned long long)) == hipSuccess &&
+              hipMalloc((void**)&c->d_stats, STAT_SLOTS * 16 * sizeof(unsigned long long)) == hipSuccess;
+    if (ok) ok = hipMemset(c->d_stats, 0, STAT_SLOTS * 16 * sizeof(unsigned long long)) == hipSuccess &&
                  hipDeviceSynchronize() == hipSuccess;
     if (!ok) { gwfa_ctx_destroy(c); return GWFA_ERR_NOMEM; }
     set_tiers(c, 16, 1 << 15);
@@ -930,10 +930,13 @@ int gwfa_mlp_logits_dev(gwfa_ctx* ctx, const float* d_feat, int64_t n, int64_t f
 int gwfa_stats(gwfa_ctx* ctx, int64_t* out16, int32_t reset) {
     if (!ctx || !out16) return GWFA_ERR_ARG;
     HIPCHK(ctx, hipSetDevice(ctx->device));
-    unsigned long long h[16];
+    unsigned long long h[STAT_SLOTS * 16];
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     HIPCHK(ctx, hipMemcpy(h, ctx->d_stats, sizeof(h), hipMemcpyDeviceToHost));
-    for (int i = 0; i < 16; ++i) out16[i] = (int64_t)h[i];
+    for (int i = 0; i < 16; ++i) {
+        out16[i] = 0;
+        for (int j = 0; j < STAT_SLOTS; ++j) out16[i] += (int64_t)h[16 * j + i];
+    }
     out16[5] = ctx->rerun_total;
     if (reset) {
         HIPCHK(ctx, hipMemset(ctx->d_stats, 0, sizeof(h)));

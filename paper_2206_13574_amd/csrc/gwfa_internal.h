@@ -5,6 +5,9 @@
 
 #include "gwfa.h"
 
+// Counters are kept on several lines, summed when they are read.
+constexpr int STAT_SLOTS = 64;
+
 struct KArgs {
     // graph (device)
     const unsigned long long* seg;   // packed labels
@@ -31,7 +34,7 @@ struct KArgs {
     int64_t path_cap;
     unsigned long long* path_cursor;
     int32_t* queue;
-    unsigned long long* stats;       // 8 counters or null
+    unsigned long long* stats;       // STAT_SLOTS lines of 16 counters, or null
     int32_t* retry;                  // queries that overflowed (or null)
     int32_t* retry_count;
     // options

