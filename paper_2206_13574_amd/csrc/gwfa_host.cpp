@@ -19,7 +19,15 @@ static_assert(sizeof(gwfa_result) == 64, "gwfa_result layout");
 
 namespace {
 
-constexpr int N_TIERS = 3;
+// Working-memory tiers.  Tier 0 is for pruned runs, whose wavefronts and record
+// sets are small: sized so that every workgroup that fits the GPU has an
+// arena, where the configured tier (1) may have memory for a few hundred.
+// Queries that outgrow a tier are re-run on the next.
+constexpr int N_TIERS = 4;
+constexpr int32_t PRUNED_DIR_LOG2 = 14, PRUNED_LIST_CAP = 4096, PRUNED_DIR_FACTOR = 16;
+// Algorithm 4 keeps diagonals that lag by less than a_diff: with more lag than
+// this the record sets of long reads outgrow tier 0 and would be run twice.
+constexpr int32_t PRUNED_A_DIFF = 1024;
 constexpr int64_t MLP_SCR_SAMPLES = 16384;
 
 struct Tier {
@@ -131,6 +139,13 @@ int ensure_tier(gwfa_ctx* ctx, int ti) {
     layout(t);
     size_t bytes = (size_t)t.stride * (size_t)t.groups;
     hipError_t e = hipMalloc((void**)&t.arena, bytes);
+    if (e != hipSuccess && ti > 0 && ctx->tier[0].arena) {
+        // make room: the pruned runs' arenas come back when they are needed
+        // (hipFree waits for the kernels using them)
+        free_tier(ctx->tier[0]);
+        ctx->epoch++;
+        e = hipMalloc((void**)&t.arena, bytes);
+    }
     if (e != hipSuccess) {
         t.arena = nullptr;
         ctx->err = "arena allocation of " + std::to_string(bytes) + " bytes failed";
@@ -145,13 +160,17 @@ int ensure_tier(gwfa_ctx* ctx, int ti) {
 }
 
 // Share of the device memory free at configuration time that each tier's
-// arenas may take (all three can be allocated at once).
-constexpr double TIER_SHARE[N_TIERS] = {0.60, 0.20, 0.05};
+// arenas may take (all of them can be allocated at once).
+constexpr double TIER_SHARE[N_TIERS] = {0.14, 0.60, 0.20, 0.05};
 
 void set_tiers(gwfa_ctx* ctx, int32_t dir_log2_max, int32_t list_cap) {
     // default: as many persistent workgroups as can be resident at once
-    int per_cu = gwfa_align_blocks_per_cu(ctx->lanes);
+    int per_cu = gwfa_align_blocks_per_cu(ctx->lanes, GWFA_PRUNE_NONE);
     if (per_cu <= 0) per_cu = 4;
+    int pruned_per_cu = std::max(gwfa_align_blocks_per_cu(ctx->lanes, GWFA_PRUNE_HEURISTIC),
+                                 gwfa_align_blocks_per_cu(ctx->lanes, GWFA_PRUNE_LEARNED));
+    if (pruned_per_cu <= 0) pruned_per_cu = per_cu;
+    const int pruned_groups = ctx->groups > 0 ? ctx->groups : ctx->n_cu * pruned_per_cu;
     const int groups = ctx->groups > 0 ? ctx->groups : ctx->n_cu * per_cu;
     // the old arenas go first, so that the free memory the new tiers are
     // sized from includes them
@@ -160,14 +179,19 @@ void set_tiers(gwfa_ctx* ctx, int32_t dir_log2_max, int32_t list_cap) {
     if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || free_b == 0) free_b = (size_t)64 << 30;
     for (int i = 0; i < N_TIERS; ++i) {
         Tier& t = ctx->tier[i];
-        t.dir_log2_max = std::min(dir_log2_max + 2 * i, 24);
-        t.list_cap = (int32_t)std::min<int64_t>((int64_t)list_cap << (2 * i), (int64_t)1 << 26);
+        if (i == 0) {
+            t.dir_log2_max = std::min(dir_log2_max, PRUNED_DIR_LOG2);
+            t.list_cap = std::min(list_cap, PRUNED_LIST_CAP);
+        } else {
+            t.dir_log2_max = std::min(dir_log2_max + 2 * (i - 1), 24);
+            t.list_cap = (int32_t)std::min<int64_t>((int64_t)list_cap << (2 * (i - 1)), (int64_t)1 << 26);
+        }
         t.cand_cap = (int32_t)std::min<int64_t>((int64_t)t.list_cap * 2, (int64_t)1 << 27);
         layout(t);
         // larger tiers keep as many workgroups as their share of memory holds:
         // queries that overflow the first tier still run at full width
         const int64_t fit = (int64_t)(TIER_SHARE[i] * (double)free_b) / t.stride;
-        t.groups = (int)std::max<int64_t>(4, std::min<int64_t>(groups, fit));
+        t.groups = (int)std::max<int64_t>(4, std::min<int64_t>(i == 0 ? pruned_groups : groups, fit));
     }
 }
 
@@ -455,6 +479,13 @@ static int ensure_lists(gwfa_ctx* ctx, int32_t n_reads) {
     return GWFA_OK;
 }
 
+// The tier a call starts on (see N_TIERS; the trace dump takes the configured
+// tier: it prunes nothing unless asked to).
+static int first_tier(const KArgs& A) {
+    if (A.dump) return 1;
+    return A.prune == GWFA_PRUNE_LEARNED || (A.prune == GWFA_PRUNE_HEURISTIC && A.a_diff <= PRUNED_A_DIFF) ? 0 : 1;
+}
+
 // Working memory of tier ti into A; returns the workgroups to launch.
 static int set_tier(gwfa_ctx* ctx, KArgs& A, int ti, const int32_t* order, int32_t n, const int32_t* n_valid,
                     int* groups) {
@@ -465,6 +496,7 @@ static int set_tier(gwfa_ctx* ctx, KArgs& A, int ti, const int32_t* order, int32
     A.retry = (ti + 1 < N_TIERS) ? ctx->d_retry[ti & 1] : nullptr;
     A.arena = t.arena; A.arena_stride = t.stride;
     A.dir_log2_max = t.dir_log2_max; A.list_cap = t.list_cap; A.cand_cap = t.cand_cap; A.sort_cap = t.sort_cap;
+    A.dir_factor = ti == 0 ? std::min(ctx->dir_factor, PRUNED_DIR_FACTOR) : ctx->dir_factor;
     A.o_hdr = t.o_hdr; A.o_dir = t.o_dir; A.o_pages = t.o_pages; A.o_mkey = t.o_mkey;
     A.o_tv = t.o_tv; A.o_tt = t.o_tt; A.o_lists = t.o_lists; A.o_cand = t.o_cand; A.o_sort = t.o_sort;
     *groups = (int)std::min<int64_t>(t.groups, n);
@@ -521,7 +553,7 @@ static int align_dev(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const 
     A.order = d_order;
     A.n_reads = n_reads;
     HIPCHK(ctx, gwfa_launch_screen(A, ctx->d_valid, ctx->d_valid_n, st));
-    return run_tiers(ctx, A, 0, n_reads, false, st);
+    return run_tiers(ctx, A, first_tier(A), n_reads, false, st);
 }
 
 int gwfa_align_batch_dev(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const uint64_t* d_packed,
@@ -593,7 +625,7 @@ int gwfa_align_batch_static_dev(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_re
     t.list_cap = STATIC_LIST_CAP;
     t.cand_cap = 2 * STATIC_LIST_CAP;
     layout(t);
-    int per_cu = gwfa_align_blocks_per_cu(ctx->lanes);
+    int per_cu = gwfa_align_blocks_per_cu(ctx->lanes, opts->prune);
     if (per_cu <= 0) per_cu = 4;
     const int64_t fit = (STATIC_BYTES - o_arenas) / t.stride;
     const int groups = (int)std::min<int64_t>(std::min<int64_t>(fit, (int64_t)ctx->n_cu * per_cu), n_reads);
@@ -656,7 +688,7 @@ int gwfa_plan_create(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const 
     KArgs S0 = p->A;   // the screen pass reads the caller's order
     S0.order = d_order;
     S0.n_reads = n_reads;
-    if (!rc) rc = set_tier(ctx, p->A, 0, ctx->d_valid, n_reads, ctx->d_valid_n, &groups);   // allocates before the capture
+    if (!rc) rc = set_tier(ctx, p->A, first_tier(p->A), ctx->d_valid, n_reads, ctx->d_valid_n, &groups);   // allocates before the capture
     if (rc) { gwfa_plan_destroy(p); return rc; }
     p->epoch = ctx->epoch;   // after any reallocation of the context's lists
     hipError_t e = hipStreamCreateWithFlags(&p->cap, hipStreamNonBlocking);
@@ -697,7 +729,7 @@ int gwfa_plan_finish(gwfa_plan* p, void* hip_stream) {
     hipStream_t st = hip_stream ? (hipStream_t)hip_stream : ctx->stream;
     HIPCHK(ctx, hipSetDevice(ctx->device));
     KArgs A = p->A;
-    return run_tiers(ctx, A, 0, p->n_reads, true, st);
+    return run_tiers(ctx, A, first_tier(A), p->n_reads, true, st);
 }
 
 int gwfa_align_batch(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const uint8_t* reads,

@@ -2041,12 +2041,8 @@ __global__ __launch_bounds__(BLOCK, MODE == 2 ? 2 : (BLOCK >= 512 ? (MODE == 0 ?
     if (threadIdx.x < 16) S.acc[threadIdx.x] = 0;
     // queries to take: those the screen pass listed, or all of `order`
     const int32_t n_q = A.n_valid ? __builtin_amdgcn_readfirstlane(*A.n_valid) : A.n_reads;
-    bool first = true;
     for (;;) {
-        // the first query of a workgroup is its own number, the others follow
-        // from the queue: device atomics on one address take their turns (7 ns)
-        if (threadIdx.x == 0) S.read = first ? (int)blockIdx.x : (int)gridDim.x + atomicAdd(A.queue, 1);
-        first = false;
+        if (threadIdx.x == 0) S.read = atomicAdd(A.queue, 1);
         __syncthreads();
         const int ridx = __builtin_amdgcn_readfirstlane(S.read);
         __syncthreads();
@@ -2212,14 +2208,20 @@ hipError_t gwfa_launch_align(const KArgs& A, int lanes, int groups, hipStream_t 
     return hipGetLastError();
 }
 
-int gwfa_align_blocks_per_cu(int lanes) {
+int gwfa_align_blocks_per_cu(int lanes, int prune) {
     int nb = 0;
     hipError_t e = hipErrorInvalidValue;
+    auto ask = [&](auto* exact, auto* heuristic, auto* learned) {
+        const void* f = prune == GWFA_PRUNE_LEARNED ? (const void*)learned
+                        : (prune != GWFA_PRUNE_NONE ? (const void*)heuristic : (const void*)exact);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, lanes, 0);
+    };
+    using namespace gwfa_dev;
     switch (lanes) {
-    case 64: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gwfa_dev::k_align<64, 0>, 64, 0); break;
-    case 128: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gwfa_dev::k_align<128, 0>, 128, 0); break;
-    case 256: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gwfa_dev::k_align<256, 0>, 256, 0); break;
-    case 512: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gwfa_dev::k_align<512, 0>, 512, 0); break;
+    case 64: ask(k_align<64, 0>, k_align<64, 1>, k_align<64, 3>); break;
+    case 128: ask(k_align<128, 0>, k_align<128, 1>, k_align<128, 3>); break;
+    case 256: ask(k_align<256, 0>, k_align<256, 1>, k_align<256, 3>); break;
+    case 512: ask(k_align<512, 0>, k_align<512, 1>, k_align<512, 3>); break;
     default: break;
     }
     return (e == hipSuccess && nb > 0) ? nb : 0;

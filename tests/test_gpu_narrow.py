@@ -104,3 +104,17 @@ def test_start_windows_around_the_narrow_limits(G, lanes):
     for a_diff in (0, 12, 100000):
         print(f"[gpu-narrow] lanes {lanes}: {len(cases)} start windows, a_diff={a_diff}", flush=True)
         _compare(gw, ctx, cases, a_diff, windows)
+
+
+@pytest.mark.parametrize("a_diff", [40, 1024, 1025])
+def test_pruned_queries_that_outgrow_the_first_tier(G, a_diff):
+    """Pruned runs up to a lag of 1,024 start on small arenas (lists of 4,096
+    entries, also before a score is pruned); a query that outgrows them is run
+    again on the configured ones.  The results do not depend on the tier."""
+    gw, ctx = G
+    ctx.config(lanes=64)
+    rng = np.random.default_rng(8300)
+    cases = [hub_case(rng, 2200, False), hub_case(rng, 5, False)]
+    ctx.stats(reset=True)
+    _compare(gw, ctx, cases, a_diff)
+    assert ctx.stats()["reruns"] > 0
