@@ -57,7 +57,7 @@ void layout(Tier& t) {
     t.o_mkey = o;  o = align_up(o + C * 8, 256);
     t.o_tv = o;    o = align_up(o + C * 4, 256);
     t.o_tt = o;    o = align_up(o + C * 4, 256);
-    t.o_lists = o; o = align_up(o + (int64_t)2 * 9 * t.list_cap * 4, 256);
+    t.o_lists = o; o = align_up(o + 2 * LIST_WORDS * t.list_cap * 4, 256);
     t.o_cand = o;  o = align_up(o + (int64_t)4 * t.cand_cap * 4, 256);
     t.o_sort = o;  o = align_up(o + (int64_t)t.sort_cap * 12, 4096);
     t.stride = o;

@@ -56,6 +56,11 @@ struct KArgs {
     int64_t o_hdr, o_dir, o_pages, o_mkey, o_tv, o_tt, o_lists, o_cand, o_sort;
 };
 
+// 4-byte words of one wavefront list per entry of its capacity (gwfa_kernels.hip,
+// list_of): 4 places of 24 bytes (3 for the main entries, 1 for the crossing
+// entries) and the crossing entries' 12-byte labels
+constexpr int64_t LIST_WORDS = 4 * 6 + 3;
+
 hipError_t gwfa_launch_align(const KArgs& A, int lanes, int groups, hipStream_t st);
 // resident workgroups per compute unit of a pruning mode's alignment kernel (0 if unknown)
 int gwfa_align_blocks_per_cu(int lanes, int prune);

@@ -20,9 +20,10 @@
 // source with the smallest k among k'-1, k', k'+1, and those sources are the
 // source's neighbours in the sorted list, so the expansion reads no table
 // except at the two ends of a run of consecutive diagonals (where the record
-// of a diagonal outside F_s decides).  Outputs come out sorted (ordered block
-// scan) and are extended by the lane that produced them in the same pass.
-// Diagonals created by crossings are sorted (bitonic) and merged in.
+// of a diagonal outside F_s decides).  Each wave expands a part of the list
+// and writes its outputs, in order, into a part of the new one; diagonals
+// created by crossings are ranked and merged in.  Lists of at most 64 entries
+// are run by one wave in LDS.
 //
 // Records of the paper's wavefront set H~ (kept for the life of a query):
 // pages of 32 consecutive diagonals of one vertex, found through an
@@ -57,11 +58,17 @@ constexpr int F_LIST = 2;   // list / candidate capacity exceeded: re-run on a l
 // Crossing entries sorted in LDS (virtual merge) up to this many per
 // workgroup of `block` lanes; larger sets are sorted in the arena.
 constexpr int xs_lds(int block) { return block >= 256 ? 1024 : 4 * block; }
-// The expansion writes the sort key of every SAMP-th entry of the list it
-// builds into LDS (up to NSAMP keys): the merge then finds an entry's place
-// in that list by a search in LDS and one round of at most SAMP-1 loads.
+// Each wave of the expansion writes the sort key of every SAMP-th entry of its
+// part of the list into LDS (nsamp keys for the workgroup): the merge then
+// finds an entry's place in that part by a search in LDS and one round of at
+// most SAMP-1 loads.
 constexpr int SAMP = 8;
 constexpr int nsamp(int block) { return block >= 256 ? 1024 : 256; }
+// A list's storage: its main entries are written by the waves of the
+// workgroup, each into a part of its own, at most three per source entry, so
+// 3 list_cap places hold any list of up to list_cap entries; the crossing
+// entries follow at place 3 list_cap.
+constexpr int MAIN_X = 3;
 // The exact mode stages the crossing rounds' data in LDS: up to xstage(block)
 // diagonals claimed by one round (read back by the next round's extension)
 // and up to twice as many crossing candidates (read back by the claims); the
@@ -263,13 +270,18 @@ __device__ __forceinline__ int read_uniform(const int& x) {
 // page d in one 16-byte word, the walk length W and the trace index t in
 // arrays of their own (each moved only by the modes that use it).  The label
 // length l and base b of v are kept only for the diagonals a crossing round
-// creates (their extension in the next round then needs no lookup); every
-// other reader takes them from the graph's per-vertex label record.
+// creates, by their number among them (their extension in the next round then
+// needs no lookup); every other reader takes them from the graph's per-vertex
+// label record.  Bit 31 of the page word is set when o = |v|, so that the
+// expansion's sources need no label.
 struct Lists {
     int4* e;          // (v, k, o, d)
     int32_t *w, *t, *l;
     int64_t* b;
 };
+constexpr int32_t AT_END = (int32_t)0x80000000;
+__device__ __forceinline__ int32_t page_word(int32_t d, int32_t o, int32_t Lv) { return o == Lv ? d | AT_END : d; }
+__device__ __forceinline__ int32_t page_of(int32_t w) { return w & ~AT_END; }
 // The diagonal (v, k) of entry i (the first 8 bytes of its word).
 __device__ __forceinline__ int2 vk_of(const Lists& L, int32_t i) {
     return *reinterpret_cast<const int2*>(&L.e[i]);
@@ -293,12 +305,25 @@ struct Narrow {
     int32_t cu[C], ck[C], cw[C], ct[C];
 };
 
+// Candidate outputs of the expansion, in list order: (v, k, offset with bit 31
+// set when the diagonal's record has to be checked, page or -1 when it has to
+// be looked up), trace index, walk length.
+template <bool TRACK>
+struct CandRing {
+    static constexpr int N = 128;
+    int4 e[N];
+    int32_t t[N];
+    int32_t w[TRACK ? N : 1];
+};
+
 // Workgroup LDS, sized for the workgroup (merge keys, the staged batch) and
 // the mode (the network's weights only where it runs).
 template <int BLOCK, int MODE>
 struct Shared {
+    using Ring = CandRing<(MODE > 0)>;
     static constexpr int XS = xs_lds(BLOCK);
-    static constexpr int NB = BLOCK + 4;
+    static constexpr int NW = BLOCK / 64;
+    static constexpr int SEGS = nsamp(BLOCK) / NW;   // samples of one part
     static constexpr int XC = MODE == 0 ? xstage(BLOCK) : 0;       // claimed diagonals staged
     static constexpr int CS = MODE == 0 ? 2 * xstage(BLOCK) : 0;   // crossing candidates staged
     int32_t read;
@@ -322,7 +347,11 @@ struct Shared {
     ull tick[4];      // wall-clock ticks per phase (thread 0)
     ull acc[16];      // counters of the queries this workgroup has finished
     int32_t scan[16];
-    ull samp[nsamp(BLOCK)]; // sort keys of list entries 0, SAMP, 2 SAMP, ... written by the expansion
+    ull samp[nsamp(BLOCK)]; // sort keys of entries 0, SAMP, 2 SAMP, ... of each part, written by the expansion
+    // the parts of the list (Parts): first entry, first place, entries, first key
+    int32_t partL[NW], partP[NW], partN[NW];
+    int32_t newN[NW];       // entries of the parts being built
+    ull partK[NW];
     // what the narrow path is called with and what it hands back (narrow_scores)
     int32_t nr_code, nr_s, nr_n, nr_n1, nr_round, nr_vmx, nr_list, nr_r;
     uint32_t nr_mask;
@@ -331,18 +360,18 @@ struct Shared {
     // score runs on one of the two.
     union {
         struct {
-            ull skeys[XS];
-            int32_t sidx[XS];
-            int32_t xcnt[XS];       // merge: main-list entries below each crossing entry
-            // expansion: the entries of one batch of the source list at slots 2 ..
-            // BLOCK+1 plus two neighbours on each side (slots 0, 1, BLOCK+2, BLOCK+3)
-            int32_t nbv[NB], nbk[NB], nbo[NB], nbd[NB], nbw[NB], nbt[NB];
-            // crossing rounds: claimed diagonals (vertex, diagonal, page, label length,
-            // predecessor's trace index, label base) and candidates (target, diagonal,
-            // trace index of the crossing diagonal)
-            int32_t xsv[XC + 1], xsk[XC + 1], xsd[XC + 1], xsl[XC + 1], xst[XC + 1];
-            int64_t xsb[XC + 1];
-            int32_t csu[CS + 1], csk[CS + 1], cst[CS + 1];
+            ull skeys[XS];          // merge: keys of the crossing entries, then the bitmap of their merged positions
+            int32_t sidx[XS];       // crossing entries in merged order
+            int32_t xcnt[XS];       // merge: merged positions, then the bits below each word of the bitmap
+            int32_t csu[CS + 1], csk[CS + 1], cst[CS + 1];   // crossing candidates: target, diagonal, trace index
+            union {
+                Ring ring[NW];      // expansion: each wave's candidates waiting to be extended
+                struct {            // crossing rounds: claimed diagonals (vertex, diagonal, page, label length,
+                                    // predecessor's trace index, label base)
+                    int32_t xsv[XC + 1], xsk[XC + 1], xsd[XC + 1], xsl[XC + 1], xst[XC + 1];
+                    int64_t xsb[XC + 1];
+                };
+            };
         };
         Narrow nw;
     };
@@ -421,16 +450,45 @@ __device__ __forceinline__ Q make_q(const KArgs& A, char* arena, int r) {
     q.gen = 0;
     return q;
 }
-// List j (0 or 1) of an arena: entry words, W, t, and the crossing diagonals'
-// labels (9 words per entry of list_cap entries).
+// List j (0 or 1) of an arena: entry words, W and t (MAIN_X + 1 times list_cap
+// places), the crossing diagonals' labels (list_cap places).
 __device__ __forceinline__ Lists list_of(const KArgs& A, char* arena, int j) {
-    const int64_t lcap = A.list_cap;
-    int32_t* p = reinterpret_cast<int32_t*>(arena + A.o_lists) + (int64_t)j * 9 * lcap;
+    const int64_t lcap = A.list_cap, n = (MAIN_X + 1) * lcap;
+    int32_t* p = reinterpret_cast<int32_t*>(arena + A.o_lists) + (int64_t)j * LIST_WORDS * lcap;
     Lists x;
     x.e = reinterpret_cast<int4*>(p);
-    x.w = p + 4 * lcap; x.t = p + 5 * lcap; x.l = p + 6 * lcap;
-    x.b = reinterpret_cast<int64_t*>(p + 7 * lcap);
+    x.w = p + 4 * n; x.t = p + 5 * n; x.l = p + 6 * n;
+    x.b = reinterpret_cast<int64_t*>(p + 6 * n + lcap);
     return x;
+}
+// Where the main entries of a list are: part w (written by wave w) holds
+// entries L[w] .. L[w+1]-1 at places from P[w].  In scalar registers.
+template <int NW>
+struct Parts {
+    int32_t L[NW], D[NW];   // first entry, place minus entry
+    template <class SH>
+    __device__ __forceinline__ explicit Parts(const SH& S) {
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            L[w] = __builtin_amdgcn_readfirstlane(S.partL[w]);
+            D[w] = __builtin_amdgcn_readfirstlane(S.partP[w]) - L[w];
+        }
+    }
+    __device__ __forceinline__ int32_t place(int32_t i) const {
+        int32_t d = D[0];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) d = i >= L[w] ? D[w] : d;
+        return i + d;
+    }
+};
+// A list in one part, from place 0.
+template <int NW, class SH>
+__device__ __forceinline__ void one_part(SH& S, int32_t n) {
+    if (threadIdx.x < NW) {
+        S.partL[threadIdx.x] = threadIdx.x == 0 ? 0 : n;
+        S.partP[threadIdx.x] = threadIdx.x == 0 ? 0 : n;
+        S.partN[threadIdx.x] = threadIdx.x == 0 ? n : 0;
+    }
 }
 
 template <class SH>
@@ -563,22 +621,14 @@ __device__ void bitonic(ull* keys, int32_t* idx, int n) {
     }
 }
 
-// Number of entries of list L[0, n) whose key is below key.
-__device__ __forceinline__ int32_t lower_bound_list(const Lists& L, int32_t n, ull key) {
-    int32_t lo = 0, hi = n;
-    while (lo < hi) {
-        const int32_t mid = (lo + hi) >> 1;
-        const int2 a = vk_of(L, mid);
-        if (skey(a.x, a.y) < key) lo = mid + 1; else hi = mid;
-    }
-    return lo;
-}
-// The same with the list's sampled keys in LDS (samp[j] = key of entry
-// SAMP*j for j < ns): a search of the samples, then the at most SAMP-1
-// entries between two samples, loaded together.  Beyond the sampled part of
-// the list it falls back to the search in the list.
-__device__ __forceinline__ int32_t lower_bound_sampled(const Lists& L, int32_t n, ull key, const ull* samp,
-                                                       int32_t ns) {
+// Number of entries of part w of the list (partN entries from place partP)
+// whose key is below key: a search of the part's sampled keys in LDS (samp[j]
+// = key of entry SAMP*j), then the at most SAMP-1 entries between two samples,
+// loaded together.  Beyond the sampled entries it searches the list itself.
+template <class SH>
+__device__ __forceinline__ int32_t lower_bound_part(const SH& S, const Lists& L, int32_t place, int32_t n, ull key,
+                                                    const ull* samp) {
+    const int32_t ns = min((int32_t)SH::SEGS, (n + SAMP - 1) / SAMP);
     int32_t lo = 0, hi = ns;                 // samples below key
     while (lo < hi) {
         const int32_t mid = (lo + hi) >> 1;
@@ -586,39 +636,51 @@ __device__ __forceinline__ int32_t lower_bound_sampled(const Lists& L, int32_t n
     }
     if (lo == 0) return 0;                   // entry 0 is not below key
     const int32_t a = SAMP * (lo - 1) + 1;   // entry a-1 is below key
-    if (lo == ns && SAMP * ns < n) {         // past the sampled part
+    if (lo == ns && SAMP * ns < n) {         // past the sampled entries
         int32_t l2 = a, h2 = n;
         while (l2 < h2) {
             const int32_t mid = (l2 + h2) >> 1;
-            const int2 a = vk_of(L, mid);
-            if (skey(a.x, a.y) < key) l2 = mid + 1; else h2 = mid;
+            const int2 x = vk_of(L, place + mid);
+            if (skey(x.x, x.y) < key) l2 = mid + 1; else h2 = mid;
         }
         return l2;
     }
     const int32_t b = min(SAMP * lo, n);     // entry b is not below key (or b = n)
     int32_t c = a;
-    // every lane loads all SAMP-1 keys (indices clamped to the list), so that
+    // every lane loads all SAMP-1 keys (indices clamped to the part), so that
     // the loads go out together
 #pragma unroll
     for (int32_t j = 0; j < SAMP - 1; ++j) {
         const int32_t e = a + j;
-        const int2 x = vk_of(L, min(e, n - 1));
+        const int2 x = vk_of(L, place + min(e, n - 1));
         c += (e < b && skey(x.x, x.y) < key) ? 1 : 0;
     }
     return c;
 }
+// Number of main entries of the list whose key is below key.
+template <class SH>
+__device__ __forceinline__ int32_t lower_bound_list(const SH& S, const Lists& L, ull key) {
+    int w = 0;                               // the last part whose first key is below key
+#pragma unroll
+    for (int j = 1; j < SH::NW; ++j)
+        if (S.partN[j] > 0 && S.partK[j] < key) w = j;
+    const int32_t n = S.partN[w];
+    return n > 0 ? S.partL[w] + lower_bound_part(S, L, S.partP[w], n, key, S.samp + w * SH::SEGS) : S.partL[w];
+}
 
-// Merged view of a list whose first n1 entries are sorted and whose last m
-// entries (crossing diagonals, unsorted in memory) have known merged
-// positions: a bitmap over the merged positions (bit p of word p >> 5 set when
-// position p holds a crossing entry), the number of bits set below each word,
-// and the physical slots of the crossing entries in merged order.  The slot of
-// merged position p takes two independent LDS reads and a count.
-__device__ __forceinline__ int32_t vm_phys_bm(const uint32_t* bm, const int32_t* pre, const int32_t* xidx, int32_t p) {
-    const uint32_t word = bm[p >> 5];
-    const int b = p & 31;
-    const int32_t c = pre[p >> 5] + __popc(word & ((1u << b) - 1u));
-    return ((word >> b) & 1u) ? xidx[c] : p - c;
+// Merged view of a list whose main entries are sorted and whose crossing
+// entries (unsorted in memory) have known merged positions: a bitmap over the
+// merged positions (bit p & 63 of word p >> 6 set when position p holds a
+// crossing entry), the number of bits set below each word, and the crossing
+// entries in merged order.  The place of merged position p takes two
+// independent LDS reads and a count; xb is the place of crossing entry 0.
+template <int NW>
+__device__ __forceinline__ int32_t merged_place(const ull* bm, const int32_t* pre, const int32_t* xidx,
+                                                const Parts<NW>& parts, int32_t xb, int32_t p) {
+    const ull word = bm[p >> 6];
+    const int b = p & 63;
+    const int32_t c = pre[p >> 6] + __popcll(word & ((1ull << b) - 1));
+    return ((word >> b) & 1) ? xb + xidx[c] : parts.place(p - c);
 }
 
 __device__ __forceinline__ int32_t lower_bound_keys(const ull* keys, int32_t n, ull key) {
@@ -706,41 +768,67 @@ __device__ __forceinline__ int64_t readlane64(int64_t x, int l) {
 __device__ __forceinline__ void wave_lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 // Continues the exact-match runs of the lanes with `more` (at query base qp,
-// label base sp, at most rem bases): the whole wave compares one lane's run,
+// label base sp, at most rem bases).  One run is compared by the whole wave,
 // 2,048 bases per memory round trip (a run between two errors of an accurate
-// read is hundreds of bases; one lane alone compares 128 per round trip).
+// read is hundreds of bases; one lane alone compares 128 per round trip);
+// several are taken four at a time, 16 lanes and 512 bases each.
 __device__ __forceinline__ int32_t wave_extend(const KArgs& A, const Q& q, bool more, int64_t qp, int64_t sp,
                                                int32_t rem, uint32_t& chunks) {
     ull need = __ballot(more);
     const int lane = __lane_id();
     int32_t ext = 0;
     while (need) {
-        const int l = __builtin_ctzll(need);
+        const bool one = (need & (need - 1)) == 0;
+        const int width = one ? 64 : 16;            // lanes per run
+        const int sub = one ? lane : lane & 15;
+        int l = __builtin_ctzll(need);               // the run this lane works on
+        bool on = true;
         need &= need - 1;
-        const int64_t uq = readlane64(qp, l), us = readlane64(sp, l);
-        const int32_t ur = __builtin_amdgcn_readlane(rem, l);
+#pragma unroll
+        for (int j = 1; j < 4; ++j) {
+            const bool any = need != 0;
+            const int b = any ? __builtin_ctzll(need) : 0;
+            if (!one && (lane >> 4) == j) { l = b; on = any; }
+            need &= need - 1;
+        }
+        const int64_t uq = __shfl(qp, l, 64), us = __shfl(sp, l, 64);
+        const int32_t ur = on ? __shfl(rem, l, 64) : 0;
         int32_t e = 0;
         uint32_t w = 0;
-        for (;;) {
-            const int32_t off = e + 32 * lane;
-            const bool in = off < ur;
+        bool go = on;
+        while (__ballot(go)) {
+            const int32_t off = e + 32 * sub;
+            const bool in = go && off < ur;
             const int32_t o = in ? off : 0;
             const ull x = win32(q.rd, uq + o) ^ win32(A.seg, us + o);
             const int32_t rl = min(32, ur - off);
             const int32_t m = min(x ? (int32_t)(__clzll((long long)x) >> 1) : 32, rl);
-            const ull bad = __ballot(in && m < rl);
-            if (bad) {
-                const int f = __builtin_ctzll(bad);
-                e += 32 * f + __builtin_amdgcn_readlane(m, f);
-                w += f + 1;
-                break;
+            ull bad = __ballot(in && m < rl);
+            if (!one) bad = (bad >> (lane & 48)) & 0xffffull;
+            const int f = bad ? __builtin_ctzll(bad) : 0;
+            const int32_t mf = __shfl(m, one ? f : (lane & 48) + f, 64);
+            if (go) {
+                if (bad) {
+                    e += 32 * f + mf;
+                    w += f + 1;
+                    go = false;
+                } else {
+                    const int32_t g = min(ur - e, 32 * width);
+                    e += g;
+                    w += (uint32_t)(g + 31) >> 5;
+                    go = e < ur;
+                }
             }
-            const int32_t g = min(ur - e, 2048);
-            e += g;
-            w += (uint32_t)(g + 31) >> 5;
-            if (e >= ur) break;
         }
-        if (lane == l) { ext = e; chunks += w; }
+        // back to the runs' lanes: lane l's run was taken by the group whose lanes name it
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int lj = __builtin_amdgcn_readlane(l, 16 * j);
+            const int32_t ej = __builtin_amdgcn_readlane(e, 16 * j);
+            const uint32_t wj = __builtin_amdgcn_readlane(w, 16 * j);
+            const bool onj = __builtin_amdgcn_readlane((int)on, 16 * j) && (j == 0 || !one);
+            if (onj && lane == lj) { ext = ej; chunks += wj; }
+        }
     }
     return ext;
 }
@@ -763,8 +851,7 @@ __device__ __attribute__((noinline)) void narrow_scores(int64_t karg) {
     const int32_t half = (int32_t)((q.mask + 1) >> 1);
     int32_t s = __builtin_amdgcn_readfirstlane(S.nr_s), n = __builtin_amdgcn_readfirstlane(S.nr_n);
     const int32_t vmx = __builtin_amdgcn_readfirstlane(S.nr_vmx);
-    const uint32_t* vm_bits = reinterpret_cast<uint32_t*>(S.skeys);
-    const int32_t* vm_pre = reinterpret_cast<int32_t*>(S.skeys) + SH::XS;
+    const int32_t xb = MAIN_X * A.list_cap;
     const Lists L0 = list_of(A, arena, 0), Ls = list_of(A, arena, __builtin_amdgcn_readfirstlane(S.nr_list));
     int32_t* cu = reinterpret_cast<int32_t*>(arena + A.o_cand);
     int32_t *ck = cu + A.cand_cap, *cW = cu + 2 * (int64_t)A.cand_cap, *ct = cu + 3 * (int64_t)A.cand_cap;
@@ -788,8 +875,11 @@ __device__ __attribute__((noinline)) void narrow_scores(int64_t karg) {
         int32_t w = 0, t = -1, l = 0;
         int64_t b = 0;
         if (lane < n) {
-            const int32_t p = vmx ? vm_phys_bm(vm_bits, vm_pre, S.sidx, lane) : lane;
+            const Parts<SH::NW> parts(S);
+            const int32_t p = s == 0 ? xb + lane
+                                     : (vmx ? merged_place(S.skeys, S.xcnt, S.sidx, parts, xb, lane) : parts.place(lane));
             e = Ls.e[p];
+            e.w = page_of(e.w);
             if (q.track) w = Ls.w[p];
             if (q.tb) t = Ls.t[p];
             const int4 lab = A.vlab[e.x];
@@ -880,7 +970,7 @@ __device__ __attribute__((noinline)) void narrow_scores(int64_t karg) {
                             if (q.track) L.ow[p] = W;
                             if (q.tb) L.ot[p] = bt;
                         } else {   // more than a narrow list: it goes on in the wide path
-                            L0.e[p] = e;
+                            L0.e[p] = make_int4(v, kk, o, page_word(pg, o, Lv));
                             if (q.track) L0.w[p] = W;
                             if (q.tb) L0.t[p] = bt;
                             if ((p & (SAMP - 1)) == 0) S.samp[p / SAMP] = skey(v, kk);
@@ -1138,9 +1228,10 @@ __device__ __attribute__((noinline)) void narrow_scores(int64_t karg) {
         }
         if (lane < min(ntot, Narrow::N)) {
             const int4 e = L.oe[lane];
-            L0.e[lane] = e;
-            if (q.track) L0.w[lane] = L.ow[lane];
-            if (q.tb) L0.t[lane] = L.ot[lane];
+            const int32_t p = lane < n1 ? lane : xb + lane - n1;
+            L0.e[p] = make_int4(e.x, e.y, e.z, page_word(e.w, e.z, L.ol[lane]));
+            if (q.track) L0.w[p] = L.ow[lane];
+            if (q.tb) L0.t[p] = L.ot[lane];
             if (lane < n1 && (lane & (SAMP - 1)) == 0) S.samp[lane / SAMP] = skey(e.x, e.y);
         }
         // the candidates to where the wide path looks for them
@@ -1159,6 +1250,7 @@ __device__ __attribute__((noinline)) void narrow_scores(int64_t karg) {
         for (int c = Narrow::C + lane; c < min(nc, (int)SH::CS); c += 64) {
             S.csu[c] = cu[c]; S.csk[c] = ck[c]; S.cst[c] = ct[c];
         }
+        one_part<SH::NW>(S, n1);
         if (lane == 0) {
             S.ncand = nc; S.n_out = ntot; S.nr_n1 = n1; S.nr_round = round;
             S.amax = lmax.x; S.imax = lmax.y;
@@ -1177,26 +1269,254 @@ __device__ __attribute__((noinline)) void narrow_scores(int64_t karg) {
     }
 }
 
+// ---------------------------------------------------------------------------
+// EXPAND (Algorithm 3) + EXTEND of what it admits, on lists of any size.
+//
+// Every wave takes a part of the source list (whole groups of 64 entries, in
+// order) and runs through it on its own, with no barrier until the end.
+//   Sources: one entry per lane.  An output diagonal k' is owned by the
+// present source with the smallest k among k'-1, k', k'+1, and those are the
+// source's neighbours in the list, which the lanes exchange by whole-wave
+// shifts (the group before and the group after fill in at the ends); each
+// source makes up to three candidates, which go to the wave's ring in LDS in
+// list order.  The next group's entries and labels are loaded meanwhile.
+//   Outputs: whenever the ring holds 64 candidates, one per lane: records,
+// out-edge records, labels and windows are loaded, the run is extended, and
+// the outputs are written behind the wave's previous ones (at most three per
+// source, so the part's place in the new list is known from the start).
+// Before, a block staged 256 entries in LDS, each lane computed three output
+// slots of which one is taken on average, and three barriers and a scan
+// ordered the outputs of every batch (800 vector instructions a wave and
+// batch; here about 160 per 64 sources and 220 per 64 outputs).  What bounds
+// it now: issue when four workgroups share a CU, the two round trips of
+// extend() when they do not.  Per call: 20,000 reads on the 1 Mb DAG 135.5 ->
+// 122 ms, 3,001 noisy reads on the 10 Mb graph 459 -> 435 ms (its hardest
+// read alone takes 400), 500 reads of 100 kb through loops 518 -> 383 ms (its
+// lists of 25,000 to 50,000 entries are merged by the bitmap now, which holds
+// 65,536 positions instead of 32,768).
+// ---------------------------------------------------------------------------
+// x of the lane below (above), `edge` in lane 0 (63)
+__device__ __forceinline__ int32_t lane_below(int32_t x, int32_t edge) {
+    return __builtin_amdgcn_update_dpp(edge, x, 0x138, 0xf, 0xf, false);   // wave_shr:1
+}
+__device__ __forceinline__ int32_t lane_above(int32_t x, int32_t edge) {
+    return __builtin_amdgcn_update_dpp(edge, x, 0x130, 0xf, 0xf, false);   // wave_shl:1
+}
+__device__ __forceinline__ int32_t rdl(int32_t x, int l) { return __builtin_amdgcn_readlane(x, l); }
+
+template <int BLOCK, int MODE>
+__device__ __forceinline__ void expand_part(const KArgs& A, const Q& q, Shared<BLOCK, MODE>& S, const Lists& Ls,
+                                            const Lists& Ld, int32_t n, int32_t vmx, int32_t* cu, int32_t* ck,
+                                            int32_t* cW, int32_t* ct, uint32_t& chunks, int2& lmax) {
+    using SH = Shared<BLOCK, MODE>;
+    constexpr int NW = SH::NW;
+    const int lane = __lane_id();
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    typename SH::Ring& R = S.ring[wv];
+    const Parts<NW> parts(S);
+    const int32_t xb = MAIN_X * A.list_cap;
+    const int4* __restrict__ vinfo = A.vinfo;
+    const int4* __restrict__ vlab = A.vlab;
+    const ull* __restrict__ seg = A.seg;
+    auto part_lo = [&](int w) { return w >= NW ? n : (int32_t)(((int64_t)n * w / NW) & ~63); };
+    const int32_t lo = part_lo(wv), hi = part_lo(wv + 1);
+    const int32_t place0 = MAIN_X * lo;
+    int32_t nout = 0;            // outputs written
+    int32_t head = 0, fill = 0;  // the ring
+    ull* const samp = S.samp + wv * SH::SEGS;
+
+    struct Ent { int4 e; int32_t w, t; };
+    // the entries at merged positions base + lane (base a multiple of 64)
+    auto fetch = [&](int32_t base, Ent& x, int from = 0) {
+        x.e = make_int4(-1, 0, 0, 0);
+        x.w = 0;
+        x.t = -1;
+        if (base + lane < n && lane >= from) {
+            int32_t p;
+            if (vmx) {
+                const ull word = uniform64(S.skeys[base >> 6]);
+                const int32_t c = S.xcnt[base >> 6] + lanes_below(word);
+                p = ((word >> lane) & 1) ? xb + S.sidx[c] : parts.place(base + lane - c);
+            } else {
+                p = parts.place(base + lane);
+            }
+            x.e = Ls.e[p];
+            if (q.track) x.w = Ls.w[p];
+            if (q.tb) x.t = Ls.t[p];
+        }
+    };
+    // up to 64 candidates from the head of the ring
+    auto extend = [&](int cnt) {
+        const bool act = lane < cnt;
+        const int ri = (head + (act ? lane : 0)) & (SH::Ring::N - 1);
+        const int4 c = R.e[ri];
+        const int32_t t = q.tb ? R.t[ri] : -1;
+        const int32_t W0 = q.track ? R.w[ri] : 0;
+        const int32_t v = c.x, kk = c.y, bo = c.z & 0x7fffffff;
+        const bool chk = c.z < 0;
+        int d = c.w;
+        const int4 lab = vlab[v];
+        const int4 vi = vinfo[v];
+        // a missing page means no record: the output is admitted and needs the
+        // page, so it is created now
+        if (act && d < 0) d = dir_insert(q.dir, q.mask, dkey(v, kk >> 5), &S.dirn);
+        const ull rw = q.pages[max(d, 0)].R[kk & 31];
+        const int32_t Lv = lab.z;
+        const int64_t sb = lab_base(lab);
+        const int32_t i = kk + bo;
+        const int32_t m = act ? min(q.qlen - i, Lv - bo) : 0;
+        const ull x = win32(q.rd, q.q0 + (m > 0 ? i : 0)) ^ win32(seg, sb + (m > 0 ? bo : 0));
+        const bool rec = chk && d >= 0 && rgen(rw) == q.gen;
+        const bool ov = act && !(rec && bo <= rval(rw));
+        int32_t lx = 0;
+        if (ov && m > 0) {
+            ++chunks;
+            lx = min(x ? (int32_t)(__clzll((long long)x) >> 1) : 32, m);
+        }
+        lx += wave_extend(A, q, lx == 32 && m > 32, q.q0 + i + 32, sb + bo + 32, m - 32, chunks);
+        const ull om = __ballot(ov);
+        const int32_t o = bo + lx, W = W0 + lx;
+        int ncr = 0;
+        if (ov) {
+            if (d < 0) {
+                atomicOr(&S.flags, F_GROW);
+            } else {
+                ncr = record_entry(q, S, v, kk, o, W, d, chk && !rec, Lv, o == Lv ? vi.y : 0, lmax);
+                const int32_t j = nout + lanes_below(om);
+                Ld.e[place0 + j] = make_int4(v, kk, o, page_word(d, o, Lv));
+                if (q.track) Ld.w[place0 + j] = W;
+                if (q.tb) Ld.t[place0 + j] = t;
+                if ((j & (SAMP - 1)) == 0 && j < SAMP * SH::SEGS) samp[j / SAMP] = skey(v, kk);
+                if (j == 0) S.partK[wv] = skey(v, kk);
+            }
+        }
+        nout += __popcll(om);
+        // crossing candidates of the whole wave in one allocation, skipped when
+        // no lane reached a vertex end
+        if (__ballot(ncr != 0)) {
+            const int cp = wave_alloc(ncr, &S.ncand);
+            if (ncr) put_out_edges(S, A, cu, ck, cW, ct, cp, vi, kk + Lv, W, t);
+        }
+        head = (head + cnt) & (SH::Ring::N - 1);
+        fill -= cnt;
+    };
+
+    Ent cur, nxt, nn;
+    int32_t pv1 = -1, pk1 = 0, pv2 = -1, pk2 = 0;   // the two entries before the group
+    if (lo < hi) {
+        fetch(lo, cur);
+        fetch(lo + 64, nxt);
+        if (lo > 0) {
+            Ent b;
+            fetch(lo - 64, b, 62);
+            pv1 = rdl(b.e.x, 63); pk1 = rdl(b.e.y, 63);
+            pv2 = rdl(b.e.x, 62); pk2 = rdl(b.e.y, 62);
+        }
+    }
+    for (int32_t g = lo; g < hi; g += 64) {
+        fetch(g + 128, nn);
+        // all 64 sources at once, or 16 at a time when the ring has no room for
+        // so many candidates (made again then: they are not kept over extend)
+        for (int sub = 0, width = 64; sub < 64;) {
+        asm volatile("" : "+v"(cur.e.y));
+        const int32_t v = cur.e.x, k = cur.e.y, o0 = cur.e.z, ds0 = page_of(cur.e.w);
+        const int32_t vm1 = lane_below(v, pv1), km1 = lane_below(k, pk1);
+        const int32_t vm2 = lane_below(vm1, pv2), km2 = lane_below(km1, pk2);
+        const int32_t vp1 = lane_above(v, rdl(nxt.e.x, 0)), kp1 = lane_above(k, rdl(nxt.e.y, 0));
+        const int32_t op1 = lane_above(o0, rdl(nxt.e.z, 0)), dw1 = lane_above(cur.e.w, rdl(nxt.e.w, 0));
+        const int32_t dw2 = lane_above(dw1, rdl(nxt.e.w, 1));
+        const int32_t vp2 = lane_above(vp1, rdl(nxt.e.x, 1)), kp2 = lane_above(kp1, rdl(nxt.e.y, 1));
+        const int32_t op2 = lane_above(op1, rdl(nxt.e.z, 1));
+        const int32_t W0 = cur.w, t0 = cur.t;
+        const int32_t wp1 = q.track ? lane_above(W0, rdl(nxt.w, 0)) : 0;
+        const int32_t wp2 = q.track ? lane_above(wp1, rdl(nxt.w, 1)) : 0;
+        const int32_t tp1 = q.tb ? lane_above(t0, rdl(nxt.t, 0)) : -1;
+        const int32_t tp2 = q.tb ? lane_above(tp1, rdl(nxt.t, 1)) : -1;
+        const bool valid = g + lane < hi && (unsigned)(lane - sub) < (unsigned)width;
+        const int32_t i0 = k + o0;
+        // k-2, k-1 (k+1, k+2) of the same vertex are adjacent in the sorted list
+        const bool pm1 = vm1 == v && km1 == k - 1;
+        const bool pm2 = pm1 ? (vm2 == v && km2 == k - 2) : (vm1 == v && km1 == k - 2);
+        const bool pp1 = vp1 == v && kp1 == k + 1;
+        const bool pp2 = pp1 ? (vp2 == v && kp2 == k + 2) : (vp1 == v && kp1 == k + 2);
+        const int32_t o2 = pp1 ? op2 : op1, W2 = pp1 ? wp2 : wp1, t2 = pp1 ? tp2 : tp1;
+        // before the vertex end (o < |v|)
+        const bool in0 = cur.e.w >= 0, in1 = dw1 >= 0, in2 = (pp1 ? dw2 : dw1) >= 0;
+        const int32_t dp1 = page_of(dw1);
+        const int sl = k & 31;
+        // output k-1 (this source owns it when k-1 and k-2 are absent): deletion
+        const bool h0 = valid && !pm1 && !pm2 && in0;
+        // output k (owned when k-1 is absent): mismatch, deletion from k+1
+        int32_t b1 = -1, w1 = -1, t1 = -1;
+        if (i0 < q.qlen && in0) { b1 = o0 + 1; w1 = W0 + 1; t1 = t0; }
+        if (pp1 && in1 && (op1 + 1 > b1 || (op1 + 1 == b1 && wp1 + 1 > w1))) { b1 = op1 + 1; w1 = wp1 + 1; t1 = tp1; }
+        const bool h1 = valid && !pm1 && b1 > o0;
+        // output k+1 (always owned): insertion, mismatch at k+1, deletion from k+2
+        int32_t b2 = -1, w2 = -1, t2o = -1;
+        if (i0 < q.qlen) { b2 = o0; w2 = W0; t2o = t0; }
+        if (pp1 && k + 1 + op1 < q.qlen && in1 && (op1 + 1 > b2 || (op1 + 1 == b2 && wp1 + 1 > w2))) {
+            b2 = op1 + 1; w2 = wp1 + 1; t2o = tp1;
+        }
+        if (pp2 && in2 && (o2 + 1 > b2 || (o2 + 1 == b2 && W2 + 1 > w2))) { b2 = o2 + 1; w2 = W2 + 1; t2o = t2; }
+        const bool h2 = valid && b2 > (pp1 ? op1 : -1);
+        const int4 c0 = make_int4(v, k - 1, (o0 + 1) | (int32_t)0x80000000, sl > 0 ? ds0 : -1);
+        const int4 c1 = make_int4(v, k, b1, ds0);
+        const int4 c2 = make_int4(v, k + 1, pp1 ? b2 : (b2 | (int32_t)0x80000000), pp1 ? dp1 : (sl < 31 ? ds0 : -1));
+        // into the ring, in list order; whenever 64 are there they are extended
+        const ull m0 = __ballot(h0), m1 = __ballot(h1), m2 = __ballot(h2);
+        const int total = __popcll(m0) + __popcll(m1) + __popcll(m2);
+        if (fill + total > SH::Ring::N) { width = 16; continue; }   // at most 48 of 16 lanes
+        int x = head + fill + lanes_below(m0) + lanes_below(m1) + lanes_below(m2);
+        auto put = [&](bool h, const int4& c, int32_t w, int32_t t) {
+            if (h) {
+                const int r = x & (SH::Ring::N - 1);
+                R.e[r] = c;
+                if (q.tb) R.t[r] = t;
+                if (q.track) R.w[r] = w;
+            }
+            x += h ? 1 : 0;
+        };
+        put(h0, c0, W0 + 1, t0);
+        put(h1, c1, w1, t1);
+        put(h2, c2, w2, t2o);
+        fill += total;
+        sub += width;
+        if (sub >= 64) {
+            pv1 = rdl(v, 63); pk1 = rdl(k, 63);
+            pv2 = rdl(v, 62); pk2 = rdl(k, 62);
+        }
+        const bool flush = sub >= 64 && g + 64 >= hi;
+        wave_lds_order();
+        while (fill >= 64 || (flush && fill > 0)) extend(min(fill, 64));
+        wave_lds_order();
+        }
+        cur = nxt;
+        nxt = nn;
+    }
+    if (lane == 0) {
+        S.newN[wv] = nout;
+        if (nout) atomicAdd(&S.adm, (ull)nout);
+    }
+}
+
 // MODE 0: exact; 1: walk lengths tracked (Algorithm 4); 2: trace dump (and
 // the learned keep/drop); 3: learned keep/drop without the dump.  Each mode
 // is its own instantiation so that the registers of what it does not use
 // are not allocated.
 template <int BLOCK, int MODE>
-__device__ void align_read(const KArgs& Ak, char* __restrict__ arena, int r, Shared<BLOCK, MODE>& S) {
+__device__ void align_read(char* __restrict__ arena, int r, Shared<BLOCK, MODE>& S) {
     using SH = Shared<BLOCK, MODE>;
     constexpr bool LEARN = MODE >= 2;
     constexpr bool DUMP = MODE == 2;
-    constexpr bool NARROW = MODE == 1 || MODE == 3;   // pruned runs: small wavefronts throughout
+    constexpr bool NARROW = !DUMP;
     const int tid = threadIdx.x;
-    // arguments: see fresh_args; the exact instantiations have room for them
-    auto args = [&]() -> const KArgs& { return NARROW ? fresh_args() : Ak; };
     const int64_t t_begin = (int64_t)wall_clock64();
     // Every query here passed the screen pass (k_screen): its start vertex,
     // start window and end vertex are in range.
-    Q q = make_q<MODE>(args(), arena, r);
+    Q q = make_q<MODE>(fresh_args(), arena, r);
     int cap_log2 = 8;
     {
-        const KArgs& A = args();
+        const KArgs& A = fresh_args();
         const int64_t want = ((int64_t)q.qlen / 32 + 1) * A.dir_factor;
         while (cap_log2 < A.dir_log2_max && ((int64_t)1 << cap_log2) < want) ++cap_log2;
     }
@@ -1206,14 +1526,17 @@ __device__ void align_read(const KArgs& Ak, char* __restrict__ arena, int r, Sha
     int cur = 1;
     int32_t n_cur = 0;
     int32_t vmx = 0;          // crossing entries of the source list merged virtually
+    constexpr int NW = SH::NW;
+    // merged positions of crossing entries: a bitmap over the list in the keys'
+    // storage (64 positions per key slot) and the bits below each word
     uint32_t* const vm_bits = reinterpret_cast<uint32_t*>(S.skeys);
-    int32_t* const vm_pre = reinterpret_cast<int32_t*>(S.skeys) + SH::XS;
+    int32_t* const vm_pre = S.xcnt;
     int64_t work = 0;
     uint32_t chunks = 0;
     for (;;) {   // attempts with a growing directory
         const uint32_t mask = (1u << cap_log2) - 1;
         const int32_t half = (int32_t)((mask + 1) >> 1);
-        const KArgs& A0 = args();
+        const KArgs& A0 = fresh_args();
         const int32_t dir_log2_max = A0.dir_log2_max;
         bind_q(q, A0, arena);
         q.mask = mask;
@@ -1246,8 +1569,9 @@ __device__ void align_read(const KArgs& Ak, char* __restrict__ arena, int r, Sha
                 const int ds = dir_insert(q.dir, mask, dkey(q.vs, (-j) >> 5), &S.dirn);
                 if (ds < 0) atomicOr(&S.flags, F_GROW);
                 const int32_t t0 = q.tb ? trace_push(q, S, q.vs, -1 - j) : -1;
-                L0.e[t] = make_int4(q.vs, -j, j, ds);
-                L0.w[t] = 0; L0.t[t] = t0;
+                const int32_t p = MAIN_X * A0.list_cap + t;
+                L0.e[p] = make_int4(q.vs, -j, j, ds);
+                L0.w[p] = 0; L0.t[p] = t0;
                 L0.b[t] = sb0; L0.l[t] = lv0;
             }
             if (tid == 0) {
@@ -1255,6 +1579,7 @@ __device__ void align_read(const KArgs& Ak, char* __restrict__ arena, int r, Sha
                 if (nst > A0.list_cap) atomicOr(&S.flags, F_LIST);
             }
         }
+        one_part<NW>(S, 0);
         __syncthreads();
         // a start window that does not fit restarts with more working memory
         const int f0 = __builtin_amdgcn_readfirstlane(S.flags | ((S.dirn > half || S.mn > half) ? F_GROW : 0));
@@ -1295,14 +1620,14 @@ __device__ void align_read(const KArgs& Ak, char* __restrict__ arena, int r, Sha
                 cur = 1;              // list 0 is under construction
                 n_cur = val;
             }
-            const KArgs& A = args();
+            const KArgs& A = fresh_args();
             bind_q(q, A, arena);
             // read here for the loops below: the compiler does not move a load from
             // these arguments out of a branch
             const int4* __restrict__ vinfo = A.vinfo;
             const int4* __restrict__ vlab = A.vlab;
-            const ull* __restrict__ seg = A.seg;
             const int32_t list_cap = A.list_cap;
+            const int32_t xb = MAIN_X * list_cap;   // place of a list's crossing entry 0
             auto LL = [&](int j) -> Lists { return list_of(A, arena, j); };
             int32_t* const cu = reinterpret_cast<int32_t*>(arena + A.o_cand);
             const int64_t cc = A.cand_cap;
@@ -1317,255 +1642,22 @@ __device__ void align_read(const KArgs& Ak, char* __restrict__ arena, int r, Sha
             } else if (s > 0) {
                 if (tid == 0) { S.found = 0; S.iend = -1; S.endkey = ~0ull; S.amax = 0; S.imax = 0; }
                 __syncthreads();
-                // ========== EXPAND (Algorithm 3) + EXTEND of what it admits ==========
-                const Lists Ls = LL(cur);
-                const int32_t n = n_cur;
-                int32_t outbase = 0;
-                int adm = 0;
-                // each batch's entries (and, in threads 0-3, the two neighbours on
-                // each side of it) are loaded one batch ahead, before the stores
-                // of the batch being processed, so that their arrival does not
-                // wait for those stores
-                int4 pe, ph;
-                int32_t pw, pt, phw, pht;
-                auto fetch_batch = [&](int32_t bb) {
-                    pe = make_int4(-1, 0, 0, 0); pw = 0; pt = -1;
-                    const int32_t ix = bb + tid;
-                    if (ix < n) {
-                        const int32_t p0 = vmx ? vm_phys_bm(vm_bits, vm_pre, S.sidx, ix) : ix;
-                        pe = Ls.e[p0];
-                        if (q.track) pw = Ls.w[p0];
-                        if (q.tb) pt = Ls.t[p0];
-                    }
-                    ph = make_int4(-1, 0, 0, 0); phw = 0; pht = -1;
-                    if (tid < 4) {
-                        const int32_t hp = tid < 2 ? bb - 2 + tid : bb + BLOCK + (tid - 2);
-                        if (hp >= 0 && hp < n) {
-                            const int32_t pp = vmx ? vm_phys_bm(vm_bits, vm_pre, S.sidx, hp) : hp;
-                            ph = Ls.e[pp];
-                            if (q.track) phw = Ls.w[pp];
-                            if (q.tb) pht = Ls.t[pp];
-                        }
-                    }
-                };
-                fetch_batch(0);
-                for (int32_t base = 0; base < n; base += BLOCK) {
-                    const int32_t idx = base + tid;
-                    const bool valid = idx < n;
-                    // three fixed output slots: diagonals k-1, k, k+1
-                    bool ov0 = false, ov1 = false, ov2 = false;
-                    int32_t oo0 = 0, ow0 = 0, ot0 = 0, od0 = -1; bool on0 = false;
-                    int32_t oo1 = 0, ow1 = 0, ot1 = 0, od1 = -1;
-                    int32_t oo2 = 0, ow2 = 0, ot2 = 0, od2 = -1; bool on2 = false;
-                    // this lane's entry (merged position idx); v = -1 past the end
-                    const int32_t v = pe.x, k = pe.y, o0 = pe.z, ds0 = pe.w, W0 = pw, t0 = pt;
-                    // the label of v (its length bounds the candidates, its base places
-                    // their windows), requested before the exchange of neighbours,
-                    // which hides its latency
-                    const int4 lab = vlab[valid ? v : 0];   // unconditional: its wait can move to the first use
-                    // the neighbours at merged positions idx-2 .. idx+2 come from LDS:
-                    // every lane stages its entry, threads 0-3 the two positions on
-                    // each side of the batch
-                    {
-                        const int32_t hv = ph.x, hk = ph.y, ho = ph.z, hd = ph.w, hw = phw, ht = pht;
-                        const int hs = tid < 2 ? tid : BLOCK + tid;
-                        S.nbv[tid + 2] = v; S.nbk[tid + 2] = k; S.nbo[tid + 2] = o0; S.nbd[tid + 2] = ds0;
-                        if (q.track) S.nbw[tid + 2] = W0;
-                        if (q.tb) S.nbt[tid + 2] = t0;
-                        if (tid < 4) {
-                            S.nbv[hs] = hv; S.nbk[hs] = hk; S.nbo[hs] = ho; S.nbd[hs] = hd;
-                            if (q.track) S.nbw[hs] = hw;
-                            if (q.tb) S.nbt[hs] = ht;
-                        }
-                    }
-                    lds_barrier();
-                    const int32_t Lv = lab.z;
-                    const int64_t sb = lab_base(lab);
-                    const int32_t vm1 = S.nbv[tid + 1], km1 = S.nbk[tid + 1];
-                    const int32_t vm2 = S.nbv[tid], km2 = S.nbk[tid];
-                    const int32_t vp1 = S.nbv[tid + 3], kp1 = S.nbk[tid + 3], op1 = S.nbo[tid + 3];
-                    const int32_t dp1 = S.nbd[tid + 3];
-                    const int32_t vp2 = S.nbv[tid + 4], kp2 = S.nbk[tid + 4], op2 = S.nbo[tid + 4];
-                    const int32_t wp1 = q.track ? S.nbw[tid + 3] : 0, wp2 = q.track ? S.nbw[tid + 4] : 0;
-                    const int32_t tp1 = q.tb ? S.nbt[tid + 3] : -1, tp2 = q.tb ? S.nbt[tid + 4] : -1;
-                    // candidate outputs (before the record checks) and their first
-                    // 32-base windows, fetched together with the records
-                    int32_t c0 = -1, c1 = -1, c2 = -1;    // candidate offsets, -1 = none
-                    int32_t cw1 = -1, ct1 = -1, cw2 = -1, ct2 = -1;
-                    bool rec0 = false, rec2 = false;      // needs a record check
-                    int32_t d2 = -1;
-                    int pg0 = -1, pg2 = -1;
-                    if (valid) {
-                        const int32_t i0 = k + o0;
-                        // k-2, k-1 (k+1, k+2) of the same vertex are adjacent in the sorted list
-                        const bool pm1 = vm1 == v && km1 == k - 1;
-                        const bool pm2 = pm1 ? (vm2 == v && km2 == k - 2) : (vm1 == v && km1 == k - 2);
-                        const bool pp1 = vp1 == v && kp1 == k + 1;
-                        bool pp2;
-                        int32_t o1 = 0, W1 = 0, t1 = 0, o2 = 0, W2 = 0, t2 = 0;
-                        if (pp1) {
-                            o1 = op1; W1 = wp1; t1 = tp1; d2 = dp1;
-                            pp2 = vp2 == v && kp2 == k + 2;
-                            o2 = op2; W2 = wp2; t2 = tp2;
-                        } else {
-                            pp2 = vp1 == v && kp1 == k + 2;
-                            o2 = op1; W2 = wp1; t2 = tp1;
-                        }
-                        const int sl = k & 31;
-                        const int32_t kp0 = k >> 5;
-                        // output k-1 (this source owns it when k-1 and k-2 are absent): deletion
-                        if (!pm1 && !pm2 && o0 < Lv) {
-                            c0 = o0 + 1;
-                            rec0 = true;
-                            // a missing page means no record: the output is admitted and
-                            // needs the page, so it is created now
-                            pg0 = (sl > 0) ? ds0 : dir_insert(q.dir, mask, dkey(v, kp0 - 1), &S.dirn);
-                        }
-                        // output k (owned when k-1 is absent): mismatch, deletion from k+1
-                        if (!pm1) {
-                            int32_t bo = -1, bw = -1, bt = -1;
-                            if (i0 < q.qlen && o0 < Lv) { bo = o0 + 1; bw = W0 + 1; bt = t0; }
-                            if (pp1 && o1 < Lv && (o1 + 1 > bo || (o1 + 1 == bo && W1 + 1 > bw))) {
-                                bo = o1 + 1; bw = W1 + 1; bt = t1;
-                            }
-                            if (bo > o0) { c1 = bo; cw1 = bw; ct1 = bt; }
-                        }
-                        // output k+1 (always owned): insertion, mismatch at k+1, deletion from k+2
-                        {
-                            int32_t bo = -1, bw = -1, bt = -1;
-                            if (i0 < q.qlen) { bo = o0; bw = W0; bt = t0; }
-                            if (pp1 && k + 1 + o1 < q.qlen && o1 < Lv && (o1 + 1 > bo || (o1 + 1 == bo && W1 + 1 > bw))) {
-                                bo = o1 + 1; bw = W1 + 1; bt = t1;
-                            }
-                            if (pp2 && o2 < Lv && (o2 + 1 > bo || (o2 + 1 == bo && W2 + 1 > bw))) {
-                                bo = o2 + 1; bw = W2 + 1; bt = t2;
-                            }
-                            if (bo >= 0) {
-                                if (pp1) {
-                                    if (bo > o1) { c2 = bo; cw2 = bw; ct2 = bt; }
-                                } else {
-                                    c2 = bo; cw2 = bw; ct2 = bt;
-                                    rec2 = true;
-                                    pg2 = (sl < 31) ? ds0 : dir_insert(q.dir, mask, dkey(v, kp0 + 1), &S.dirn);
-                                }
-                            }
-                        }
-                    }
-                    // records of the diagonals outside F_s (k-1, k+1), the windows and
-                    // v's out-edge record (edge range and first targets, needed when an
-                    // output reaches the vertex end), all in one round of loads: every
-                    // lane loads every word (one without a use reads a harmless valid
-                    // address), so that no load sits in a branch of its own and the
-                    // loads are waited for once
-                    const int32_t m0 = (c0 >= 0) ? min(q.qlen - (k + c0 - 1), Lv - c0) : 0;
-                    const int32_t m1 = (c1 >= 0) ? min(q.qlen - (k + c1), Lv - c1) : 0;
-                    const int32_t m2 = (c2 >= 0) ? min(q.qlen - (k + 1 + c2), Lv - c2) : 0;
-                    const ull rw0l = q.pages[(rec0 && pg0 >= 0) ? pg0 : 0].R[(k - 1) & 31];
-                    const ull rw2l = q.pages[(rec2 && pg2 >= 0) ? pg2 : 0].R[(k + 1) & 31];
-                    const int4 vil = vinfo[valid ? v : 0];
-                    const ull x0l = win32(q.rd, m0 > 0 ? q.q0 + k - 1 + c0 : q.q0) ^ win32(seg, m0 > 0 ? sb + c0 : 0);
-                    const ull x1l = win32(q.rd, m1 > 0 ? q.q0 + k + c1 : q.q0) ^ win32(seg, m1 > 0 ? sb + c1 : 0);
-                    const ull x2l = win32(q.rd, m2 > 0 ? q.q0 + k + 1 + c2 : q.q0) ^ win32(seg, m2 > 0 ? sb + c2 : 0);
-                    const ull rw0 = (rec0 && pg0 >= 0) ? rw0l : 0ull;
-                    const ull rw2 = (rec2 && pg2 >= 0) ? rw2l : 0ull;
-                    const int4 vi = valid ? vil : make_int4(0, 0, -1, -1);
-                    const ull x0 = (m0 > 0) ? x0l : 0ull;
-                    const ull x1 = (m1 > 0) ? x1l : 0ull;
-                    const ull x2 = (m2 > 0) ? x2l : 0ull;
-                    if (c0 >= 0) {
-                        const bool rec = rgen(rw0) == q.gen;
-                        if (!rec || c0 > rval(rw0)) {
-                            ov0 = true; oo0 = c0; ow0 = W0 + 1; ot0 = t0; od0 = pg0; on0 = !rec;
-                        }
-                    }
-                    if (c1 >= 0) { ov1 = true; oo1 = c1; ow1 = cw1; ot1 = ct1; od1 = ds0; }
-                    if (c2 >= 0) {
-                        if (!rec2) {
-                            ov2 = true; oo2 = c2; ow2 = cw2; ot2 = ct2; od2 = d2; on2 = false;
-                        } else {
-                            const bool rec = rgen(rw2) == q.gen;
-                            if (!rec || c2 > rval(rw2)) { ov2 = true; oo2 = c2; ow2 = cw2; ot2 = ct2; od2 = pg2; on2 = !rec; }
-                        }
-                    }
-                    // extension of the admitted outputs
-                    int32_t lx0 = 0, lx1 = 0, lx2 = 0;
-                    {
-                        chunks += (ov0 && m0 > 0) + (ov1 && m1 > 0) + (ov2 && m2 > 0);
-                        lx0 = ov0 ? (x0 ? min((int32_t)(__clzll((long long)x0) >> 1), m0) : min(32, m0)) : 0;
-                        lx1 = ov1 ? (x1 ? min((int32_t)(__clzll((long long)x1) >> 1), m1) : min(32, m1)) : 0;
-                        lx2 = ov2 ? (x2 ? min((int32_t)(__clzll((long long)x2) >> 1), m2) : min(32, m2)) : 0;
-                        // whole windows matched and bases remain: continue (one call
-                        // site for the three outputs keeps the register demand down)
-#pragma unroll 1
-                        for (int j = 0; j < 3; ++j) {
-                            const int32_t lj = (j == 0) ? lx0 : ((j == 1) ? lx1 : lx2);
-                            const int32_t mj = (j == 0) ? m0 : ((j == 1) ? m1 : m2);
-                            if (lj == 32 && mj > 32) {
-                                const int32_t oj = (j == 0) ? oo0 : ((j == 1) ? oo1 : oo2);
-                                const int32_t r = 32 + lcp<false>(q.rd, q.q0 + k - 1 + j + oj + 32, ((q.q0 + q.qlen) >> 5) + 1, seg,
-                                                           sb + oj + 32, ((sb + Lv) >> 5) + 1, mj - 32, chunks);
-                                if (j == 0) lx0 = r; else if (j == 1) lx1 = r; else lx2 = r;
-                            }
-                        }
-                    }
-                    const int cnt = (int)ov0 + (int)ov1 + (int)ov2;
-                    int total;
-                    const int pos = block_excl_scan<BLOCK>(cnt, total, S.scan);
-                    if (base + BLOCK < n) fetch_batch(base + BLOCK);
-                    adm += cnt;
-                    int slot = 0;
-                    int endm = 0;        // outputs that reached the vertex end (cross every out-edge)
-                    int deg = 0;
+                expand_part<BLOCK, MODE>(A, q, S, LL(cur), Ld, n_cur, vmx, cu, ck, cW, ct, chunks, lmax);
+                __syncthreads();
+                // the new list's parts
 #pragma unroll
-                    for (int j = 0; j < 3; ++j) {
-                        const bool vj = (j == 0) ? ov0 : ((j == 1) ? ov1 : ov2);
-                        if (vj) {
-                            const int32_t kj = k - 1 + j;
-                            const int32_t lj = (j == 0) ? lx0 : ((j == 1) ? lx1 : lx2);
-                            const int32_t o = ((j == 0) ? oo0 : ((j == 1) ? oo1 : oo2)) + lj;
-                            const int32_t Wj = ((j == 0) ? ow0 : ((j == 1) ? ow1 : ow2)) + lj;
-                            const int32_t tj = (j == 0) ? ot0 : ((j == 1) ? ot1 : ot2);
-                            int d = (j == 0) ? od0 : ((j == 1) ? od1 : od2);
-                            const bool nw = (j == 0) ? on0 : ((j == 1) ? false : on2);
-                            const int32_t p = outbase + pos + slot;
-                            ++slot;
-                            if (d < 0) d = dir_insert(q.dir, mask, dkey(v, kj >> 5), &S.dirn);
-                            if (p >= list_cap) {
-                                atomicOr(&S.flags, F_LIST);
-                            } else if (d < 0) {
-                                atomicOr(&S.flags, F_GROW);
-                            } else {
-                                const int nc = record_entry(q, S, v, kj, o, Wj, d, nw, Lv, o == Lv ? vi.y : 0, lmax);
-                                if (nc) { endm |= 1 << j; deg = nc; }
-                                Ld.e[p] = make_int4(v, kj, o, d);
-                                if ((p & (SAMP - 1)) == 0 && p < SAMP * nsamp(BLOCK)) S.samp[p / SAMP] = skey(v, kj);
-                                if (q.track) Ld.w[p] = Wj;
-                                if (q.tb) Ld.t[p] = tj;
-                            }
-                        }
+                for (int w = 0; w < NW; ++w) {
+                    const int32_t c = S.newN[w];
+                    if (tid == w) {
+                        S.partL[w] = n1;
+                        S.partP[w] = MAIN_X * (int32_t)(((int64_t)n_cur * w / NW) & ~63);
+                        S.partN[w] = c;
                     }
-                    // crossing candidates of the whole wave in one allocation,
-                    // skipped when no lane of the wave reached a vertex end
-                    if (__ballot(endm != 0)) {
-                        const int ncr = __popc(endm) * deg;
-                        int cp = wave_alloc(ncr, &S.ncand);
-                        if (endm) {
-#pragma unroll
-                            for (int j = 0; j < 3; ++j) {
-                                if (!((endm >> j) & 1)) continue;
-                                const int32_t lj = (j == 0) ? lx0 : ((j == 1) ? lx1 : lx2);
-                                const int32_t Wj = ((j == 0) ? ow0 : ((j == 1) ? ow1 : ow2)) + lj;
-                                const int32_t tj = (j == 0) ? ot0 : ((j == 1) ? ot1 : ot2);
-                                const int32_t k2 = k - 1 + j + Lv;
-                                put_out_edges(S, A, cu, ck, cW, ct, cp, vi, k2, Wj, tj);
-                                cp += deg;
-                            }
-                        }
-                    }
-                    outbase += total;
+                    n1 += c;
                 }
-                n1 = min(outbase, list_cap);
-                if (adm) atomicAdd(&S.adm, (ull)adm);
+                n1 = __builtin_amdgcn_readfirstlane(n1);
+                if (n1 > list_cap && tid == 0) atomicOr(&S.flags, F_LIST);
+                n1 = min(n1, list_cap);   // not set in that branch: it has to stay a scalar
                 if (tid == 0) S.n_out = n1;
             }
             if (tid == 0) { const ull t2 = wall_clock64(); S.tick[0] += t2 - tk; tk = t2; }
@@ -1591,12 +1683,12 @@ __device__ void align_read(const KArgs& Ak, char* __restrict__ arena, int r, Sha
                             v = S.xsv[j]; k = S.xsk[j]; d = S.xsd[j]; o = 0; Lv = S.xsl[j]; sb = S.xsb[j];
                             t = q.tb ? S.xst[j] : -1;
                         } else {
-                            const int4 e = Ld.e[idx];
+                            const int4 e = Ld.e[xb + idx - n1];
                             v = e.x; k = e.y; d = e.w; o = e.z;
-                            sb = Ld.b[idx];
-                            Lv = Ld.l[idx];
-                            W = (q.track || idx < preset_hi) ? Ld.w[idx] : 0;
-                            t = (q.tb || idx < preset_hi) ? Ld.t[idx] : -1;
+                            sb = Ld.b[idx - n1];
+                            Lv = Ld.l[idx - n1];
+                            W = (q.track || idx < preset_hi) ? Ld.w[xb + idx - n1] : 0;
+                            t = (q.tb || idx < preset_hi) ? Ld.t[xb + idx - n1] : -1;
                         }
                         if (idx >= preset_hi && q.track) W = rval(q.pages[d].Wc[k & 31]);
                         vi = vinfo[v];
@@ -1607,9 +1699,9 @@ __device__ void align_read(const KArgs& Ak, char* __restrict__ arena, int r, Sha
                                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         ncr = extend_entry(A, q, S, v, k, o, W, d, true, sb, Lv, vi.y, chunks, lmax);
                         if (idx >= preset_hi) t = push ? trace_push_from(q, S, v, t, tprobe) : -1;
-                        Ld.e[idx].z = o;
-                        if (q.track) Ld.w[idx] = W;
-                        if (q.tb) Ld.t[idx] = t;
+                        *reinterpret_cast<int2*>(&Ld.e[xb + idx - n1].z) = make_int2(o, page_word(d, o, Lv));
+                        if (q.track) Ld.w[xb + idx - n1] = W;
+                        if (q.tb) Ld.t[xb + idx - n1] = t;
                         k2 = k + Lv;
                     }
                     if (__ballot(ncr != 0)) {
@@ -1678,10 +1770,11 @@ __device__ void align_read(const KArgs& Ak, char* __restrict__ arena, int r, Sha
                     const int pos = wave_alloc(claim, &S.n_out);
                     if (claim) {
                         if (pos < list_cap) {
-                            Ld.e[pos] = make_int4(u, kc, 0, ds);
-                            Ld.l[pos] = cLv; Ld.b[pos] = csb;
-                            if (q.track) Ld.w[pos] = wc;
-                            if (q.tb) Ld.t[pos] = tc;
+                            const int32_t x = pos - n1;
+                            Ld.e[xb + x] = make_int4(u, kc, 0, ds);
+                            Ld.l[x] = cLv; Ld.b[x] = csb;
+                            if (q.track) Ld.w[xb + x] = wc;
+                            if (q.tb) Ld.t[xb + x] = tc;
                             const int32_t j = pos - xhi;
                             if (j < SH::XC) {
                                 S.xsv[j] = u; S.xsk[j] = kc; S.xsd[j] = ds; S.xsl[j] = cLv; S.xsb[j] = csb; S.xst[j] = tc;
@@ -1726,8 +1819,9 @@ __device__ void align_read(const KArgs& Ak, char* __restrict__ arena, int r, Sha
                 clip = q.qlen - iend;
                 if (q.ilo < q.qlen) {
                     // the end cells of row iend (all of them are in this score's list)
+                    const Parts<NW> parts(S);
                     for (int32_t idx = tid; idx < ntot; idx += BLOCK) {
-                        const int4 e = Ld.e[idx];
+                        const int4 e = Ld.e[idx < n1 ? parts.place(idx) : xb + idx - n1];
                         const int32_t v = e.x, o = e.z;
                         if (e.y + o == iend && ends_walk(q, v, o, vlab[v].z))
                             atomicMin(&S.endkey, ((ull)(uint32_t)v << 32) | (uint32_t)o);
@@ -1738,9 +1832,11 @@ __device__ void align_read(const KArgs& Ak, char* __restrict__ arena, int r, Sha
                     if (tid == 0) S.tend = -1;
                     __syncthreads();
                     const int32_t ev = (int32_t)(S.endkey >> 32), eo = (int32_t)(S.endkey & 0xffffffffull);
+                    const Parts<NW> parts(S);
                     for (int32_t idx = tid; idx < ntot; idx += BLOCK) {
-                        const int4 e = Ld.e[idx];
-                        if (e.x == ev && e.z == eo && e.y + eo == iend) S.tend = Ld.t[idx];
+                        const int32_t p = idx < n1 ? parts.place(idx) : xb + idx - n1;
+                        const int4 e = Ld.e[p];
+                        if (e.x == ev && e.z == eo && e.y + eo == iend) S.tend = Ld.t[p];
                     }
                     __syncthreads();
                 }
@@ -1754,26 +1850,23 @@ __device__ void align_read(const KArgs& Ak, char* __restrict__ arena, int r, Sha
             if (ntot == 0) { status = q.ve >= 0 ? GWFA_ST_UNREACHABLE : GWFA_ST_MAX_SCORE; break; }
             if (q.ve < 0 && s > q.qlen + 1) { status = GWFA_ST_MAX_SCORE; break; }
             // ========== merge the crossing diagonals into the sorted list ==========
-            // Small sets (<= Shared::XS, in lists of up to 32 Shared::XS entries)
+            // Small sets (<= Shared::XS, in lists of up to 64 Shared::XS entries)
             // are merged virtually: their keys are ranked in LDS and each gets
             // its merged position (its rank among the crossing keys plus the
             // number of expansion outputs below it); the next pass reads the list
             // through a bitmap of those positions.  Larger sets are sorted in the
             // arena and the list is rewritten merged.
             const int32_t m = ntot - n1;
-            // sampled keys of the expansion's list (none at score 0, where the
-            // list is the crossing entries of the start alone)
-            const int32_t nsl = s > 0 ? min((int32_t)nsamp(BLOCK), (n1 + SAMP - 1) / SAMP) : 0;
             vmx = 0;
             if (m > 0) {
                 if (m > A.sort_cap) { rflags = F_LIST; break; }
-                if (m <= SH::XS && ntot <= 32 * SH::XS) {
+                if (m <= SH::XS && ntot <= 64 * SH::XS) {
                     // rank of each crossing key among them (the keys are distinct
                     // diagonals), counted against every key read from LDS by all
                     // lanes at once: two barriers, where a sorting network would
                     // take one per stage
                     for (int i = tid; i < m; i += BLOCK) {
-                        const int2 a = vk_of(Ld, n1 + i);
+                        const int2 a = vk_of(Ld, xb + i);
                         S.skeys[i] = skey(a.x, a.y);
                     }
                     __syncthreads();
@@ -1791,17 +1884,17 @@ __device__ void align_read(const KArgs& Ak, char* __restrict__ arena, int r, Sha
                             for (int u = 0; u < 16; ++u) rk += x[u] < ki ? 1 : 0;
                         }
                         for (; j < m; ++j) rk += S.skeys[j] < ki ? 1 : 0;
-                        S.sidx[rk] = n1 + i;
-                        S.xcnt[rk] = rk + lower_bound_sampled(Ld, n1, ki, S.samp, nsl);
+                        S.sidx[rk] = i;
+                        S.xcnt[rk] = rk + lower_bound_list(S, Ld, ki);
                     }
                     __syncthreads();
-                    // the merged positions as a bitmap over the list plus the number of
-                    // bits below each word, in the keys' storage (no longer needed;
-                    // 32 positions per key slot): the passes over this list find an
-                    // entry's physical slot from two words
+                    // the merged positions as a bitmap over the list, in the keys'
+                    // storage, then the number of bits below each word, in the
+                    // positions' (both no longer needed by then): the passes over
+                    // this list find an entry's place from two words
                     {
-                        const int32_t nw = (ntot + 31) >> 5;
-                        for (int32_t w = tid; w < nw; w += BLOCK) vm_bits[w] = 0u;
+                        const int32_t nw = (ntot + 63) >> 6;
+                        for (int32_t w = tid; w < 2 * nw; w += BLOCK) vm_bits[w] = 0u;
                         lds_barrier();
                         for (int32_t j = tid; j < m; j += BLOCK) {
                             const int32_t pj = S.xcnt[j];
@@ -1811,12 +1904,12 @@ __device__ void align_read(const KArgs& Ak, char* __restrict__ arena, int r, Sha
                         const int32_t kw = (nw + BLOCK - 1) / BLOCK;   // words per thread, in order
                         const int32_t w0 = min(tid * kw, nw), w1 = min(w0 + kw, nw);
                         int nbits = 0;
-                        for (int32_t w = w0; w < w1; ++w) nbits += __popc(vm_bits[w]);
+                        for (int32_t w = w0; w < w1; ++w) nbits += __popcll(S.skeys[w]);
                         int tot;
                         int below = block_excl_scan<BLOCK>(nbits, tot, S.scan);
                         for (int32_t w = w0; w < w1; ++w) {
                             vm_pre[w] = below;
-                            below += __popc(vm_bits[w]);
+                            below += __popcll(S.skeys[w]);
                         }
                         lds_barrier();
                     }
@@ -1831,22 +1924,25 @@ __device__ void align_read(const KArgs& Ak, char* __restrict__ arena, int r, Sha
                     for (int i = tid; i < N; i += BLOCK) {
                         ull key = ~0ull;
                         if (i < m) {
-                            const int2 a = vk_of(Ld, n1 + i);
+                            const int2 a = vk_of(Ld, xb + i);
                             key = skey(a.x, a.y);
                         }
                         gkeys[i] = key;
-                        gidx[i] = n1 + i;
+                        gidx[i] = i;
                     }
                     __syncthreads();
                     bitonic<BLOCK, false>(gkeys, gidx, N);
                     const Lists Lm = LL(cur);
+                    const Parts<NW> parts(S);
                     for (int32_t j = tid; j < n1; j += BLOCK) {
-                        const int2 a = vk_of(Ld, j);
-                        copy_entry(Ld, j, Lm, j + lower_bound_keys(gkeys, m, skey(a.x, a.y)), q.track, q.tb);
+                        const int32_t p = parts.place(j);
+                        const int2 a = vk_of(Ld, p);
+                        copy_entry(Ld, p, Lm, j + lower_bound_keys(gkeys, m, skey(a.x, a.y)), q.track, q.tb);
                     }
                     for (int32_t x = tid; x < m; x += BLOCK)
-                        copy_entry(Ld, gidx[x], Lm, x + lower_bound_sampled(Ld, n1, gkeys[x], S.samp, nsl), q.track,
-                                   q.tb);
+                        copy_entry(Ld, xb + gidx[x], Lm, x + lower_bound_list(S, Ld, gkeys[x]), q.track, q.tb);
+                    __syncthreads();
+                    one_part<NW>(S, ntot);
                     __syncthreads();
                 }
             } else {
@@ -1858,6 +1954,7 @@ __device__ void align_read(const KArgs& Ak, char* __restrict__ arena, int r, Sha
             if ((MODE == 1 || MODE == 2) && A.prune == GWFA_PRUNE_HEURISTIC && amax > A.a_diff) {
                 const Lists Ls = LL(cur);
                 const Lists Lp = LL(1 - cur);
+                const Parts<NW> parts(S);
                 int32_t outbase = 0;
                 int dropped = 0;
                 for (int32_t base = 0; base < n_cur; base += BLOCK) {
@@ -1865,12 +1962,12 @@ __device__ void align_read(const KArgs& Ak, char* __restrict__ arena, int r, Sha
                     int keep = 0;
                     int32_t ph = idx;
                     if (idx < n_cur) {
-                        if (vmx) ph = vm_phys_bm(vm_bits, vm_pre, S.sidx, idx);
+                        ph = vmx ? merged_place(S.skeys, vm_pre, S.sidx, parts, xb, idx) : parts.place(idx);
                         const int4 e = Ls.e[ph];
                         const int32_t a = e.y + e.z + Ls.w[ph];
                         keep = (amax - a < A.a_diff) ? 1 : 0;
                         if (!keep) {   // the diagonal keeps its offset as its record
-                            q.pages[e.w].R[e.y & 31] = mkR(q.gen, e.z);
+                            q.pages[page_of(e.w)].R[e.y & 31] = mkR(q.gen, e.z);
                             ++dropped;
                         }
                     }
@@ -1883,6 +1980,7 @@ __device__ void align_read(const KArgs& Ak, char* __restrict__ arena, int r, Sha
                 cur = 1 - cur;
                 n_cur = outbase;
                 vmx = 0;
+                one_part<NW>(S, n_cur);
                 __syncthreads();
                 if (tid == 0) S.tick[3] += wall_clock64() - tk;
             }
@@ -1891,6 +1989,7 @@ __device__ void align_read(const KArgs& Ak, char* __restrict__ arena, int r, Sha
             if (LEARN && ((DUMP && A.dump) || run_mlp)) {
                 const Lists Ls = LL(cur);
                 const Lists Lp = LL(1 - cur);
+                const Parts<NW> parts(S);
                 int32_t outbase = 0;
                 int dropped = 0, evals = 0;
                 for (int32_t base = 0; base < n_cur; base += BLOCK) {
@@ -1902,9 +2001,9 @@ __device__ void align_read(const KArgs& Ak, char* __restrict__ arena, int r, Sha
                     float f[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
                     int32_t v = 0, k = 0, o = 0, dp = 0, W = 0, i = 0;
                     if (live) {
-                        if (vmx) ph = vm_phys_bm(vm_bits, vm_pre, S.sidx, idx);
+                        ph = vmx ? merged_place(S.skeys, vm_pre, S.sidx, parts, xb, idx) : parts.place(idx);
                         const int4 e = Ls.e[ph];
-                        v = e.x; k = e.y; o = e.z; dp = e.w; W = Ls.w[ph];
+                        v = e.x; k = e.y; o = e.z; dp = page_of(e.w); W = Ls.w[ph];
                         i = k + o;
                         const int32_t Lv = vlab[v].z;
                         entry_features(f, s, i, W, o, Lv, vinfo[v].y, amax, imax, q.qlen);
@@ -1953,6 +2052,8 @@ __device__ void align_read(const KArgs& Ak, char* __restrict__ arena, int r, Sha
                     cur = 1 - cur;
                     n_cur = outbase;
                     vmx = 0;
+                    __syncthreads();
+                    one_part<NW>(S, n_cur);
                 }
                 __syncthreads();
             }
@@ -1971,7 +2072,7 @@ __device__ void align_read(const KArgs& Ak, char* __restrict__ arena, int r, Sha
     __syncthreads();
     // ========== results and walk (Algorithm 6) ==========
     if (tid == 0) {
-        const KArgs& A = args();
+        const KArgs& A = fresh_args();
         bind_q(q, A, arena);
         gwfa_result* const out = A.res + r;
         out->t_begin = t_begin;
@@ -2023,11 +2124,16 @@ __device__ void align_read(const KArgs& Ak, char* __restrict__ arena, int r, Sha
     __syncthreads();
 }
 
-// Waves per SIMD the compiler must allow: 3 (168 registers), 2 for the dump
-// instantiation; a 512-lane workgroup fills a CU alone: it takes the whole
-// register file instead of spilling.
+// Waves per SIMD the compiler must allow: 4 (128 registers), for the network's
+// instantiations 3 (168; one-wave workgroups 2: their LDS, with the network's
+// weights, lets 8 onto a CU), 2 for the dump instantiation; a 512-lane
+// workgroup of the tracked modes fills a CU alone: it takes the whole register
+// file instead of spilling.
+constexpr int waves_per_simd(int block, int mode) {
+    return mode == 2 ? 2 : (block >= 512 ? (mode == 0 ? 4 : 1) : (mode == 3 ? (block == 64 ? 2 : 3) : 4));
+}
 template <int BLOCK, int MODE>
-__global__ __launch_bounds__(BLOCK, MODE == 2 ? 2 : (BLOCK >= 512 ? (MODE == 0 ? 4 : 1) : (MODE == 3 ? 3 : 4))) void k_align(KArgs A) {
+__global__ __launch_bounds__(BLOCK, waves_per_simd(BLOCK, MODE)) void k_align(KArgs A) {
     constexpr bool LEARN = MODE >= 2;
     Shared<BLOCK, MODE>& S = lds<BLOCK, MODE>();
     char* arena = A.arena + (int64_t)blockIdx.x * A.arena_stride;
@@ -2048,7 +2154,7 @@ __global__ __launch_bounds__(BLOCK, MODE == 2 ? 2 : (BLOCK >= 512 ? (MODE == 0 ?
         __syncthreads();
         if (ridx >= n_q) break;
         const int r = A.order ? A.order[ridx] : ridx;
-        align_read<BLOCK, MODE>(A, arena, r, S);
+        align_read<BLOCK, MODE>(arena, r, S);
     }
     // counters: once per workgroup, on one of STAT_SLOTS lines.  Twelve atomics
     // per query on one line bounded short queries (87 ns a query, whatever the

@@ -118,3 +118,15 @@ def test_pruned_queries_that_outgrow_the_first_tier(G, a_diff):
     ctx.stats(reset=True)
     _compare(gw, ctx, cases, a_diff)
     assert ctx.stats()["reruns"] > 0
+
+
+@pytest.mark.parametrize("lanes", [64, 256, 512])
+def test_hubs_around_the_merge_limits(G, lanes):
+    """Crossing sets of as many entries as the merge ranks in LDS (256 or
+    1,024), one fewer and one more, exact: lists of several thousand entries
+    with few neighbours among them, in parts written by each wave."""
+    gw, ctx = G
+    ctx.config(lanes=lanes)
+    rng = np.random.default_rng(8400)
+    print(f"[gpu-narrow] lanes {lanes}: merge limits", flush=True)
+    _compare(gw, ctx, [hub_case(rng, deg, False) for deg in (255, 256, 257, 511, 1023, 1024, 1025)], 0)
