@@ -91,6 +91,7 @@ struct gwfa_ctx {
     size_t cig_bytes = 0;
     int32_t* d_cig_queue = nullptr;
     int n_cu = 256;
+    int exact_per_cu[4] = {0, 0, 0, 0}; // resident workgroups of 64 << i lanes per compute unit, exact mode
     char* static_base = nullptr;       // the device's static working memory (gwfa_align_batch_static_dev)
     std::string err;
 };
@@ -165,6 +166,7 @@ constexpr double TIER_SHARE[N_TIERS] = {0.14, 0.60, 0.20, 0.05};
 
 void set_tiers(gwfa_ctx* ctx, int32_t dir_log2_max, int32_t list_cap) {
     // default: as many persistent workgroups as can be resident at once
+    for (int i = 0; i < 4; ++i) ctx->exact_per_cu[i] = gwfa_align_blocks_per_cu(64 << i, GWFA_PRUNE_NONE);
     int per_cu = gwfa_align_blocks_per_cu(ctx->lanes, GWFA_PRUNE_NONE);
     if (per_cu <= 0) per_cu = 4;
     int pruned_per_cu = std::max(gwfa_align_blocks_per_cu(ctx->lanes, GWFA_PRUNE_HEURISTIC),
@@ -486,6 +488,20 @@ static int first_tier(const KArgs& A) {
     return A.prune == GWFA_PRUNE_LEARNED || (A.prune == GWFA_PRUNE_HEURISTIC && A.a_diff <= PRUNED_A_DIFF) ? 0 : 1;
 }
 
+// Lanes per query of a launch: the configured ones, or, for an exact batch that
+// would leave workgroup slots empty, twice or more as many, as long as every
+// query still has a workgroup resident at once.  An exact wavefront has work
+// for all of them: 500 reads of 100 kb take 384 ms at 256 lanes (half the
+// slots empty) and 237 ms at 512; with more queries than slots the wider
+// workgroups cost throughput (20,000 reads of 10 kb: 122 and 185 ms).
+static int launch_lanes(const gwfa_ctx* ctx, const KArgs& A, int64_t n) {
+    int lanes = ctx->lanes;
+    if (A.prune != GWFA_PRUNE_NONE || A.dump || ctx->groups > 0) return lanes;
+    for (int i = 1; i < 4; ++i)
+        if ((64 << i) > lanes && n <= (int64_t)ctx->n_cu * ctx->exact_per_cu[i]) lanes = 64 << i;
+    return lanes;
+}
+
 // Working memory of tier ti into A; returns the workgroups to launch.
 static int set_tier(gwfa_ctx* ctx, KArgs& A, int ti, const int32_t* order, int32_t n, const int32_t* n_valid,
                     int* groups) {
@@ -516,7 +532,7 @@ static int run_tiers(gwfa_ctx* ctx, KArgs& A, int ti0, int32_t n, bool launched,
             int groups = 0;
             int rc = set_tier(ctx, A, ti, order, n, n_valid, &groups);
             if (rc) return rc;
-            HIPCHK(ctx, gwfa_launch_align(A, ctx->lanes, groups, st));
+            HIPCHK(ctx, gwfa_launch_align(A, launch_lanes(ctx, A, n), groups, st));
         }
         if (ti + 1 == N_TIERS) break;
         int32_t h_retry = 0;
@@ -698,7 +714,7 @@ int gwfa_plan_create(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const 
         // screen pass, then the first tier
         hipError_t e1 = gwfa_launch_reset(ctx->d_queue, p->A.path_cursor, ctx->d_retry_count, nullptr, p->cap);
         if (e1 == hipSuccess) e1 = gwfa_launch_screen(S0, ctx->d_valid, ctx->d_valid_n, p->cap);
-        if (e1 == hipSuccess) e1 = gwfa_launch_align(p->A, ctx->lanes, groups, p->cap);
+        if (e1 == hipSuccess) e1 = gwfa_launch_align(p->A, launch_lanes(ctx, p->A, n_reads), groups, p->cap);
         e = hipStreamEndCapture(p->cap, &p->graph);
         if (e1 != hipSuccess) e = e1;
     }

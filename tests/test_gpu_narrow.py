@@ -10,6 +10,7 @@ import numpy as np
 import pytest
 
 import oracle as O
+from paper_2206_13574_amd import synth
 from tests.test_gpu_parity import check_path, reads_of, union_graph
 
 pytestmark = pytest.mark.gpu
@@ -130,3 +131,26 @@ def test_hubs_around_the_merge_limits(G, lanes):
     rng = np.random.default_rng(8400)
     print(f"[gpu-narrow] lanes {lanes}: merge limits", flush=True)
     _compare(gw, ctx, [hub_case(rng, deg, False) for deg in (255, 256, 257, 511, 1023, 1024, 1025)], 0)
+
+
+def test_batches_around_the_widening_limits(G):
+    """Exact batches small enough to be resident at more lanes per query are
+    launched with more: the same results at every size."""
+    gw, ctx = G
+    g = synth.bubble_graph(90, 5000, snp_gap=50, indel_gap=300, indel_arm=(1, 20))
+    r = synth.sample_reads(g, 91, 3600, lambda rng, n: rng.integers(50, 400, size=n), 0.04)
+    graph = gw.Graph.of(ctx, g)
+    try:
+        ctx.config(lanes=64, groups=300)           # a given number of workgroups: no widening
+        ref, _ = gw.align(ctx, graph, r.seq, r.off, r.v_start)
+        ctx.config(lanes=64)
+        for n in (1, 767, 768, 769, 1023, 1024, 1025, 2303, 2304, 2305, 3600):
+            print(f"[gpu-narrow] {n} queries", flush=True)
+            s = r.subset(np.arange(n))
+            res, paths = gw.align(ctx, graph, s.seq, s.off, s.v_start)
+            for f in ("status", "dist", "end_v", "end_off", "n_scores", "work"):
+                assert np.array_equal(res[f], ref[f][:n]), (n, f)
+            for i in range(0, n, 97):
+                check_path(g, s.read(i), int(s.v_start[i]), res[i], paths[i])
+    finally:
+        graph.close()
