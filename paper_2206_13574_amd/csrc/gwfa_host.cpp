@@ -28,7 +28,6 @@ constexpr int32_t PRUNED_DIR_LOG2 = 14, PRUNED_LIST_CAP = 4096, PRUNED_DIR_FACTO
 // Algorithm 4 keeps diagonals that lag by less than a_diff: with more lag than
 // this the record sets of long reads outgrow tier 0 and would be run twice.
 constexpr int32_t PRUNED_A_DIFF = 1024;
-constexpr int64_t MLP_SCR_SAMPLES = 16384;
 
 struct Tier {
     int32_t dir_log2_max = 16;
@@ -85,7 +84,7 @@ struct gwfa_ctx {
     uint16_t* d_mlp = nullptr;
     float* d_mlp_scale = nullptr;
     bool mlp_loaded = false;
-    float* d_mlp_scr = nullptr;        // training activations, MLP_SCR_SAMPLES samples
+    float* d_mlp_scr = nullptr;        // training: the workgroups' partial gradients
     int64_t epoch = 0;                 // bumped when working memory is freed (invalidates plans)
     char* d_cig_arena = nullptr;       // base-level alignment: per-workgroup regions
     size_t cig_bytes = 0;
@@ -934,12 +933,12 @@ int gwfa_mlp_grad_dev(gwfa_ctx* ctx, const float* d_feat, int64_t n, int64_t fea
     hipStream_t st = hip_stream ? (hipStream_t)hip_stream : ctx->stream;
     HIPCHK(ctx, hipSetDevice(ctx->device));
     if (!ctx->d_mlp_scr)
-        if (hipMalloc((void**)&ctx->d_mlp_scr, (size_t)gwfa_mlp_scratch_floats(MLP_SCR_SAMPLES) * 4) != hipSuccess) {
+        if (hipMalloc((void**)&ctx->d_mlp_scr, (size_t)gwfa_mlp_scratch_floats() * 4) != hipSuccess) {
             ctx->d_mlp_scr = nullptr;
             return GWFA_ERR_NOMEM;
         }
     HIPCHK(ctx, gwfa_launch_mlp_grad(d_feat, feat_stride, sc, d_label, n, pos_weight, d_w, ctx->d_mlp_scr,
-                                     MLP_SCR_SAMPLES, d_grad, d_loss, st));
+                                     d_grad, d_loss, st));
     return GWFA_OK;
 }
 

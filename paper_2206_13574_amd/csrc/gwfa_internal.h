@@ -92,10 +92,10 @@ hipError_t gwfa_launch_screen(const KArgs& A, int32_t* valid, int32_t* n_valid, 
 struct Scale8 {
     float s[8];
 };
-int64_t gwfa_mlp_scratch_floats(int64_t samples);
+int64_t gwfa_mlp_scratch_floats();
 hipError_t gwfa_launch_mlp_grad(const float* feat, int64_t stride, const Scale8& scale, const uint8_t* label,
-                                int64_t n, float pos_weight, const uint16_t* w, float* scr, int64_t scr_samples,
-                                float* grad, float* loss, hipStream_t st);
+                                int64_t n, float pos_weight, const uint16_t* w, float* scr, float* grad, float* loss,
+                                hipStream_t st);
 hipError_t gwfa_launch_mlp_adam(float* master, float* m1, float* m2, const float* grad, uint16_t* wb, float lr,
                                 float beta1, float beta2, float eps, float bc1, float bc2, hipStream_t st);
 hipError_t gwfa_launch_mlp_cast(const float* src, uint16_t* dst, int64_t n, hipStream_t st);

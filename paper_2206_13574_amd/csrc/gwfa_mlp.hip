@@ -21,10 +21,14 @@ namespace gwfa_train {
 
 using namespace gwfa_nn;
 
-// per-sample activations kept between the two passes:
-// x[8] | h1[64] | h2[64] | g2[64] = dL/da2 | g1[64] = dL/da1 | dz = dL/dz
-constexpr int C_X = 0, C_H1 = 8, C_H2 = 72, C_G2 = 136, C_G1 = 200, C_DZ = 264, SS = 265;
-constexpr int SPB = 256;   // samples per block of the weight-gradient kernel
+// One workgroup's partial sums: the gradient, then the loss, padded.
+constexpr int PART = 4864;
+constexpr int GRAD_WAVES = 4;       // waves of a gradient workgroup
+constexpr int GRAD_BLOCKS = 256;    // at most: one per compute unit
+
+// LDS written by some lanes of a wave is read by others: its DS operations run
+// in order, only the compiler has to keep them so.
+__device__ __forceinline__ void wave_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 __device__ __forceinline__ float softplus(float z) { return fmaxf(z, 0.0f) + log1pf(expf(-fabsf(z))); }
 __device__ __forceinline__ float sigmoid(float z) {
@@ -32,97 +36,222 @@ __device__ __forceinline__ float sigmoid(float z) {
     return z >= 0.0f ? 1.0f / (1.0f + e) : e / (1.0f + e);
 }
 
-__global__ void k_zero(float* __restrict__ p, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0.0f;
-}
-
-// Forward and per-sample backward, one thread per sample.
-__global__ __launch_bounds__(256) void k_act(const float* __restrict__ feat, int64_t stride, Scale8 scale,
-                                             const uint8_t* __restrict__ label, int64_t n, float pos_weight,
-                                             float inv_n, const uint16_t* __restrict__ w, float* __restrict__ scr,
-                                             float* __restrict__ loss) {
-    __shared__ float sw[MLP_N];
-    __shared__ float part[4];
-    for (int i = threadIdx.x; i < MLP_N; i += blockDim.x) sw[i] = bf2f(w[i]);
-    __syncthreads();
-    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    float my_loss = 0.0f;
-    if (b < n) {
-        float* S = scr + b * SS;
-        const float* f = feat + b * stride;
-        float x[8];
+// Forward and backward of 16 samples per wave and step, all products on the
+// matrix cores: the forward pass in bfloat16 (the values are bfloat16), the
+// backward pass and the weight gradients in float32 (v_mfma_f32_16x16x4_f32),
+// so nothing is rounded that a float32 sum would not round.  Lane (g = l/16,
+// m = l%16) holds:
+//   h1   unit 16c + 4g + i of sample m          (layer 1, transposed)
+//   a2   unit 16c + m of sample 4g + i          (layer 2, and g2 = dL/da2)
+// Products over samples take sample 4g + q in step q, so g2 and g1 are operands
+// as they lie; h1 and g2 are turned once each through LDS.  Every wave keeps
+// its whole gradient in registers over its samples; the waves of a workgroup
+// are added in LDS and the workgroups by k_grad_sum, without atomics and in
+// a fixed order.
+// 32,768 samples: 17 us, bound by the waves' chain of steps (two per wave), the
+// matrix work being 4 us; one thread per sample and per parameter took 300 us.
+__global__ __launch_bounds__(64 * GRAD_WAVES, 1) void k_grad(const float* __restrict__ feat, int64_t stride,
+                                                             Scale8 scale, const uint8_t* __restrict__ label, int64_t n,
+                                                             float pos_weight, float inv_n,
+                                                             const uint16_t* __restrict__ w, float* __restrict__ part) {
+    constexpr int LD = 68;                       // row of a turned tile
+    struct Tile { float h[16 * LD], g[16 * LD], x[16 * 17]; };
+    __shared__ float w2f[64 * 65];               // W2 as float
+    __shared__ union { Tile tile[GRAD_WAVES]; float sum[PART]; } L;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int col = lane & 15, grp = lane >> 4;
+    Tile& T = L.tile[wv];
+    for (int p = threadIdx.x; p < 4096; p += 64 * GRAD_WAVES) w2f[(p >> 6) * 65 + (p & 63)] = bf2f(w[MW_W2 + p]);
+    // weights as operands, kept over the samples
+    const __bf16 zero = bf_bits(0);
+    bf16x8 w1a[4], w2b[2][4];
+    float b1[16], b2[4], w3[4];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            x[i] = round_bf16(f[i] * scale.s[i]);
-            S[C_X + i] = x[i];
-        }
-        float h1[64];
-        unsigned long long m1 = 0, m2 = 0;   // ReLU masks
+    for (int c = 0; c < 4; ++c) {
 #pragma unroll
-        for (int j = 0; j < 64; ++j) {
-            float a = sw[MW_B1 + j];
+        for (int i = 0; i < 8; ++i) w1a[c][i] = grp == 0 ? bf_bits(w[(16 * c + col) * 8 + i]) : zero;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) a = fmaf(sw[j * 8 + i], x[i], a);
-            if (a > 0.0f) m1 |= 1ull << j;
-            h1[j] = round_bf16(fmaxf(a, 0.0f));
-            S[C_H1 + j] = h1[j];
-        }
-        float z = sw[MW_B3];
-        for (int j = 0; j < 64; ++j) {
-            float a = sw[MW_B2 + j];
+        for (int i = 0; i < 4; ++i) b1[4 * c + i] = bf2f(w[MW_B1 + 16 * c + 4 * grp + i]);
+        b2[c] = bf2f(w[MW_B2 + 16 * c + col]);
+        w3[c] = bf2f(w[MW_W3 + 16 * c + col]);
 #pragma unroll
-            for (int k = 0; k < 64; ++k) a = fmaf(sw[MW_W2 + j * 64 + k], h1[k], a);
-            if (a > 0.0f) m2 |= 1ull << j;
-            const float h2 = round_bf16(fmaxf(a, 0.0f));
-            S[C_H2 + j] = h2;
-            z = fmaf(sw[MW_W3 + j], h2, z);
-        }
-        const bool pos = label[b] != 0;
-        my_loss = pos ? pos_weight * softplus(-z) : softplus(z);
-        const float sz = sigmoid(z);
-        const float dz = (pos ? pos_weight * (sz - 1.0f) : sz) * inv_n;
-        S[C_DZ] = dz;
-        float g2[64];
+        for (int ks = 0; ks < 2; ++ks) {
+            const uint16_t* row = w + MW_W2 + (16 * c + col) * 64 + 32 * ks + 4 * grp;
 #pragma unroll
-        for (int j = 0; j < 64; ++j) {
-            g2[j] = ((m2 >> j) & 1) ? dz * sw[MW_W3 + j] : 0.0f;
-            S[C_G2 + j] = g2[j];
-        }
-        for (int k = 0; k < 64; ++k) {
-            float a = 0.0f;
-#pragma unroll
-            for (int j = 0; j < 64; ++j) a = fmaf(sw[MW_W2 + j * 64 + k], g2[j], a);
-            S[C_G1 + k] = ((m1 >> k) & 1) ? a : 0.0f;
+            for (int i = 0; i < 4; ++i) {
+                w2b[ks][c][i] = bf_bits(row[i]);
+                w2b[ks][c][4 + i] = bf_bits(row[16 + i]);
+            }
         }
     }
-    // block sum of the loss: wave sums, then one atomic per block
-    float v = my_loss;
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
+    const float b3 = bf2f(w[MW_B3]);
+    f32x4 d2[4][4], d1[4];                       // dW2 by unit pair; dW1 with db1 as column 8
+    float db2[4], dw3[4], db3 = 0.0f, loss = 0.0f;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        db2[c] = 0.0f; dw3[c] = 0.0f;
+        d1[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) d2[c][k] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
     __syncthreads();
-    if (threadIdx.x == 0) atomicAdd(loss, (part[0] + part[1] + part[2] + part[3]) * inv_n);
+    const int64_t tiles = (n + 15) / 16;
+    for (int64_t t = (int64_t)blockIdx.x * GRAD_WAVES + wv; t < tiles; t += (int64_t)gridDim.x * GRAD_WAVES) {
+        // inputs: two features per lane, column 8 is 1 (the bias)
+        {
+            const int64_t b = 16 * t + col;
+            const bool ok = b < n;
+            const float* f = feat + (ok ? b : 0) * stride + 2 * grp;
+            const float s0 = scale.s[2 * grp], s1 = scale.s[2 * grp + 1];
+            T.x[col * 17 + 2 * grp] = ok ? round_bf16(f[0] * s0) : 0.0f;
+            T.x[col * 17 + 2 * grp + 1] = ok ? round_bf16(f[1] * s1) : 0.0f;
+            T.x[col * 17 + 8 + 2 * grp] = ok && grp == 0 ? 1.0f : 0.0f;
+            T.x[col * 17 + 9 + 2 * grp] = 0.0f;
+        }
+        bool pos[4], ok[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int64_t b = 16 * t + 4 * grp + i;
+            ok[i] = b < n;
+            pos[i] = ok[i] && label[ok[i] ? b : 0] != 0;
+        }
+        wave_order();
+        bf16x8 xb;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) xb[i] = grp == 0 ? bf_of(T.x[col * 17 + i]) : zero;
+        float h[16];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            f32x4 d;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) d[i] = b1[4 * c + i];
+            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1a[c], xb, d, 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                h[4 * c + i] = round_bf16(fmaxf(d[i], 0.0f));
+                T.h[col * LD + 16 * c + 4 * grp + i] = h[4 * c + i];
+            }
+        }
+        f32x4 a2[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) a2[c] = f32x4{b2[c], b2[c], b2[c], b2[c]};
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            bf16x8 a;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                a[i] = bf_of(h[8 * ks + i]);
+                a[4 + i] = bf_of(h[8 * ks + 4 + i]);
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) a2[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, w2b[ks][c], a2[c], 0, 0, 0);
+        }
+        // logits of samples 4g + i, loss and dL/dz; g2 = dL/da2
+        float g2[4][4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float h2[4], z = 0.0f;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                h2[c] = round_bf16(fmaxf(a2[c][i], 0.0f));
+                z = fmaf(w3[c], h2[c], z);
+            }
+#pragma unroll
+            for (int o = 8; o >= 1; o >>= 1) z += __shfl_xor(z, o, 64);
+            z += b3;
+            const float sz = sigmoid(z);
+            const float dz = ok[i] ? (pos[i] ? pos_weight * (sz - 1.0f) : sz) * inv_n : 0.0f;
+            if (col == 0 && ok[i]) {
+                loss += pos[i] ? pos_weight * softplus(-z) : softplus(z);
+                db3 += dz;
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                dw3[c] = fmaf(dz, h2[c], dw3[c]);
+                g2[c][i] = a2[c][i] > 0.0f ? dz * w3[c] : 0.0f;
+                db2[c] += g2[c][i];
+                T.g[(4 * grp + i) * LD + 16 * c + col] = g2[c][i];
+            }
+        }
+        wave_order();
+        float hb[4][4];                          // h1 of unit 16k + m, sample 4g + q
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) hb[k][q] = T.h[(4 * grp + q) * LD + 16 * k + col];
+        f32x4 a1[4];                             // dL/dh1 of unit 16k + m, sample 4g + i
+#pragma unroll
+        for (int k = 0; k < 4; ++k) a1[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {           // unit 16g + q of layer 2
+            const float ga = T.g[col * LD + 16 * grp + q];
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                a1[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(ga, w2f[(16 * grp + q) * 65 + 16 * k + col], a1[k], 0, 0, 0);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float xv = T.x[(4 * grp + q) * 17 + col];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    d2[c][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(g2[c][q], hb[k][q], d2[c][k], 0, 0, 0);
+                d1[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(hb[c][q] > 0.0f ? a1[c][q] : 0.0f, xv, d1[c], 0, 0, 0);
+            }
+        }
+        wave_order();                            // the tile's rows are read before they are written again
+    }
+    // the biases' and w3's lanes: sum over the four groups
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        db2[c] += __shfl_xor(db2[c], 16, 64); db2[c] += __shfl_xor(db2[c], 32, 64);
+        dw3[c] += __shfl_xor(dw3[c], 16, 64); dw3[c] += __shfl_xor(dw3[c], 32, 64);
+    }
+    db3 += __shfl_xor(db3, 16, 64); db3 += __shfl_xor(db3, 32, 64);
+    loss += __shfl_xor(loss, 16, 64); loss += __shfl_xor(loss, 32, 64);
+    for (int v = 0; v < GRAD_WAVES; ++v) {
+        __syncthreads();
+        if (wv == v) {
+            auto add = [&](int p, float x) { L.sum[p] = v == 0 ? x : L.sum[p] + x; };
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int j = 16 * c + 4 * grp + i;
+                    if (col < 8) add(j * 8 + col, d1[c][i]);
+                    if (col == 8) add(MW_B1 + j, d1[c][i]);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) add(MW_W2 + j * 64 + 16 * k + col, d2[c][k][i]);
+                }
+                if (grp == 0) {
+                    add(MW_B2 + 16 * c + col, db2[c]);
+                    add(MW_W3 + 16 * c + col, dw3[c]);
+                }
+            }
+            if (lane == 0) { add(MW_B3, db3); add(MLP_N, loss * inv_n); }
+        }
+    }
+    __syncthreads();
+    for (int p = threadIdx.x; p <= MLP_N; p += 64 * GRAD_WAVES) part[(int64_t)blockIdx.x * PART + p] = L.sum[p];
 }
 
-// Weight gradients: thread = parameter, block row = SPB samples.
-__global__ __launch_bounds__(256) void k_wgrad(const float* __restrict__ scr, int64_t n, float* __restrict__ grad) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t b0 = (int64_t)blockIdx.y * SPB;
-    if (p >= MLP_N || b0 >= n) return;
-    int ca, cb;   // columns multiplied; cb < 0: column ca alone
-    if (p < MW_B1) { ca = C_G1 + p / 8; cb = C_X + p % 8; }                         // W1[j][i]
-    else if (p < MW_W2) { ca = C_G1 + (p - MW_B1); cb = -1; }                       // b1[j]
-    else if (p < MW_B2) { ca = C_G2 + (p - MW_W2) / 64; cb = C_H1 + (p - MW_W2) % 64; }   // W2[j][k]
-    else if (p < MW_W3) { ca = C_G2 + (p - MW_B2); cb = -1; }                       // b2[j]
-    else if (p < MW_B3) { ca = C_DZ; cb = C_H2 + (p - MW_W3); }                     // W3[j]
-    else { ca = C_DZ; cb = -1; }                                                    // b3
-    const int64_t b1 = min(n, b0 + SPB);
-    float acc = 0.0f;
-    for (int64_t b = b0; b < b1; ++b) {
-        const float* S = scr + b * SS;
-        acc = fmaf(S[ca], cb >= 0 ? S[cb] : 1.0f, acc);
+// Sums the workgroups' parts: 32 values per workgroup, eight lanes a value.
+__global__ __launch_bounds__(256) void k_grad_sum(const float* __restrict__ part, int blocks, float* __restrict__ grad,
+                                                  float* __restrict__ loss) {
+    __shared__ float s[8][32];
+    const int p = blockIdx.x * 32 + (threadIdx.x & 31), q = threadIdx.x >> 5;
+    float a = 0.0f;
+    if (p <= MLP_N)
+#pragma unroll 8
+        for (int b = q; b < blocks; b += 8) a += part[(int64_t)b * PART + p];
+    s[q][threadIdx.x & 31] = a;
+    __syncthreads();
+    if (q == 0 && p <= MLP_N) {
+#pragma unroll
+        for (int k = 1; k < 8; ++k) a += s[k][threadIdx.x];
+        if (p < MLP_N) grad[p] = a; else *loss = a;
     }
-    atomicAdd(&grad[p], acc);
 }
 
 __global__ void k_adam(float* __restrict__ master, float* __restrict__ m1, float* __restrict__ m2,
@@ -168,24 +297,20 @@ __global__ __launch_bounds__(256) void k_logits(const float* __restrict__ feat, 
 // ---------------------------------------------------------------------------
 // launch helpers
 // ---------------------------------------------------------------------------
-int64_t gwfa_mlp_scratch_floats(int64_t samples) { return samples * gwfa_train::SS; }
+int64_t gwfa_mlp_scratch_floats() { return (int64_t)gwfa_train::GRAD_BLOCKS * gwfa_train::PART; }
 
 hipError_t gwfa_launch_mlp_grad(const float* feat, int64_t stride, const Scale8& scale, const uint8_t* label,
-                                int64_t n, float pos_weight, const uint16_t* w, float* scr, int64_t scr_samples,
-                                float* grad, float* loss, hipStream_t st) {
+                                int64_t n, float pos_weight, const uint16_t* w, float* scr, float* grad, float* loss,
+                                hipStream_t st) {
     using namespace gwfa_train;
     (void)hipGetLastError();   // report only this call's launch status
-    hipLaunchKernelGGL(k_zero, dim3((MLP_N + 255) / 256), dim3(256), 0, st, grad, MLP_N);
-    hipLaunchKernelGGL(k_zero, dim3(1), dim3(64), 0, st, loss, 1);
-    if (n <= 0) return hipGetLastError();
-    const float inv_n = 1.0f / (float)n;
-    for (int64_t c0 = 0; c0 < n; c0 += scr_samples) {
-        const int64_t m = std::min<int64_t>(scr_samples, n - c0);
-        hipLaunchKernelGGL(k_act, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st, feat + c0 * stride, stride,
-                           scale, label + c0, m, pos_weight, inv_n, w, scr, loss);
-        hipLaunchKernelGGL(k_wgrad, dim3((MLP_N + 255) / 256, (unsigned)((m + SPB - 1) / SPB)), dim3(256), 0, st, scr,
-                           m, grad);
-    }
+    // workgroups enough for one 16-sample step per wave, at most one per
+    // compute unit (each ends by writing 19 KB of sums)
+    const int blocks = (int)std::min<int64_t>(GRAD_BLOCKS, (n + 16 * GRAD_WAVES - 1) / (16 * GRAD_WAVES));
+    if (n > 0)
+        hipLaunchKernelGGL(k_grad, dim3(blocks), dim3(64 * GRAD_WAVES), 0, st, feat, stride, scale, label, n, pos_weight,
+                           1.0f / (float)n, w, scr);
+    hipLaunchKernelGGL(k_grad_sum, dim3((MLP_N + 1 + 31) / 32), dim3(256), 0, st, scr, n > 0 ? blocks : 0, grad, loss);
     return hipGetLastError();
 }
 
