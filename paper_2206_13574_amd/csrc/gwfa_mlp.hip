@@ -275,21 +275,89 @@ __global__ void k_cast(const float* __restrict__ src, uint16_t* __restrict__ dst
     if (i < n) dst[i] = f2bf(src[i]);
 }
 
-// Logits of n samples with the alignment kernel's inference routine.
-__global__ __launch_bounds__(256) void k_logits(const float* __restrict__ feat, int64_t stride, Scale8 scale,
+// Logits of n samples: the network of the alignment kernel's inference routine
+// (same products and roundings, the last sums in another order), persistent
+// waves with the weights in registers.  A wave takes 64 samples, one per lane,
+// and scores them 16 at a time.  The weights of layer 1 stand in all four
+// quarters of the product's 32 positions and the samples of tile t in quarter
+// t, so each lane's inputs are its operand as they lie; layer 2 is taken
+// transposed (units by samples), so its inputs are layer 1's outputs and the
+// last sum is 16 products in a lane and two exchanges.
+// 1,000,003 samples: 29 us (36 MB: 1.2 TB/s); with the weights gathered from
+// LDS for every tile and 20 exchanges 81 us.  Bound by the roundings and
+// packing between the layers (about 120 vector instructions per 16 samples).
+__global__ __launch_bounds__(256, 3) void k_logits(const float* __restrict__ feat, int64_t stride, Scale8 scale,
                                                 int64_t n, const uint16_t* __restrict__ w, float* __restrict__ out) {
-    __shared__ __align__(16) uint16_t sw[MLP_N + 7];
-    for (int i = threadIdx.x; i < MLP_N; i += blockDim.x) sw[i] = w[i];
-    __syncthreads();
-    // every lane of the wave takes part in the matrix products
-    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    float f[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (b < n) {
+    const int lane = threadIdx.x & 63, col = lane & 15, grp = lane >> 4;
+    bf16x8 w1a[4], w2a[2][4];
+    f32x4 b1[4], b2[4], w3[4];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) f[i] = feat[b * stride + i];
+    for (int c = 0; c < 4; ++c) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) w1a[c][i] = bf_bits(w[(16 * c + col) * 8 + i]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int j = 16 * c + 4 * grp + i;
+            b1[c][i] = bf2f(w[MW_B1 + j]);
+            b2[c][i] = bf2f(w[MW_B2 + j]);
+            w3[c][i] = bf2f(w[MW_W3 + j]);
+        }
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            const uint16_t* row = w + MW_W2 + (16 * c + col) * 64 + 32 * ks + 4 * grp;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                w2a[ks][c][i] = bf_bits(row[i]);
+                w2a[ks][c][4 + i] = bf_bits(row[16 + i]);
+            }
+        }
     }
-    const float z = mlp_logit_wave(f, scale.s, sw);
-    if (b < n) out[b] = z;
+    const float b3 = bf2f(w[MW_B3]);
+    const bool wide = (stride & 3) == 0 && (reinterpret_cast<uintptr_t>(feat) & 15) == 0;   // rows of 16-byte words
+    const int64_t waves = (int64_t)gridDim.x * 4;
+    for (int64_t g = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); g * 64 < n; g += waves) {
+        const int64_t b = g * 64 + lane;
+        const bool ok = b < n;
+        const float* f = feat + (ok ? b : 0) * stride;
+        float x[8];
+        if (wide) {
+            const float4 lo = *reinterpret_cast<const float4*>(f), hi = *reinterpret_cast<const float4*>(f + 4);
+            x[0] = lo.x; x[1] = lo.y; x[2] = lo.z; x[3] = lo.w;
+            x[4] = hi.x; x[5] = hi.y; x[6] = hi.z; x[7] = hi.w;
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x[i] = f[i];
+        }
+        bf16x8 xp;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) xp[i] = bf_of(round_bf16(x[i] * scale.s[i]));
+        float z_out = 0.0f;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            bf16x8 xb;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) xb[i] = grp == t ? xp[i] : bf_bits(0);
+            bf16x8 h[2];   // units 32ks + 4g + i and 32ks + 16 + 4g + i of sample 16t + m
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const f32x4 d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1a[c], xb, b1[c], 0, 0, 0);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) h[c >> 1][4 * (c & 1) + i] = (__bf16)fmaxf(d[i], 0.0f);
+            }
+            float z = 0.0f;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                f32x4 a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w2a[0][c], h[0], b2[c], 0, 0, 0);
+                a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w2a[1][c], h[1], a, 0, 0, 0);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) z = fmaf(w3[c][i], round_bf16(fmaxf(a[i], 0.0f)), z);
+            }
+            z += __shfl_xor(z, 16, 64);
+            z += __shfl_xor(z, 32, 64);
+            z_out = grp == t ? z + b3 : z_out;
+        }
+        if (ok) out[b] = z_out;
+    }
 }
 
 }  // namespace gwfa_train
@@ -334,7 +402,8 @@ hipError_t gwfa_launch_mlp_logits(const float* feat, int64_t stride, const Scale
                                   const uint16_t* w, float* out, hipStream_t st) {
     if (n <= 0) return hipSuccess;
     (void)hipGetLastError();
-    hipLaunchKernelGGL(gwfa_train::k_logits, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, feat, stride, scale,
-                       n, w, out);
+    // workgroups that fit the chip at once (three a compute unit), fewer for few samples
+    const unsigned blocks = (unsigned)std::min<int64_t>(768, (n + 255) / 256);
+    hipLaunchKernelGGL(gwfa_train::k_logits, dim3(blocks), dim3(256), 0, st, feat, stride, scale, n, w, out);
     return hipGetLastError();
 }
