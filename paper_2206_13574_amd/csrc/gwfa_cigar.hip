@@ -2,20 +2,29 @@
 // graph alignment traced (the last step the paper leaves to a pairwise
 // aligner, noting that it is cheap).
 //
-// One persistent workgroup per query: the walk's string T (the labels of the
-// walk, the first one from start_off, the last one cut at end_off) is
-// spelled into a 2-bit packed buffer,
-// then a pairwise wavefront alignment (the score-ordered diagonal recurrence
-// of Eq. 2 on a single path: mismatch, insertion, deletion, then extension
-// by the exact-match run) finds an optimal global alignment of q and T, and
-// one thread walks the stored wavefronts back into CIGAR operations.
+// One persistent workgroup per query, the largest distances first: the walk's
+// string T (the labels of the walk, the first one from start_off, the last one
+// cut at end_off) is spelled into a 2-bit packed buffer, then a pairwise
+// wavefront alignment (the score-ordered diagonal recurrence of Eq. 2 on a
+// single path: mismatch, insertion, deletion, then extension by the
+// exact-match run) finds an optimal global alignment of q and T, and a
+// traceback turns the stored wavefronts into CIGAR operations.
 //
-// Wavefront s covers diagonals k = j - i in [-s, s] (i query bases, j bases
-// of T consumed) and is stored at offset s*s of the workgroup's buffer, so a
-// distance d needs (d+1)^2 words.  Operation words are (length << 4) | op
-// with op 7 ('=', match), 8 ('X', mismatch), 1 ('I', query base absent from
-// the walk), 2 ('D', walk base absent from the query), 4 ('S', query bases
-// left unaligned by a free end gap in the query), as in SAM/BAM.
+// The cost is at most the query's graph distance D, so wavefront s only needs
+// the diagonals k = j - i (i query bases, j bases of T consumed) that can be
+// reached with s edits and can still reach the end's diagonal with D - s:
+// -s <= k <= s and |k - kend| <= D - s.  That is half of the full triangle,
+// and every diagonal kept has its three sources kept.  Row s is stored at
+// row_at(s) of the workgroup's buffer.
+//
+// Where the packed query, T and two wavefronts fit LDS (k_cigar<.., true>) a
+// score is one pass over LDS and one barrier; each cell's start and source go
+// to memory for the traceback, which reads 8 scores per memory round trip.
+// Longer queries keep them in memory.  Operation words are
+// (length << 4) | op with op 7 ('=', match), 8 ('X', mismatch), 1 ('I', query
+// base absent from the walk), 2 ('D', walk base absent from the query), 4
+// ('S', query bases left unaligned by a free end gap in the query), as in
+// SAM/BAM.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -46,27 +55,64 @@ __device__ int32_t run_len(const ull* __restrict__ q, int64_t qp, const ull* __r
     return l;
 }
 
-// the three sources of diagonal k at score s (Eq. 2 on one path); NEG if absent
-__device__ __forceinline__ void sources(const int32_t* __restrict__ Wp, int32_t sp, int32_t k, int32_t qlen,
+// The diagonals of wavefront s that are kept, and where its row is stored:
+// at most 2 min(s, D - s) + 1 of them, rows packed by that bound.
+struct Band {
+    int32_t D, kend;
+    __device__ __forceinline__ int32_t lo(int32_t s) const { return max(-s, kend - (D - s)); }
+    __device__ __forceinline__ int32_t hi(int32_t s) const { return min(s, kend + (D - s)); }
+    __device__ __forceinline__ int64_t row_at(int32_t s) const {
+        const int64_t h = D / 2, a = s, b = D - (int64_t)s + 1;
+        return a <= h ? a * a : (h + 1) * (h + 1) + (D - h) * (D - h) - b * b;
+    }
+};
+
+// the three sources of diagonal k at the next score (Eq. 2 on one path), from
+// row Wp of the diagonals lo..hi; NEG if absent
+__device__ __forceinline__ void sources(const int32_t* Wp, int32_t lo, int32_t hi, int32_t k, int32_t qlen,
                                         int32_t tlen, int32_t& mis, int32_t& ins, int32_t& del) {
     mis = ins = del = NEG;
-    if (k >= -sp && k <= sp) {                    // mismatch: (i, j) -> (i+1, j+1)
-        const int32_t i0 = Wp[k + sp];
+    if (k >= lo && k <= hi) {                     // mismatch: (i, j) -> (i+1, j+1)
+        const int32_t i0 = Wp[k - lo];
         if (i0 >= 0 && i0 < qlen && i0 + k < tlen) mis = i0 + 1;
     }
-    if (k + 1 >= -sp && k + 1 <= sp) {            // query base alone: (i, j) -> (i+1, j), from k+1
-        const int32_t i1 = Wp[k + 1 + sp];
+    if (k + 1 >= lo && k + 1 <= hi) {             // query base alone: (i, j) -> (i+1, j), from k+1
+        const int32_t i1 = Wp[k + 1 - lo];
         if (i1 >= 0 && i1 < qlen) ins = i1 + 1;
     }
-    if (k - 1 >= -sp && k - 1 <= sp) {            // walk base alone: (i, j) -> (i, j+1), from k-1
-        const int32_t i2 = Wp[k - 1 + sp];
+    if (k - 1 >= lo && k - 1 <= hi) {             // walk base alone: (i, j) -> (i, j+1), from k-1
+        const int32_t i2 = Wp[k - 1 - lo];
         if (i2 >= 0 && i2 + k - 1 < tlen) del = i2;
     }
 }
 
+// The operations of one query, from the end: run-length merged in registers,
+// each finished one stored by lane 0.
+struct Ops {
+    uint32_t* out;
+    int32_t n = 0;           // stored
+    uint32_t op = 0;
+    int32_t len = 0;         // the run being built
+    __device__ __forceinline__ void emit(uint32_t o, int32_t l) {
+        if (l <= 0) return;
+        if (o != op) flush();
+        op = o;
+        len += l;
+    }
+    __device__ __forceinline__ void flush() {
+        if (len > 0) {
+            if (threadIdx.x == 0) out[n] = ((uint32_t)len << 4) | op;
+            ++n;
+            len = 0;
+        }
+    }
+};
+
 struct Shared {
     int32_t read;
-    int32_t done;
+    int32_t done[2];         // by parity of the score, so that one barrier a score is enough
+    int32_t n_ops;
+    int64_t pos;
     int32_t scan[16];
     int64_t carry;
 };
@@ -94,33 +140,52 @@ __device__ __forceinline__ UniRes load_res(const gwfa_result* p) {
     return u;
 }
 
+// Barrier for phases that exchange only LDS data (stores to memory stay in
+// flight).
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
 // Persistent loop over the queries.  No query leaves the loop body early
 // (no continue, no return): a per-query exit in front of the queue fetch
 // (thread 0's atomic, then a barrier) lets the compiler send the other lanes
 // straight back to that barrier while thread 0 waits outside the loop, and
 // the workgroup never fetches again.  Every branch that decides the loop's
 // course is on values the whole workgroup shares (scalar registers).
-template <int BLOCK>
+//
+// 4,001 reads of 8 kb (1-8% errors): 4.4 ms, bound by the scores of its hardest
+// query (LDS latency and a barrier each); 28.7 ms before, with the full
+// triangle, rows, query and T in memory, two barriers a score and one thread
+// tracing back with read-modify-writes of its operations.
+template <int BLOCK, bool LDS>
 __global__ __launch_bounds__(BLOCK) void k_cigar(CigArgs A) {
     __shared__ Shared S;
+    extern __shared__ ull dyn[];
     char* arena = A.arena + (int64_t)blockIdx.x * A.arena_stride;
-    ull* T = reinterpret_cast<ull*>(arena);
+    ull* const Tg = reinterpret_cast<ull*>(arena);
     int64_t* P = reinterpret_cast<int64_t*>(arena + A.o_pref);
     int32_t* W = reinterpret_cast<int32_t*>(arena + A.o_wf);
     uint32_t* ops = reinterpret_cast<uint32_t*>(arena + A.o_ops);
+    // LDS: query, T, two rows
+    ull* const Ql = dyn;
+    ull* const Tl = Ql + A.lds_q;
+    int32_t* const rows = reinterpret_cast<int32_t*>(Tl + A.lds_t);
     const int tid = threadIdx.x;
     for (;;) {
         if (tid == 0) S.read = atomicAdd(A.queue, 1);
         __syncthreads();
-        const int r = __builtin_amdgcn_readfirstlane(S.read);
+        const int ri = __builtin_amdgcn_readfirstlane(S.read);
         __syncthreads();
-        if (r >= A.n_reads) break;
+        if (ri >= A.n_reads) break;
+        const int r = __builtin_amdgcn_readfirstlane(A.order[ri]);
         const UniRes res = load_res(A.res + r);
         const int64_t q0 = uni64(A.rd_off[r]);
         const int32_t qfull = __builtin_amdgcn_readfirstlane((int32_t)(A.rd_off[r + 1] - q0));
         // the graph alignment covers q[0, qfull - clip); the rest is soft-clipped
         const int32_t qlen = qfull - res.clip;
-        const bool usable = res.status == GWFA_ST_OK && res.path_off >= 0 && res.path_len > 0 &&
+        const bool usable = res.status == GWFA_ST_OK && res.path_off >= 0 && res.path_len > 0 && res.dist >= 0 &&
                             res.dist <= A.max_d && qfull <= A.max_q && res.start_off >= 0 && res.clip >= 0 &&
                             qlen >= 0;
         if (!usable) {
@@ -165,6 +230,13 @@ __global__ __launch_bounds__(BLOCK) void k_cigar(CigArgs A) {
                 if (tid == 0) { A.cigar_off[r] = -1; A.cigar_len[r] = -3; }
             } else {
                 const int32_t tlen = (int32_t)tlen64;
+                const ull* const qw = LDS ? Ql : A.rd;
+                const int64_t qb = LDS ? (q0 & 31) : q0;   // the query's first base in qw
+                ull* const T = LDS ? Tl : Tg;
+                if (LDS) {
+                    const int32_t w0 = (int32_t)((qb + qlen) >> 5) + 2;
+                    for (int32_t w = tid; w < w0; w += BLOCK) Ql[w] = A.rd[(q0 >> 5) + w];
+                }
                 // ---- spell T, 2-bit packed, 32 bases per word, plus two zero words
                 const int32_t tw = tlen / 32 + 2;
                 for (int32_t w = tid; w < tw; w += BLOCK) {
@@ -177,80 +249,114 @@ __global__ __launch_bounds__(BLOCK) void k_cigar(CigArgs A) {
                             if (P[mid] <= p) lo = mid; else hi = mid - 1;
                         }
                         int32_t j = lo;
-                        for (int b = 0; b < 32 && p < tlen; ++b, ++p) {
+                        for (int b = 0; b < 32 && p < tlen;) {
                             while (j + 1 < L && P[j + 1] <= p) ++j;
                             const int64_t g = A.seg_off[walk[j]] + (j == 0 ? j0 : 0) + (p - P[j]);
-                            const ull c = (A.seg[g >> 5] >> (62 - 2 * (g & 31))) & 3ull;
-                            word |= c << (62 - 2 * b);
+                            const int n = (int)min((int64_t)(32 - b), P[j + 1] - p);   // bases of this vertex
+                            ull x = win32(A.seg, g);
+                            if (n < 32) x &= ~(~0ull >> (2 * n));
+                            word |= x >> (2 * b);
+                            b += n;
+                            p += n;
                         }
                     }
                     T[w] = word;
                 }
+                const int32_t kend = tlen - qlen;
+                const Band B{res.dist, kend};
+                if (tid == 0) S.done[0] = S.done[1] = -1;
                 __syncthreads();
                 // ---- wavefronts
-                const int32_t kend = tlen - qlen;
-                if (tid == 0) {
-                    const int32_t l = run_len(A.rd, q0, T, 0, min(qlen, tlen));
-                    W[0] = l;
-                    S.done = (kend == 0 && l == qlen) ? 0 : -1;
-                }
-                __syncthreads();
-                int32_t done = __builtin_amdgcn_readfirstlane(S.done);
-                __syncthreads();
-                int32_t s = 0;
-                while (done < 0 && s < A.max_d) {
-                    ++s;
-                    const int32_t* Wp = W + (int64_t)(s - 1) * (s - 1);
-                    int32_t* Ws = W + (int64_t)s * s;
-                    for (int32_t k = -s + tid; k <= s; k += BLOCK) {
-                        int32_t mis, ins, del;
-                        sources(Wp, s - 1, k, qlen, tlen, mis, ins, del);
-                        int32_t i = max(mis, max(ins, del));
-                        if (i >= 0) i += run_len(A.rd, q0 + i, T, (int64_t)i + k, min(qlen - i, tlen - i - k));
-                        Ws[k + s] = i < 0 ? NEG : i;
-                        if (k == kend && i == qlen) S.done = s;
+                // (a cost of at most D implies |kend| <= D)
+                int32_t s = 0, done = -1;
+                if (kend >= -B.D && kend <= B.D) {
+                    const int32_t l = run_len(qw, qb, T, 0, min(qlen, tlen));   // by every thread: one value
+                    if (tid == 0) {
+                        if (LDS) rows[0] = l; else W[0] = l;
                     }
-                    // every thread reads the flag between two barriers, so all take
-                    // the same decision before anyone can set it again
-                    __syncthreads();
-                    done = __builtin_amdgcn_readfirstlane(S.done);
-                    __syncthreads();
-                }
-                const int32_t dd = done;
-                if (tid == 0) {
-                    if (dd < 0) {
-                        A.cigar_off[r] = -1;
-                        A.cigar_len[r] = -3;
-                    } else {
-                        // ---- traceback: operations from the end, run-length merged
-                        int32_t n = 0;
-                        auto emit = [&](uint32_t op, int32_t len) {
-                            if (len <= 0) return;
-                            if (n > 0 && (ops[n - 1] & 15u) == op) ops[n - 1] += (uint32_t)len << 4;
-                            else ops[n++] = ((uint32_t)len << 4) | op;
-                        };
-                        emit(OP_S, qfull - qlen);
-                        int32_t k = kend, i = qlen;
-                        for (int32_t ss = dd; ss > 0; --ss) {
+                    done = __builtin_amdgcn_readfirstlane((kend == 0 && l == qlen) ? 0 : -1);
+                    if (LDS) lds_barrier(); else __syncthreads();
+                    while (done < 0 && s < B.D) {
+                        ++s;
+                        const int32_t plo = B.lo(s - 1), phi = B.hi(s - 1), lo = B.lo(s), hi = B.hi(s);
+                        int32_t* const Wg = W + B.row_at(s);
+                        const int32_t* const Wp = LDS ? rows + ((s - 1) & 1) * A.lds_row : W + B.row_at(s - 1);
+                        int32_t* const Ws = LDS ? rows + (s & 1) * A.lds_row : Wg;
+                        for (int32_t k = lo + tid; k <= hi; k += BLOCK) {
                             int32_t mis, ins, del;
-                            sources(W + (int64_t)(ss - 1) * (ss - 1), ss - 1, k, qlen, tlen, mis, ins, del);
+                            sources(Wp, plo, phi, k, qlen, tlen, mis, ins, del);
                             const int32_t v = max(mis, max(ins, del));
-                            emit(OP_EQ, i - v);
-                            if (mis == v) { emit(OP_X, 1); i = v - 1; }
-                            else if (ins == v) { emit(OP_I, 1); i = v - 1; k += 1; }
-                            else { emit(OP_D, 1); i = v; k -= 1; }
+                            int32_t i = v;
+                            if (v >= 0) i += run_len(qw, qb + v, T, (int64_t)v + k, min(qlen - v, tlen - v - k));
+                            Ws[k - lo] = v < 0 ? NEG : i;
+                            // for the traceback: where the cell's run starts and its source
+                            if (LDS) Wg[k - lo] = (v << 2) | (mis == v ? 0 : (ins == v ? 1 : 2));
+                            if (k == kend && i == qlen) S.done[s & 1] = s;
                         }
-                        emit(OP_EQ, i);
-                        // reverse into the output
-                        const ull pos = atomicAdd(A.cigar_cursor, (ull)n);
-                        if ((int64_t)pos + n <= A.cigar_cap) {
-                            for (int32_t x = 0; x < n; ++x) A.cigar[pos + x] = ops[n - 1 - x];
-                            A.cigar_off[r] = (int64_t)pos;
-                            A.cigar_len[r] = n;
+                        if (LDS) lds_barrier(); else __syncthreads();
+                        done = __builtin_amdgcn_readfirstlane(S.done[s & 1]);
+                    }
+                }
+                __syncthreads();   // the rows are in memory
+                if (done < 0) {
+                    if (tid == 0) { A.cigar_off[r] = -1; A.cigar_len[r] = -3; }
+                } else {
+                    // ---- traceback, by wave 0: operations from the end, run-length merged
+                    if (tid < 64) {
+                        Ops o{ops};
+                        o.emit(OP_S, qfull - qlen);
+                        int32_t k = kend, i = qlen, ss = done;
+                        if (LDS) {
+                            // lane l holds the cell at score ss - x, x = floor(sqrt(l)), diagonal
+                            // k + l - x(x+1): every cell the next eight steps can reach
+                            const int x = (tid >= 1) + (tid >= 4) + (tid >= 9) + (tid >= 16) + (tid >= 25) + (tid >= 36) +
+                                          (tid >= 49);
+                            const int dk = tid - x * (x + 1);
+                            while (ss > 0) {
+                                int32_t c = 0;
+                                const int32_t sx = ss - x, kx = k + dk;
+                                if (sx > 0 && kx >= B.lo(sx) && kx <= B.hi(sx)) c = W[B.row_at(sx) + kx - B.lo(sx)];
+                                const int32_t k0 = k;
+                                const int steps = min(ss, 8);
+                                for (int y = 0; y < steps; ++y) {
+                                    const int32_t cell = __builtin_amdgcn_readlane(c, y * (y + 1) + k - k0);
+                                    const int32_t v = cell >> 2, op = cell & 3;
+                                    o.emit(OP_EQ, i - v);
+                                    if (op == 0) { o.emit(OP_X, 1); i = v - 1; }
+                                    else if (op == 1) { o.emit(OP_I, 1); i = v - 1; k += 1; }
+                                    else { o.emit(OP_D, 1); i = v; k -= 1; }
+                                }
+                                ss -= steps;
+                            }
                         } else {
-                            A.cigar_off[r] = -1;
-                            A.cigar_len[r] = -2;
+                            for (; ss > 0; --ss) {
+                                int32_t mis, ins, del;
+                                sources(W + B.row_at(ss - 1), B.lo(ss - 1), B.hi(ss - 1), k, qlen, tlen, mis, ins, del);
+                                const int32_t v = __builtin_amdgcn_readfirstlane(max(mis, max(ins, del)));
+                                const int op = __builtin_amdgcn_readfirstlane(mis == v ? 0 : (ins == v ? 1 : 2));
+                                o.emit(OP_EQ, i - v);
+                                if (op == 0) { o.emit(OP_X, 1); i = v - 1; }
+                                else if (op == 1) { o.emit(OP_I, 1); i = v - 1; k += 1; }
+                                else { o.emit(OP_D, 1); i = v; k -= 1; }
+                            }
                         }
+                        o.emit(OP_EQ, i);
+                        o.flush();
+                        if (tid == 0) {
+                            S.n_ops = o.n;
+                            S.pos = (int64_t)atomicAdd(A.cigar_cursor, (ull)o.n);
+                        }
+                    }
+                    __syncthreads();
+                    // ---- reversed into the output
+                    const int32_t n = __builtin_amdgcn_readfirstlane(S.n_ops);
+                    const int64_t pos = uni64(S.pos);
+                    const bool fits = pos + n <= A.cigar_cap;
+                    if (fits)
+                        for (int32_t x = tid; x < n; x += BLOCK) A.cigar[pos + x] = ops[n - 1 - x];
+                    if (tid == 0) {
+                        A.cigar_off[r] = fits ? pos : -1;
+                        A.cigar_len[r] = fits ? n : -2;
                     }
                 }
             }
@@ -265,9 +371,28 @@ __global__ void k_cig_reset(int32_t* queue, ull* cursor) {
 
 }  // namespace gwfa_cig
 
-hipError_t gwfa_launch_cigar(const CigArgs& A, int groups, hipStream_t st) {
+// words of a workgroup's wavefront rows for distances up to d (Band::row_at)
+int64_t gwfa_cigar_row_words(int64_t d) {
+    const int64_t h = d / 2;
+    return (h + 1) * (h + 1) + (d - h) * (d - h);
+}
+
+int64_t gwfa_cigar_lds_bytes(const CigArgs& A) { return 8 * ((int64_t)A.lds_q + A.lds_t) + 2 * 4 * (int64_t)A.lds_row; }
+
+hipError_t gwfa_launch_cigar(const CigArgs& A, int groups, int lanes, int lds_bytes, hipStream_t st) {
+    using namespace gwfa_cig;
     (void)hipGetLastError();
-    hipLaunchKernelGGL(gwfa_cig::k_cig_reset, dim3(1), dim3(64), 0, st, A.queue, A.cigar_cursor);
-    hipLaunchKernelGGL(gwfa_cig::k_cigar<256>, dim3(groups), dim3(256), 0, st, A);
+    hipLaunchKernelGGL(k_cig_reset, dim3(1), dim3(64), 0, st, A.queue, A.cigar_cursor);
+    if (lds_bytes > 0) {
+        const void* f = lanes == 512 ? (const void*)k_cigar<512, true> : (const void*)k_cigar<256, true>;
+        if (lds_bytes > 48 << 10) {
+            const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+            if (e != hipSuccess) return e;
+        }
+        if (lanes == 512) hipLaunchKernelGGL((k_cigar<512, true>), dim3(groups), dim3(512), lds_bytes, st, A);
+        else hipLaunchKernelGGL((k_cigar<256, true>), dim3(groups), dim3(256), lds_bytes, st, A);
+    } else {
+        hipLaunchKernelGGL((k_cigar<256, false>), dim3(groups), dim3(256), 0, st, A);
+    }
     return hipGetLastError();
 }

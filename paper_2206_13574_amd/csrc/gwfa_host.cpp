@@ -40,6 +40,13 @@ struct Tier {
     int64_t o_hdr = 0, o_dir = 0, o_pages = 0, o_mkey = 0, o_tv = 0, o_tt = 0, o_lists = 0, o_cand = 0, o_sort = 0;
 };
 
+// Base-level alignment: most dynamic LDS of a workgroup (two fit a compute
+// unit), and the distance from which a workgroup has 512 lanes: the call then
+// waits for its hardest query, whose rows are two passes or more of 512 (4,001
+// reads with distances up to 3,000: 6.9 ms, 8.9 with 256).
+constexpr int64_t CIG_LDS_MAX = 78 << 10;
+constexpr int64_t CIG_WIDE_D = 1024;
+
 int64_t align_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 
 // One arena per persistent workgroup: header (generation counter), page
@@ -89,6 +96,9 @@ struct gwfa_ctx {
     char* d_cig_arena = nullptr;       // base-level alignment: per-workgroup regions
     size_t cig_bytes = 0;
     int32_t* d_cig_queue = nullptr;
+    int32_t* d_cig_order = nullptr;    // queries by distance, and its host copy (kept for the asynchronous copy)
+    std::vector<int32_t> cig_order;
+    int64_t cig_order_cap = 0;
     int n_cu = 256;
     int exact_per_cu[4] = {0, 0, 0, 0}; // resident workgroups of 64 << i lanes per compute unit, exact mode
     char* static_base = nullptr;       // the device's static working memory (gwfa_align_batch_static_dev)
@@ -281,6 +291,7 @@ void gwfa_ctx_destroy(gwfa_ctx* c) {
     if (c->d_mlp_scr) (void)hipFree(c->d_mlp_scr);
     if (c->d_cig_arena) (void)hipFree(c->d_cig_arena);
     if (c->d_cig_queue) (void)hipFree(c->d_cig_queue);
+    if (c->d_cig_order) (void)hipFree(c->d_cig_order);
     if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
     delete c;
 }
@@ -883,10 +894,20 @@ int gwfa_cigar_dev(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const ui
     memset(&A, 0, sizeof(A));
     A.o_pref = align_up((max_t / 32 + 3) * 8, 256);
     A.o_wf = A.o_pref + align_up((max_path + 2) * 8, 256);
-    A.o_ops = A.o_wf + align_up((max_d + 1) * (max_d + 1) * 4, 256);
+    A.o_ops = A.o_wf + align_up(gwfa_cigar_row_words(max_d) * 4, 256);
     A.arena_stride = A.o_ops + align_up((2 * max_d + 4) * 4, 4096);
-    // as many workgroups as fit in a 16 GiB region, at most two per compute unit
-    int64_t groups = std::min<int64_t>(std::max<int64_t>(n_ok, 1), (int64_t)ctx->n_cu * 2);
+    // The variant with query, T and rows in LDS where they leave room for two
+    // workgroups on a compute unit; 512 lanes where rows are wide (a row has up
+    // to max_d + 1 cells).
+    A.lds_q = (int32_t)std::min<int64_t>(max_q / 32 + 4, 1 << 20);
+    A.lds_t = (int32_t)std::min<int64_t>(max_t / 32 + 4, 1 << 20);
+    A.lds_row = (int32_t)(max_d + 2) & ~1;
+    int64_t lds = gwfa_cigar_lds_bytes(A);
+    if (lds > CIG_LDS_MAX) lds = 0;
+    const int lanes = lds > 0 && max_d >= CIG_WIDE_D ? 512 : 256;
+    // as many workgroups as fit in a 16 GiB region and on the device at once
+    const int64_t per_cu = lds > 0 ? std::max<int64_t>(1, std::min<int64_t>(2048 / lanes, ((int64_t)160 << 10) / (lds + 512))) : 8;
+    int64_t groups = std::min<int64_t>(std::max<int64_t>(n_ok, 1), (int64_t)ctx->n_cu * per_cu);
     groups = std::max<int64_t>(1, std::min<int64_t>(groups, ((int64_t)16 << 30) / A.arena_stride));
     const size_t need = (size_t)(A.arena_stride * groups);
     if (need > ctx->cig_bytes) {
@@ -903,6 +924,31 @@ int gwfa_cigar_dev(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const ui
         ctx->d_cig_queue = nullptr;
         return GWFA_ERR_NOMEM;
     }
+    // the largest distances first (a counting sort: distances are small)
+    if (ctx->cig_order_cap < n_reads) {
+        if (ctx->d_cig_order) (void)hipFree(ctx->d_cig_order);
+        ctx->d_cig_order = nullptr;
+        ctx->cig_order_cap = 0;
+        if (hipMalloc((void**)&ctx->d_cig_order, (size_t)n_reads * 4) != hipSuccess) {
+            ctx->d_cig_order = nullptr;
+            return GWFA_ERR_NOMEM;
+        }
+        ctx->cig_order_cap = n_reads;
+    }
+    {
+        auto key = [&](int32_t r) {   // 0: the largest distance; the last: no walk
+            const gwfa_result& x = res[r];
+            const bool ok = x.status == GWFA_ST_OK && x.path_off >= 0 && x.path_len > 0 && x.dist >= 0;
+            return ok ? max_d - x.dist : max_d + 1;
+        };
+        std::vector<int32_t> at((size_t)max_d + 3, 0);
+        for (int32_t r = 0; r < n_reads; ++r) at[key(r) + 1]++;
+        for (int64_t d = 0; d <= max_d + 1; ++d) at[d + 1] += at[d];
+        ctx->cig_order.resize((size_t)n_reads);
+        for (int32_t r = 0; r < n_reads; ++r) ctx->cig_order[at[key(r)]++] = r;
+    }
+    HIPCHK(ctx, hipMemcpyAsync(ctx->d_cig_order, ctx->cig_order.data(), (size_t)n_reads * 4, hipMemcpyHostToDevice, st));
+    A.order = ctx->d_cig_order;
     A.seg = g->d_seg; A.seg_off = g->d_seg_off;
     A.rd = (const unsigned long long*)d_packed; A.rd_off = d_read_off; A.n_reads = n_reads;
     A.res = d_res; A.path_buf = d_path_buf;
@@ -912,7 +958,7 @@ int gwfa_cigar_dev(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const ui
     A.queue = ctx->d_cig_queue;
     A.arena = ctx->d_cig_arena;
     A.max_d = (int32_t)max_d; A.max_q = (int32_t)max_q; A.max_t = (int32_t)max_t;
-    HIPCHK(ctx, gwfa_launch_cigar(A, (int)groups, st));
+    HIPCHK(ctx, gwfa_launch_cigar(A, (int)groups, lanes, (int)lds, st));
     return GWFA_OK;
 }
 

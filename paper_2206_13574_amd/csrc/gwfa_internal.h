@@ -120,5 +120,10 @@ struct CigArgs {
     char* arena;                     // one region per workgroup
     int64_t arena_stride, o_pref, o_wf, o_ops;
     int32_t max_d, max_q, max_t;     // capacities of the regions
+    const int32_t* order;            // queries, the largest distances first
+    int32_t lds_q, lds_t, lds_row;   // LDS words of the query and of T (64 bits), entries of a wavefront row
 };
-hipError_t gwfa_launch_cigar(const CigArgs& A, int groups, hipStream_t st);
+int64_t gwfa_cigar_row_words(int64_t d);
+int64_t gwfa_cigar_lds_bytes(const CigArgs& A);
+// lds_bytes: dynamic LDS of the variant that keeps queries there, 0 for the other
+hipError_t gwfa_launch_cigar(const CigArgs& A, int groups, int lanes, int lds_bytes, hipStream_t st);

@@ -48,8 +48,9 @@ __device__ __forceinline__ float sigmoid(float z) {
 // its whole gradient in registers over its samples; the waves of a workgroup
 // are added in LDS and the workgroups by k_grad_sum, without atomics and in
 // a fixed order.
-// 32,768 samples: 17 us, bound by the waves' chain of steps (two per wave), the
-// matrix work being 4 us; one thread per sample and per parameter took 300 us.
+// 32,768 samples: about 27 us, bound by the waves' chain of steps (two per wave,
+// then the sum in LDS), the matrix work being 4 us; one thread per sample and
+// per parameter took 300 us.
 __global__ __launch_bounds__(64 * GRAD_WAVES, 1) void k_grad(const float* __restrict__ feat, int64_t stride,
                                                              Scale8 scale, const uint8_t* __restrict__ label, int64_t n,
                                                              float pos_weight, float inv_n,
