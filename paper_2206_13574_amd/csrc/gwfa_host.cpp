@@ -84,8 +84,7 @@ struct gwfa_ctx {
     int32_t* d_retry_count = nullptr;
     unsigned long long* d_stats = nullptr;
     int32_t* d_retry[2] = {nullptr, nullptr};
-    int32_t* d_valid = nullptr;        // queries that passed the screen pass, in work-queue order
-    int32_t* d_valid_n = nullptr;
+    int32_t* d_valid = nullptr;        // the work queue's list, from the screen pass
     int64_t retry_cap = 0;
     int64_t rerun_total = 0;
     uint16_t* d_mlp = nullptr;
@@ -258,10 +257,9 @@ int gwfa_ctx_create(int device, void* hip_stream, gwfa_ctx** out) {
     // stream of the device (e.g. the default stream of a framework)
     c->stream = (hipStream_t)hip_stream;
     c->own_stream = false;
-    bool ok = hipMalloc((void**)&c->d_queue, sizeof(int32_t)) == hipSuccess &&
+    bool ok = hipMalloc((void**)&c->d_queue, Q_SLOTS * Q_STRIDE * sizeof(int32_t)) == hipSuccess &&
               hipMalloc((void**)&c->d_cursor, sizeof(unsigned long long)) == hipSuccess &&
               hipMalloc((void**)&c->d_retry_count, sizeof(int32_t)) == hipSuccess &&
-              hipMalloc((void**)&c->d_valid_n, sizeof(int32_t)) == hipSuccess &&
               hipMalloc((void**)&c->d_stats, STAT_SLOTS * 16 * sizeof(unsigned long long)) == hipSuccess;
     if (ok) ok = hipMemset(c->d_stats, 0, STAT_SLOTS * 16 * sizeof(unsigned long long)) == hipSuccess &&
                  hipDeviceSynchronize() == hipSuccess;
@@ -285,7 +283,6 @@ void gwfa_ctx_destroy(gwfa_ctx* c) {
     if (c->d_stats) (void)hipFree(c->d_stats);
     for (auto p : c->d_retry) if (p) (void)hipFree(p);
     if (c->d_valid) (void)hipFree(c->d_valid);
-    if (c->d_valid_n) (void)hipFree(c->d_valid_n);
     if (c->d_mlp) (void)hipFree(c->d_mlp);
     if (c->d_mlp_scale) (void)hipFree(c->d_mlp_scale);
     if (c->d_mlp_scr) (void)hipFree(c->d_mlp_scr);
@@ -513,12 +510,11 @@ static int launch_lanes(const gwfa_ctx* ctx, const KArgs& A, int64_t n) {
 }
 
 // Working memory of tier ti into A; returns the workgroups to launch.
-static int set_tier(gwfa_ctx* ctx, KArgs& A, int ti, const int32_t* order, int32_t n, const int32_t* n_valid,
-                    int* groups) {
+static int set_tier(gwfa_ctx* ctx, KArgs& A, int ti, const int32_t* order, int32_t n, int* groups) {
     int rc = ensure_tier(ctx, ti);
     if (rc) return rc;
     const Tier& t = ctx->tier[ti];
-    A.order = order; A.n_reads = n; A.n_valid = n_valid; A.tier = ti;
+    A.order = order; A.n_reads = n; A.tier = ti;
     A.retry = (ti + 1 < N_TIERS) ? ctx->d_retry[ti & 1] : nullptr;
     A.arena = t.arena; A.arena_stride = t.stride;
     A.dir_log2_max = t.dir_log2_max; A.list_cap = t.list_cap; A.cand_cap = t.cand_cap; A.sort_cap = t.sort_cap;
@@ -532,15 +528,14 @@ static int set_tier(gwfa_ctx* ctx, KArgs& A, int ti, const int32_t* order, int32
 // Tiers ti0, ti0+1, ...: after each launch the queries that overflowed
 // their working memory (if any) are re-run on the next, larger tier.  When
 // `launched` the launch of tier ti0 has already been issued.  The first
-// tier takes the queries the screen pass listed (ctx->d_valid, their number
-// on the device); a re-run takes the retry list of the tier before.
+// tier takes the queries the screen pass listed (ctx->d_valid); a re-run takes
+// the retry list of the tier before.
 static int run_tiers(gwfa_ctx* ctx, KArgs& A, int ti0, int32_t n, bool launched, hipStream_t st) {
     const int32_t* order = ctx->d_valid;
-    const int32_t* n_valid = ctx->d_valid_n;
     for (int ti = ti0; ti < N_TIERS; ++ti) {
         if (!(launched && ti == ti0)) {
             int groups = 0;
-            int rc = set_tier(ctx, A, ti, order, n, n_valid, &groups);
+            int rc = set_tier(ctx, A, ti, order, n, &groups);
             if (rc) return rc;
             HIPCHK(ctx, gwfa_launch_align(A, launch_lanes(ctx, A, n), groups, st));
         }
@@ -552,7 +547,6 @@ static int run_tiers(gwfa_ctx* ctx, KArgs& A, int ti0, int32_t n, bool launched,
         ctx->rerun_total += h_retry;
         order = ctx->d_retry[ti & 1];
         n = h_retry;
-        n_valid = nullptr;
         // reset the queue and the retry counter, keep the path cursor and the dump counter
         HIPCHK(ctx, gwfa_launch_reset(ctx->d_queue, nullptr, ctx->d_retry_count, nullptr, st));
     }
@@ -575,10 +569,9 @@ static int align_dev(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const 
     A.v_off = d_start_off;
     A.v_off_hi = d_start_hi;
     hipStream_t st = hip_stream ? (hipStream_t)hip_stream : ctx->stream;
-    HIPCHK(ctx, gwfa_launch_reset(ctx->d_queue, A.path_cursor, ctx->d_retry_count, A.dump_count, st));
     A.order = d_order;
     A.n_reads = n_reads;
-    HIPCHK(ctx, gwfa_launch_screen(A, ctx->d_valid, ctx->d_valid_n, st));
+    HIPCHK(ctx, gwfa_launch_screen(A, ctx->d_valid, st));
     return run_tiers(ctx, A, first_tier(A), n_reads, false, st);
 }
 
@@ -640,9 +633,8 @@ int gwfa_align_batch_static_dev(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_re
     if (rc || n_reads == 0) return rc;
     // layout of the static array: header, screened list, one tier of arenas
     char* base = ctx->static_base;
-    int32_t* queue = reinterpret_cast<int32_t*>(base);
-    int32_t* retry_count = queue + 1;
-    int32_t* n_valid = queue + 2;
+    int32_t* retry_count = reinterpret_cast<int32_t*>(base);
+    int32_t* queue = reinterpret_cast<int32_t*>(base + STATIC_QUEUE);
     unsigned long long* cursor = reinterpret_cast<unsigned long long*>(base + 64);
     int32_t* valid = reinterpret_cast<int32_t*>(base + STATIC_HDR);
     const int64_t o_arenas = align_up(STATIC_HDR + (int64_t)STATIC_MAX_READS * 4, 4096);
@@ -660,11 +652,10 @@ int gwfa_align_batch_static_dev(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_re
     A.retry_count = retry_count;
     A.retry = nullptr;   // one tier: a query that overflows it keeps GWFA_ST_ARENA
     if (!d_path_used) A.path_cursor = cursor;
-    HIPCHK(ctx, gwfa_launch_reset(queue, A.path_cursor, retry_count, nullptr, st));
     A.order = d_order;
     A.n_reads = n_reads;
-    HIPCHK(ctx, gwfa_launch_screen(A, valid, n_valid, st));
-    A.order = valid; A.n_valid = n_valid; A.tier = 0;
+    HIPCHK(ctx, gwfa_launch_screen(A, valid, st));
+    A.order = valid; A.tier = 0;
     A.arena = base + o_arenas; A.arena_stride = t.stride;
     A.dir_log2_max = t.dir_log2_max; A.list_cap = t.list_cap; A.cand_cap = t.cand_cap; A.sort_cap = t.sort_cap;
     A.o_hdr = t.o_hdr; A.o_dir = t.o_dir; A.o_pages = t.o_pages; A.o_mkey = t.o_mkey;
@@ -714,16 +705,15 @@ int gwfa_plan_create(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const 
     KArgs S0 = p->A;   // the screen pass reads the caller's order
     S0.order = d_order;
     S0.n_reads = n_reads;
-    if (!rc) rc = set_tier(ctx, p->A, first_tier(p->A), ctx->d_valid, n_reads, ctx->d_valid_n, &groups);   // allocates before the capture
+    if (!rc) rc = set_tier(ctx, p->A, first_tier(p->A), ctx->d_valid, n_reads, &groups);   // allocates before the capture
     if (rc) { gwfa_plan_destroy(p); return rc; }
     p->epoch = ctx->epoch;   // after any reallocation of the context's lists
     hipError_t e = hipStreamCreateWithFlags(&p->cap, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipStreamBeginCapture(p->cap, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
-        // kernels only (no memset nodes): reset of the queue and counters, the
-        // screen pass, then the first tier
-        hipError_t e1 = gwfa_launch_reset(ctx->d_queue, p->A.path_cursor, ctx->d_retry_count, nullptr, p->cap);
-        if (e1 == hipSuccess) e1 = gwfa_launch_screen(S0, ctx->d_valid, ctx->d_valid_n, p->cap);
+        // kernels only (no memset nodes): the screen pass (which resets the
+        // queue and the counters), then the first tier
+        hipError_t e1 = gwfa_launch_screen(S0, ctx->d_valid, p->cap);
         if (e1 == hipSuccess) e1 = gwfa_launch_align(p->A, launch_lanes(ctx, p->A, n_reads), groups, p->cap);
         e = hipStreamEndCapture(p->cap, &p->graph);
         if (e1 != hipSuccess) e = e1;

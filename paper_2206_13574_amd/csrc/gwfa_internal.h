@@ -7,6 +7,8 @@
 
 // Counters are kept on several lines, summed when they are read.
 constexpr int STAT_SLOTS = 64;
+// Counters of the work queue, on lines of their own.
+constexpr int Q_SLOTS = 8, Q_STRIDE = 32;
 
 struct KArgs {
     // graph (device)
@@ -23,8 +25,7 @@ struct KArgs {
     const int32_t* v_start;
     const int32_t* v_off;            // per-query start offsets in the start vertex, or null (all 0)
     const int32_t* v_off_hi;         // per-query end of a free start window, or null (= v_off)
-    const int32_t* order;            // work-queue order or null
-    const int32_t* n_valid;          // queries in `order` (written by the screen pass), or null: n_reads
+    const int32_t* order;            // work-queue order (-1: no query) or null
     const int32_t* v_end;            // per-query end vertices (global form) or null
     int32_t end_vertex;              // end vertex of every query (global form) or -1
     int32_t n_reads;
@@ -33,7 +34,7 @@ struct KArgs {
     int32_t* path_buf;
     int64_t path_cap;
     unsigned long long* path_cursor;
-    int32_t* queue;
+    int32_t* queue;                  // Q_SLOTS counters, Q_STRIDE apart
     unsigned long long* stats;       // STAT_SLOTS lines of 16 counters, or null
     int32_t* retry;                  // queries that overflowed (or null)
     int32_t* retry_count;
@@ -78,15 +79,16 @@ constexpr int64_t STATIC_BYTES = (int64_t)512 << 20;
 constexpr int32_t STATIC_MAX_READS = 1 << 20;
 constexpr int32_t STATIC_DIR_LOG2 = 14;
 constexpr int32_t STATIC_LIST_CAP = 8192;
-constexpr int64_t STATIC_HDR = 4096;   // queue, retry counter, screened count, path cursor
+constexpr int64_t STATIC_HDR = 4096;   // retry counter, path cursor, queue (STATIC_QUEUE)
+constexpr int64_t STATIC_QUEUE = 1024;
 // Device address of the static array on `device` (the current device),
 // looked up and cleared once per device and process; null if that fails.
 void* gwfa_static_scratch(int device);
 
 // per-query parameter check before the alignment: results of the queries
-// that are out of range (GWFA_ST_BAD_INPUT), the others listed in `valid`
-// in work-queue order, their number in *n_valid
-hipError_t gwfa_launch_screen(const KArgs& A, int32_t* valid, int32_t* n_valid, hipStream_t st);
+// that are out of range (GWFA_ST_BAD_INPUT) and the work queue's list, `valid`;
+// resets the queue, A.path_cursor, A.retry_count and A.dump_count
+hipError_t gwfa_launch_screen(const KArgs& A, int32_t* valid, hipStream_t st);
 
 // pruning network: training and batch inference (gwfa_mlp.hip)
 struct Scale8 {

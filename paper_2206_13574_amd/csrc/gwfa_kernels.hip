@@ -2145,16 +2145,27 @@ __global__ __launch_bounds__(BLOCK, waves_per_simd(BLOCK, MODE)) void k_align(KA
         }
     }
     if (threadIdx.x < 16) S.acc[threadIdx.x] = 0;
-    // queries to take: those the screen pass listed, or all of `order`
-    const int32_t n_q = A.n_valid ? __builtin_amdgcn_readfirstlane(*A.n_valid) : A.n_reads;
-    for (;;) {
-        if (threadIdx.x == 0) S.read = atomicAdd(A.queue, 1);
+    // The work queue: query ridx of `order` (-1: turned away by the screen pass).
+    // Device atomics on one address take their turns (7 ns each), so a batch
+    // with many queries per workgroup is dealt out by Q_SLOTS counters, every
+    // Q_SLOTS-th query each; a workgroup goes on to the next counter when one
+    // has run out.  Small batches use one: the last, empty, takes cost a round
+    // trip each.
+    const int n_q = A.n_reads;
+    const int slots = n_q > 4 * (int)gridDim.x ? Q_SLOTS : 1;
+    int slot = (int)blockIdx.x % slots, left = slots;
+    while (left > 0) {
+        if (threadIdx.x == 0) S.read = atomicAdd(&A.queue[Q_STRIDE * slot], 1);
         __syncthreads();
-        const int ridx = __builtin_amdgcn_readfirstlane(S.read);
+        const int ridx = __builtin_amdgcn_readfirstlane(S.read) * slots + slot;
         __syncthreads();
-        if (ridx >= n_q) break;
-        const int r = A.order ? A.order[ridx] : ridx;
-        align_read<BLOCK, MODE>(arena, r, S);
+        if (ridx < n_q) {
+            const int r = __builtin_amdgcn_readfirstlane(A.order ? A.order[ridx] : ridx);
+            if (r >= 0) align_read<BLOCK, MODE>(arena, r, S);
+        } else {
+            --left;
+            slot = slot + 1 == slots ? 0 : slot + 1;
+        }
     }
     // counters: once per workgroup, on one of STAT_SLOTS lines.  Twelve atomics
     // per query on one line bounded short queries (87 ns a query, whatever the
@@ -2163,59 +2174,43 @@ __global__ __launch_bounds__(BLOCK, waves_per_simd(BLOCK, MODE)) void k_align(KA
         atomicAdd(&A.stats[16 * (blockIdx.x % STAT_SLOTS) + threadIdx.x], S.acc[threadIdx.x]);
 }
 
-// Screen pass (one workgroup, before the alignment kernel): a query whose
-// start vertex, start window (0 <= j0 <= j1 <= |v_s|) or end vertex is out
-// of range gets its result here, with status GWFA_ST_BAD_INPUT; the others
-// are listed in `valid` in the work-queue order (an ordered block scan per
-// chunk of SCREEN queries), so that the alignment kernel only ever takes
-// queries whose parameters index the graph in bounds.
-constexpr int SCREEN = 1024;
-__global__ __launch_bounds__(SCREEN) void k_screen(KArgs A, int32_t* valid, int32_t* n_valid) {
-    __shared__ int32_t wsum[SCREEN / 64];
-    __shared__ int32_t base;
-    const int tid = threadIdx.x;
-    if (tid == 0) base = 0;
-    __syncthreads();
-    for (int32_t c = 0; c < A.n_reads; c += SCREEN) {
-        const int32_t idx = c + tid;
-        int ok = 0;
-        int32_t r = 0;
-        if (idx < A.n_reads) {
-            r = A.order ? A.order[idx] : idx;
-            const int32_t vs = A.v_start[r];
-            const int32_t ve = A.v_end ? A.v_end[r] : A.end_vertex;
-            const int32_t j0 = A.v_off ? A.v_off[r] : 0;
-            const int32_t j1 = A.v_off_hi ? A.v_off_hi[r] : j0;
-            bool good = vs >= 0 && vs < A.n_vtx && ve >= -1 && ve < A.n_vtx && !(A.v_end && ve < 0) && j0 >= 0 &&
-                        j1 >= j0;
-            if (good) good = (int64_t)j1 <= A.seg_off[vs + 1] - A.seg_off[vs];
-            ok = good ? 1 : 0;
-            if (!good) {
-                gwfa_result* out = A.res + r;
-                const int64_t t = (int64_t)wall_clock64();
-                out->t_begin = t; out->t_end = t;
-                out->dist = -1; out->end_v = -1; out->end_off = -1; out->status = GWFA_ST_BAD_INPUT;
-                out->path_off = -1; out->path_len = 0; out->n_scores = 0; out->work = 0;
-                out->start_off = j0; out->clip = 0;
-            }
-        }
-        // ordered exclusive scan of ok over the block
-        const ull m = __ballot(ok);
-        const int ex = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-        if (__lane_id() == 0) wsum[tid >> 6] = __popcll(m);
-        __syncthreads();
-        int before = base, tot = 0;
-        for (int w = 0; w < SCREEN / 64; ++w) {
-            const int x = wsum[w];
-            before += (w < (tid >> 6)) ? x : 0;
-            tot += x;
-        }
-        if (ok) valid[before + ex] = r;
-        __syncthreads();
-        if (tid == 0) base += tot;
-        __syncthreads();
+// Screen pass, before the alignment kernel, one thread per place of the work
+// queue: a query whose start vertex, start window (0 <= j0 <= j1 <= |v_s|) or
+// end vertex is out of range gets its result here, with status
+// GWFA_ST_BAD_INPUT, and leaves -1 in its place of `valid`; the others are
+// listed there, so that the alignment kernel only ever takes queries whose
+// parameters index the graph in bounds.  It also resets the queue and the
+// call's counters (20,011 queries: 6 us; 60 us when one workgroup compacted
+// the list, and a launch of its own for the reset).
+constexpr int SCREEN = 256;
+__device__ __forceinline__ void reset_counters(int32_t* queue, ull* path_cursor, int32_t* retry_count, ull* dump_count) {
+    if (threadIdx.x < Q_SLOTS) queue[Q_STRIDE * threadIdx.x] = 0;
+    if (threadIdx.x == 0) {
+        if (path_cursor) *path_cursor = 0;
+        if (retry_count) *retry_count = 0;
+        if (dump_count) *dump_count = 0;
     }
-    if (tid == 0) *n_valid = base;
+}
+__global__ __launch_bounds__(SCREEN) void k_screen(KArgs A, int32_t* valid) {
+    if (blockIdx.x == 0) reset_counters(A.queue, A.path_cursor, A.retry_count, A.dump_count);
+    const int32_t idx = (int32_t)blockIdx.x * SCREEN + (int32_t)threadIdx.x;
+    if (idx >= A.n_reads) return;
+    const int32_t r = A.order ? A.order[idx] : idx;
+    const int32_t vs = A.v_start[r];
+    const int32_t ve = A.v_end ? A.v_end[r] : A.end_vertex;
+    const int32_t j0 = A.v_off ? A.v_off[r] : 0;
+    const int32_t j1 = A.v_off_hi ? A.v_off_hi[r] : j0;
+    bool good = vs >= 0 && vs < A.n_vtx && ve >= -1 && ve < A.n_vtx && !(A.v_end && ve < 0) && j0 >= 0 && j1 >= j0;
+    if (good) good = (int64_t)j1 <= A.seg_off[vs + 1] - A.seg_off[vs];
+    if (!good) {
+        gwfa_result* out = A.res + r;
+        const int64_t t = (int64_t)wall_clock64();
+        out->t_begin = t; out->t_end = t;
+        out->dist = -1; out->end_v = -1; out->end_off = -1; out->status = GWFA_ST_BAD_INPUT;
+        out->path_off = -1; out->path_len = 0; out->n_scores = 0; out->work = 0;
+        out->start_off = j0; out->clip = 0;
+    }
+    valid[idx] = good ? r : -1;
 }
 
 // Four ASCII bases (the first in the low byte) -> 8 bits, the first base in
@@ -2276,12 +2271,7 @@ __global__ void k_zero(ull* p, int64_t n_words) {
 }
 
 __global__ void k_reset(int32_t* queue, ull* path_cursor, int32_t* retry_count, ull* dump_count) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        *queue = 0;
-        if (path_cursor) *path_cursor = 0;
-        if (retry_count) *retry_count = 0;
-        if (dump_count) *dump_count = 0;
-    }
+    reset_counters(queue, path_cursor, retry_count, dump_count);
 }
 
 }  // namespace gwfa_dev
@@ -2360,9 +2350,10 @@ void* gwfa_static_scratch(int device) {
     return p;
 }
 
-hipError_t gwfa_launch_screen(const KArgs& A, int32_t* valid, int32_t* n_valid, hipStream_t st) {
+hipError_t gwfa_launch_screen(const KArgs& A, int32_t* valid, hipStream_t st) {
     (void)hipGetLastError();
-    hipLaunchKernelGGL(gwfa_dev::k_screen, dim3(1), dim3(gwfa_dev::SCREEN), 0, st, A, valid, n_valid);
+    const int blocks = (A.n_reads + gwfa_dev::SCREEN - 1) / gwfa_dev::SCREEN;
+    hipLaunchKernelGGL(gwfa_dev::k_screen, dim3(blocks), dim3(gwfa_dev::SCREEN), 0, st, A, valid);
     return hipGetLastError();
 }
 
