@@ -8,6 +8,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <new>
 #include <numeric>
 #include <string>
 #include <vector>
@@ -46,6 +47,12 @@ struct Tier {
 // reads with distances up to 3,000: 6.9 ms, 8.9 with 256).
 constexpr int64_t CIG_LDS_MAX = 78 << 10;
 constexpr int64_t CIG_WIDE_D = 1024;
+
+// Host-buffer entry points: device workspace kept between calls, inputs that go
+// through pinned memory in one copy (larger ones are copied from where they
+// are), and results that come back in one.
+constexpr int64_t HOST_WS_KEEP = (int64_t)256 << 20;
+constexpr int64_t STAGE_IN = 1 << 20, STAGE_OUT = 1 << 16;
 
 int64_t align_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 
@@ -101,6 +108,12 @@ struct gwfa_ctx {
     int n_cu = 256;
     int exact_per_cu[4] = {0, 0, 0, 0}; // resident workgroups of 64 << i lanes per compute unit, exact mode
     char* static_base = nullptr;       // the device's static working memory (gwfa_align_batch_static_dev)
+    int32_t* h_retry = nullptr;         // pinned: the overflow count of a tier's launch
+    // the host-buffer entry points: device workspace (kept up to HOST_WS_KEEP
+    // bytes) and pinned staging for small batches
+    char* ws = nullptr;
+    int64_t ws_bytes = 0;
+    char* stage = nullptr;
     std::string err;
 };
 
@@ -132,9 +145,19 @@ int dev_fail(gwfa_ctx* ctx, hipError_t e, const char* what) {
         if (e_ != hipSuccess) return dev_fail((ctx), e_, #call);       \
     } while (0)
 
-inline bool is_acgt(uint8_t c) {
-    const uint8_t u = c & 0xdf;
-    return u == 'A' || u == 'C' || u == 'G' || u == 'T';
+// Whether all n bytes are bases (ACGTacgt).  Blocks without an exit, so that
+// the compiler compares 16 bytes at a time.
+bool all_acgt(const uint8_t* s, int64_t n) {
+    for (int64_t b = 0; b < n; b += 4096) {
+        const int64_t m = std::min<int64_t>(4096, n - b);
+        uint8_t bad = 0;
+        for (int64_t i = 0; i < m; ++i) {
+            const uint8_t u = s[b + i] & 0xdf;
+            bad |= (uint8_t)((u != 'A') & (u != 'C') & (u != 'G') & (u != 'T'));
+        }
+        if (bad) return false;
+    }
+    return true;
 }
 
 void free_tier(Tier& t) {
@@ -260,6 +283,7 @@ int gwfa_ctx_create(int device, void* hip_stream, gwfa_ctx** out) {
     bool ok = hipMalloc((void**)&c->d_queue, Q_SLOTS * Q_STRIDE * sizeof(int32_t)) == hipSuccess &&
               hipMalloc((void**)&c->d_cursor, sizeof(unsigned long long)) == hipSuccess &&
               hipMalloc((void**)&c->d_retry_count, sizeof(int32_t)) == hipSuccess &&
+              hipHostMalloc((void**)&c->h_retry, sizeof(int32_t), hipHostMallocDefault) == hipSuccess &&
               hipMalloc((void**)&c->d_stats, STAT_SLOTS * 16 * sizeof(unsigned long long)) == hipSuccess;
     if (ok) ok = hipMemset(c->d_stats, 0, STAT_SLOTS * 16 * sizeof(unsigned long long)) == hipSuccess &&
                  hipDeviceSynchronize() == hipSuccess;
@@ -280,6 +304,9 @@ void gwfa_ctx_destroy(gwfa_ctx* c) {
     if (c->d_queue) (void)hipFree(c->d_queue);
     if (c->d_cursor) (void)hipFree(c->d_cursor);
     if (c->d_retry_count) (void)hipFree(c->d_retry_count);
+    if (c->h_retry) (void)hipHostFree(c->h_retry);
+    if (c->ws) (void)hipFree(c->ws);
+    if (c->stage) (void)hipHostFree(c->stage);
     if (c->d_stats) (void)hipFree(c->d_stats);
     for (auto p : c->d_retry) if (p) (void)hipFree(p);
     if (c->d_valid) (void)hipFree(c->d_valid);
@@ -326,8 +353,7 @@ int gwfa_graph_create(gwfa_ctx* ctx, int32_t n_vtx, const uint8_t* seq, const in
     const int64_t bases = seq_off[n_vtx];
     if (bases > 0 && !seq) return GWFA_ERR_ARG;
     if (bases >= ((int64_t)1 << 40)) return GWFA_ERR_ARG;
-    for (int64_t i = 0; i < bases; ++i)
-        if (!is_acgt(seq[i])) return GWFA_ERR_ALPHABET;
+    if (!all_acgt(seq, bases)) return GWFA_ERR_ALPHABET;
     for (int32_t v = 0; v < n_vtx; ++v)
         if (seq_off[v + 1] - seq_off[v] > (int64_t)1 << 30) return GWFA_ERR_ARG;
     for (int64_t e = 0; e < n_edge; ++e)
@@ -540,9 +566,9 @@ static int run_tiers(gwfa_ctx* ctx, KArgs& A, int ti0, int32_t n, bool launched,
             HIPCHK(ctx, gwfa_launch_align(A, launch_lanes(ctx, A, n), groups, st));
         }
         if (ti + 1 == N_TIERS) break;
-        int32_t h_retry = 0;
-        HIPCHK(ctx, hipMemcpyAsync(&h_retry, ctx->d_retry_count, 4, hipMemcpyDeviceToHost, st));
+        HIPCHK(ctx, hipMemcpyAsync(ctx->h_retry, ctx->d_retry_count, 4, hipMemcpyDeviceToHost, st));
         HIPCHK(ctx, hipStreamSynchronize(st));
+        const int32_t h_retry = *ctx->h_retry;
         if (h_retry <= 0) break;
         ctx->rerun_total += h_retry;
         order = ctx->d_retry[ti & 1];
@@ -550,6 +576,29 @@ static int run_tiers(gwfa_ctx* ctx, KArgs& A, int ti0, int32_t n, bool launched,
         // reset the queue and the retry counter, keep the path cursor and the dump counter
         HIPCHK(ctx, gwfa_launch_reset(ctx->d_queue, nullptr, ctx->d_retry_count, nullptr, st));
     }
+    return GWFA_OK;
+}
+
+// Checks the arguments and launches the screen pass and the first tier; A is
+// left as run_tiers(.., launched) takes it.
+static int align_begin(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const uint64_t* d_packed,
+                       const int64_t* d_read_off, const int32_t* d_v_start, const int32_t* d_v_end,
+                       const int32_t* d_order, const gwfa_opts* opts, gwfa_result* d_res, int32_t* d_path_buf,
+                       int64_t path_cap, int64_t* d_path_used, float* d_dump, int64_t dump_cap, int64_t* d_dump_count,
+                       hipStream_t st, const int32_t* d_start_off, const int32_t* d_start_hi, KArgs& A) {
+    int rc = fill_args(ctx, g, n_reads, d_packed, d_read_off, d_v_start, d_v_end, opts, d_res, d_path_buf,
+                       path_cap, d_path_used, d_dump, dump_cap, d_dump_count, A);
+    if (!rc) rc = ensure_lists(ctx, n_reads);
+    if (rc || n_reads == 0) return rc;
+    A.v_off = d_start_off;
+    A.v_off_hi = d_start_hi;
+    A.order = d_order;
+    A.n_reads = n_reads;
+    HIPCHK(ctx, gwfa_launch_screen(A, ctx->d_valid, st));
+    int groups = 0;
+    rc = set_tier(ctx, A, first_tier(A), ctx->d_valid, n_reads, &groups);
+    if (rc) return rc;
+    HIPCHK(ctx, gwfa_launch_align(A, launch_lanes(ctx, A, n_reads), groups, st));
     return GWFA_OK;
 }
 
@@ -561,18 +610,13 @@ static int align_dev(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const 
                      const int32_t* d_start_hi = nullptr) {
     if (!ctx) return GWFA_ERR_ARG;
     HIPCHK(ctx, hipSetDevice(ctx->device));
-    KArgs A;
-    int rc = fill_args(ctx, g, n_reads, d_packed, d_read_off, d_v_start, d_v_end, opts, d_res, d_path_buf,
-                       path_cap, d_path_used, d_dump, dump_cap, d_dump_count, A);
-    if (!rc) rc = ensure_lists(ctx, n_reads);
-    if (rc || n_reads == 0) return rc;
-    A.v_off = d_start_off;
-    A.v_off_hi = d_start_hi;
     hipStream_t st = hip_stream ? (hipStream_t)hip_stream : ctx->stream;
-    A.order = d_order;
-    A.n_reads = n_reads;
-    HIPCHK(ctx, gwfa_launch_screen(A, ctx->d_valid, st));
-    return run_tiers(ctx, A, first_tier(A), n_reads, false, st);
+    KArgs A;
+    const int rc = align_begin(ctx, g, n_reads, d_packed, d_read_off, d_v_start, d_v_end, d_order, opts, d_res,
+                               d_path_buf, path_cap, d_path_used, d_dump, dump_cap, d_dump_count, st, d_start_off,
+                               d_start_hi, A);
+    if (rc || n_reads == 0) return rc;
+    return run_tiers(ctx, A, first_tier(A), n_reads, true, st);
 }
 
 int gwfa_align_batch_dev(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const uint64_t* d_packed,
@@ -748,9 +792,28 @@ int gwfa_plan_finish(gwfa_plan* p, void* hip_stream) {
     return run_tiers(ctx, A, first_tier(A), p->n_reads, true, st);
 }
 
+// The workspace of the host-buffer entry points, at least `bytes`.
+static int ensure_ws(gwfa_ctx* ctx, int64_t bytes) {
+    if (!ctx->stage && hipHostMalloc((void**)&ctx->stage, STAGE_IN + STAGE_OUT, hipHostMallocDefault) != hipSuccess) {
+        ctx->stage = nullptr;
+        return GWFA_ERR_NOMEM;
+    }
+    if (ctx->ws_bytes >= bytes) return GWFA_OK;
+    if (ctx->ws) (void)hipFree(ctx->ws);
+    ctx->ws = nullptr;
+    ctx->ws_bytes = 0;
+    const int64_t want = std::max<int64_t>(bytes, STAGE_IN);
+    if (hipMalloc((void**)&ctx->ws, (size_t)want) != hipSuccess) {
+        ctx->ws = nullptr;
+        return GWFA_ERR_NOMEM;
+    }
+    ctx->ws_bytes = want;
+    return GWFA_OK;
+}
+
 int gwfa_align_batch(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const uint8_t* reads,
                      const int64_t* read_off, const int32_t* v_start, const gwfa_opts* opts, gwfa_result* res,
-                     int32_t* path_buf, int64_t path_cap, int64_t* path_needed) {
+                     int32_t* path_buf, int64_t path_cap, int64_t* path_needed) try {
     if (!ctx || !g || n_reads < 0 || path_cap < 0) return GWFA_ERR_ARG;
     int rc = check_opts(ctx, opts);
     if (rc) return rc;
@@ -766,8 +829,7 @@ int gwfa_align_batch(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const 
     }
     const int64_t bases = read_off[n_reads];
     if (bases > 0 && !reads) return GWFA_ERR_ARG;
-    for (int64_t i = 0; i < bases; ++i)
-        if (!is_acgt(reads[i])) return GWFA_ERR_ALPHABET;
+    if (!all_acgt(reads, bases)) return GWFA_ERR_ALPHABET;
     // longest queries first
     std::vector<int32_t> order(n_reads);
     std::iota(order.begin(), order.end(), 0);
@@ -777,59 +839,88 @@ int gwfa_align_batch(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const 
     HIPCHK(ctx, hipSetDevice(ctx->device));
     hipStream_t st = ctx->stream;
     const int64_t words = gwfa_packed_words(bases);
-    uint8_t* d_ascii = nullptr;
-    unsigned long long* d_packed = nullptr;
-    int64_t* d_off = nullptr;
-    int32_t *d_vs = nullptr, *d_order = nullptr, *d_err = nullptr, *d_path = nullptr;
-    gwfa_result* d_res = nullptr;
-    int64_t* d_used = nullptr;
     const bool want_path = opts->traceback && path_buf && path_cap > 0;
-    bool ok = hipMalloc((void**)&d_ascii, (size_t)std::max<int64_t>(bases, 1)) == hipSuccess &&
-              hipMalloc((void**)&d_packed, (size_t)words * 8) == hipSuccess &&
-              hipMalloc((void**)&d_off, (size_t)(n_reads + 1) * 8) == hipSuccess &&
-              hipMalloc((void**)&d_vs, (size_t)n_reads * 4) == hipSuccess &&
-              hipMalloc((void**)&d_order, (size_t)n_reads * 4) == hipSuccess &&
-              hipMalloc((void**)&d_err, 4) == hipSuccess &&
-              hipMalloc((void**)&d_res, (size_t)n_reads * sizeof(gwfa_result)) == hipSuccess &&
-              hipMalloc((void**)&d_used, 8) == hipSuccess &&
-              (!want_path || hipMalloc((void**)&d_path, (size_t)path_cap * 4) == hipSuccess);
-    int out_rc = ok ? GWFA_OK : GWFA_ERR_NOMEM;
+    // one device block: inputs (offsets, starts, order, bases), packed queries,
+    // outputs (ids used, results, walks)
+    const int64_t n = n_reads;
+    int64_t lay = 0;
+    auto take = [&](int64_t b) { const int64_t o = lay; lay = align_up(lay + b, 256); return o; };
+    const int64_t o_off = take((n + 1) * 8), o_vs = take(n * 4), o_order = take(n * 4), o_ascii = take(std::max<int64_t>(bases, 1));
+    const int64_t in_bytes = o_ascii + bases;
+    const int64_t o_packed = take(words * 8);
+    const int64_t o_used = take(8), o_res = take(n * (int64_t)sizeof(gwfa_result));
+    const int64_t o_path = lay, out_bytes = o_path - o_used + (want_path ? path_cap * 4 : 0);
+    take(want_path ? path_cap * 4 : 0);
+    rc = ensure_ws(ctx, lay);
+    if (rc) return rc;
+    char* const d = ctx->ws;
     hipError_t e = hipSuccess;
-    if (ok) {
-        if (e == hipSuccess) e = hipMemcpyAsync(d_ascii, reads, (size_t)bases, hipMemcpyHostToDevice, st);
-        if (e == hipSuccess) e = hipMemcpyAsync(d_off, read_off, (size_t)(n_reads + 1) * 8, hipMemcpyHostToDevice, st);
-        if (e == hipSuccess) e = hipMemcpyAsync(d_vs, v_start, (size_t)n_reads * 4, hipMemcpyHostToDevice, st);
-        if (e == hipSuccess) e = hipMemcpyAsync(d_order, order.data(), (size_t)n_reads * 4, hipMemcpyHostToDevice, st);
-        if (e == hipSuccess) e = hipMemsetAsync(d_err, 0, 4, st);
-        if (e == hipSuccess) e = gwfa_launch_pack(d_ascii, bases, d_packed, words, d_err, st);
-        if (e != hipSuccess) out_rc = dev_fail(ctx, e, "query upload");
+    if (in_bytes <= STAGE_IN) {
+        char* const h = ctx->stage;
+        memcpy(h + o_off, read_off, (size_t)(n + 1) * 8);
+        memcpy(h + o_vs, v_start, (size_t)n * 4);
+        memcpy(h + o_order, order.data(), (size_t)n * 4);
+        if (bases > 0) memcpy(h + o_ascii, reads, (size_t)bases);
+        e = hipMemcpyAsync(d, h, (size_t)in_bytes, hipMemcpyHostToDevice, st);
+    } else {
+        e = hipMemcpyAsync(d + o_off, read_off, (size_t)(n + 1) * 8, hipMemcpyHostToDevice, st);
+        if (e == hipSuccess) e = hipMemcpyAsync(d + o_vs, v_start, (size_t)n * 4, hipMemcpyHostToDevice, st);
+        if (e == hipSuccess) e = hipMemcpyAsync(d + o_order, order.data(), (size_t)n * 4, hipMemcpyHostToDevice, st);
+        if (e == hipSuccess && bases > 0)
+            e = hipMemcpyAsync(d + o_ascii, reads, (size_t)bases, hipMemcpyHostToDevice, st);
     }
+    // (the bases are validated above: no error flag)
+    if (e == hipSuccess)
+        e = gwfa_launch_pack((const uint8_t*)d + o_ascii, bases, (unsigned long long*)(d + o_packed), words, nullptr, st);
+    int out_rc = e == hipSuccess ? GWFA_OK : dev_fail(ctx, e, "query upload");
+    KArgs A;
     if (out_rc == GWFA_OK)
-        out_rc = gwfa_align_batch_dev(ctx, g, n_reads, (const uint64_t*)d_packed, d_off, d_vs, d_order, opts, d_res,
-                                      want_path ? d_path : nullptr, want_path ? path_cap : 0, d_used, st);
+        out_rc = align_begin(ctx, g, n_reads, (const uint64_t*)(d + o_packed), (const int64_t*)(d + o_off),
+                             (const int32_t*)(d + o_vs), nullptr, (const int32_t*)(d + o_order), opts,
+                             (gwfa_result*)(d + o_res), want_path ? (int32_t*)(d + o_path) : nullptr,
+                             want_path ? path_cap : 0, (int64_t*)(d + o_used), nullptr, 0, nullptr, st, nullptr, nullptr, A);
     if (out_rc == GWFA_OK) {
-        int64_t used = 0;
-        e = hipMemcpyAsync(res, d_res, (size_t)n_reads * sizeof(gwfa_result), hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipMemcpyAsync(&used, d_used, 8, hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
-        if (e == hipSuccess && want_path && used > 0)
-            e = hipMemcpy(path_buf, d_path, (size_t)std::min(used, path_cap) * 4, hipMemcpyDeviceToHost);
-        if (e != hipSuccess) out_rc = dev_fail(ctx, e, "result download");
-        if (out_rc == GWFA_OK) {
+        // results and the overflow count in one wait; after a re-run (rare) again
+        char* const h = ctx->stage + STAGE_IN;
+        const int64_t head = std::min<int64_t>(out_bytes, STAGE_OUT);   // ids used, results, first walks
+        auto fetch = [&]() {
+            hipError_t f = hipMemcpyAsync(ctx->h_retry, ctx->d_retry_count, 4, hipMemcpyDeviceToHost, st);
+            if (f == hipSuccess) f = hipMemcpyAsync(h, d + o_used, (size_t)head, hipMemcpyDeviceToHost, st);
+            if (f == hipSuccess && o_path - o_used > head)
+                f = hipMemcpyAsync(res, d + o_res, (size_t)n * sizeof(gwfa_result), hipMemcpyDeviceToHost, st);
+            if (f == hipSuccess) f = hipStreamSynchronize(st);
+            return f;
+        };
+        e = fetch();
+        if (e == hipSuccess && *ctx->h_retry > 0) {
+            out_rc = run_tiers(ctx, A, first_tier(A), n_reads, true, st);
+            if (out_rc == GWFA_OK) e = fetch();
+        }
+        if (out_rc == GWFA_OK && e == hipSuccess) {
+            int64_t used = 0;
+            memcpy(&used, h, 8);
+            if (o_path - o_used <= head) memcpy(res, h + (o_res - o_used), (size_t)n * sizeof(gwfa_result));
+            if (want_path && used > 0) {
+                const int64_t ids = std::min(used, path_cap), got = std::max<int64_t>(0, (head - (o_path - o_used)) / 4);
+                const int64_t k = std::min(ids, got);
+                if (k > 0) memcpy(path_buf, h + (o_path - o_used), (size_t)k * 4);
+                if (ids > k)
+                    e = hipMemcpy(path_buf + k, d + o_path + 4 * k, (size_t)(ids - k) * 4, hipMemcpyDeviceToHost);
+            }
             if (path_needed) *path_needed = opts->traceback ? used : 0;
             if (opts->traceback && used > (want_path ? path_cap : 0)) out_rc = GWFA_ERR_PATH_CAP;
         }
+        if (e != hipSuccess) out_rc = dev_fail(ctx, e, "result download");
     }
-    if (d_ascii) (void)hipFree(d_ascii);
-    if (d_packed) (void)hipFree(d_packed);
-    if (d_off) (void)hipFree(d_off);
-    if (d_vs) (void)hipFree(d_vs);
-    if (d_order) (void)hipFree(d_order);
-    if (d_err) (void)hipFree(d_err);
-    if (d_res) (void)hipFree(d_res);
-    if (d_used) (void)hipFree(d_used);
-    if (d_path) (void)hipFree(d_path);
+    if (out_rc != GWFA_OK && out_rc != GWFA_ERR_PATH_CAP) (void)hipStreamSynchronize(st);   // nothing still uses the buffers
+    if (ctx->ws_bytes > HOST_WS_KEEP) {
+        (void)hipFree(ctx->ws);
+        ctx->ws = nullptr;
+        ctx->ws_bytes = 0;
+    }
     return out_rc;
+} catch (const std::bad_alloc&) {
+    return GWFA_ERR_NOMEM;
 }
 
 int gwfa_align(gwfa_ctx* ctx, const gwfa_graph* g, const uint8_t* q, int32_t qlen, int32_t v_start,
@@ -854,7 +945,7 @@ int gwfa_mlp_load(gwfa_ctx* ctx, const uint16_t* w, int64_t n, const float* scal
 int gwfa_cigar_dev(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const uint64_t* d_packed,
                    const int64_t* d_read_off, const gwfa_result* d_res, const int32_t* d_path_buf, uint32_t* d_cigar,
                    int64_t cigar_cap, int64_t* d_cigar_off, int32_t* d_cigar_len, int64_t* d_cigar_used,
-                   void* hip_stream) {
+                   void* hip_stream) try {
     if (!ctx || !g || n_reads < 0 || cigar_cap < 0 || g->device != ctx->device) return GWFA_ERR_ARG;
     if (n_reads == 0) return GWFA_OK;
     if (!d_packed || !d_read_off || !d_res || !d_path_buf || !d_cigar_off || !d_cigar_len || !d_cigar_used ||
@@ -950,6 +1041,8 @@ int gwfa_cigar_dev(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const ui
     A.max_d = (int32_t)max_d; A.max_q = (int32_t)max_q; A.max_t = (int32_t)max_t;
     HIPCHK(ctx, gwfa_launch_cigar(A, (int)groups, lanes, (int)lds, st));
     return GWFA_OK;
+} catch (const std::bad_alloc&) {
+    return GWFA_ERR_NOMEM;
 }
 
 static bool get_scale(const float* h, Scale8& s) {
