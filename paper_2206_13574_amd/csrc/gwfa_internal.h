@@ -18,6 +18,7 @@ struct KArgs {
     const int32_t* out_dst;          // n_edge targets
     const int4* vinfo;               // n_vtx: first out-edge index, out-degree, first and second target (-1: none)
     const int4* vlab;                // n_vtx: label base (low, high 32 bits), label length, 0
+    const int4* vsucc;               // 2 n_vtx: vlab of the first and the second target (zeros: none)
     int32_t n_vtx;
     // queries (device)
     const unsigned long long* rd;    // packed queries

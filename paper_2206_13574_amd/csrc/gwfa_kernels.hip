@@ -63,7 +63,7 @@ constexpr int xs_lds(int block) { return block >= 256 ? 1024 : 4 * block; }
 // finds an entry's place in that part by a search in LDS and one round of at
 // most SAMP-1 loads.
 constexpr int SAMP = 8;
-constexpr int nsamp(int block) { return block >= 256 ? 1024 : 256; }
+constexpr int nsamp(int block) { return block >= 256 ? 1024 : (block >= 128 ? 256 : 128); }
 // A list's storage: its main entries are written by the waves of the
 // workgroup, each into a part of its own, at most three per source entry, so
 // 3 list_cap places hold any list of up to list_cap entries; the crossing
@@ -296,13 +296,15 @@ __device__ __forceinline__ int64_t lab_base(int4 lab) {
 // candidates.  Entries carry their vertex's label base and length.
 struct Narrow {
     static constexpr int N = 64;       // entries of a list: one per lane of the wave
-    static constexpr int C = 128;      // crossing candidates kept here, the rest in the arena
+    static constexpr int C = 48;       // crossing candidates kept here, the rest in the arena
+    static constexpr int R = 128;      // the expansion's candidates: up to 63 waiting and 63 of a step
     int4 ie[N + 4];
     int4 oe[N];
-    int64_t ib[N + 4], ob[N];
+    int2 ring[R];                      // offset; source, slot and which source decides
+    int64_t ib[N + 4], ob[N], cb[C];
     int32_t iw[N + 4], it[N + 4], il[N + 4];
     int32_t ow[N], ot[N], ol[N];
-    int32_t cu[C], ck[C], cw[C], ct[C];
+    int32_t cu[C], ck[C], cw[C], ct[C], cl[C];
 };
 
 // Candidate outputs of the expansion, in list order: (v, k, offset with bit 31
@@ -733,18 +735,20 @@ __device__ __forceinline__ void entry_features(float* f, int32_t s, int32_t i, i
 // ---------------------------------------------------------------------------
 // Narrow wavefronts: scores whose lists have at most 64 entries are run by one
 // wave on lists in LDS, with no barrier and one memory round trip per score
-// (records, windows and out-edge records together) where the wide path takes
-// about eight (list, labels, records, stores drained before each barrier,
-// list again for the merge and the pruning).  Pruned runs and short reads
-// stay here: a score of Algorithm 4 on the 1 Mb DAG has 5 entries, and its
-// wide cost is round trips and about 1,500 instructions per wave, whatever
-// the number of lanes at work.  Each lane takes one output diagonal (three
-// slots of 21 source entries per step) instead of one source with three
-// outputs, so the windows, records and extension are written once.
-// Bound now by the round trip and by issue (16 waves per CU): 2.2 us a score
-// alone, 3.1 us with 10 waves on the CU, against 4.6 and 7.7 us on the wide
-// path.  20,000 reads of 10 kb on the 1 Mb DAG, Algorithm 4 (64 lanes): 15.9 ->
-// 6.5 ms; 8,009 reads on the 10 Mb graph, learned: 92.3 -> 57.8 ms.
+// (records, windows, out-edges and their labels together) and one per crossing
+// round, where the wide path takes about eight (list, labels, records, stores
+// drained before each barrier, list again for the merge and the pruning).
+// Pruned runs and short reads stay here: a score of Algorithm 4 on the 1 Mb DAG
+// has 5 entries, and its wide cost is round trips and about 1,500 instructions
+// per wave, whatever the number of lanes at work.  Each lane makes one output
+// diagonal's candidate (three slots of 21 source entries per step) and then
+// extends one, so the windows, records and extension are written once.
+// Bound now half by instructions (about 630 a score, one wave after the other
+// on its SIMD) and half by the round trips: 2.2 us a score with 5 entries, 3 us
+// with 16 waves on the CU, against 4.6 and 7.7 us on the wide path.  20,000
+// reads of 10 kb on the 1 Mb DAG, Algorithm 4 (64 lanes): 15.9 -> 6.3 ms.  LDS is
+// kept small enough for 16 one-wave workgroups on a CU (10,240 bytes each; the
+// same code with 11,088 was 10% slower).
 // Entered at 48 entries or fewer: from 49 on the next list usually exceeds 64
 // and the score would be started here only to be handed over.
 // ---------------------------------------------------------------------------
@@ -767,28 +771,66 @@ __device__ __forceinline__ int64_t readlane64(int64_t x, int l) {
 // of a wave execute in order, so only the compiler has to keep the order.
 __device__ __forceinline__ void wave_lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
+// Largest x of the wave, in every lane's scalar registers: six steps of
+// data-parallel moves (within rows of 16, then from row to row).
+__device__ __forceinline__ int32_t wave_max(int32_t x) {
+    x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x111, 0xf, 0xf, false));   // row_shr:1, 2, 4, 8
+    x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x112, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x114, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x118, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x142, 0xa, 0xf, false));   // row_bcast:15 into rows 1, 3
+    x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x143, 0xc, 0xf, false));   // row_bcast:31 into rows 2, 3
+    return __builtin_amdgcn_readlane(x, 63);
+}
+
 // Continues the exact-match runs of the lanes with `more` (at query base qp,
 // label base sp, at most rem bases).  One run is compared by the whole wave,
 // 2,048 bases per memory round trip (a run between two errors of an accurate
 // read is hundreds of bases; one lane alone compares 128 per round trip);
 // several are taken four at a time, 16 lanes and 512 bases each.
-__device__ __forceinline__ int32_t wave_extend(const KArgs& A, const Q& q, bool more, int64_t qp, int64_t sp,
+__device__ __forceinline__ int32_t wave_extend(const ull* __restrict__ seg, const Q& q, bool more, int64_t qp, int64_t sp,
                                                int32_t rem, uint32_t& chunks) {
     ull need = __ballot(more);
+    if (!need) return 0;
     const int lane = __lane_id();
     int32_t ext = 0;
+    if ((need & (need - 1)) == 0) {
+        const int l = __builtin_ctzll(need);
+        const int64_t uq = readlane64(qp, l), us = readlane64(sp, l);
+        const int32_t ur = __builtin_amdgcn_readlane(rem, l);
+        int32_t e = 0;
+        uint32_t w = 0;
+        for (;;) {
+            const int32_t off = e + 32 * lane;
+            const bool in = off < ur;
+            const int32_t o = in ? off : 0;
+            const ull x = win32(q.rd, uq + o) ^ win32(seg, us + o);
+            const int32_t rl = min(32, ur - off);
+            const int32_t m = min(x ? (int32_t)(__clzll((long long)x) >> 1) : 32, rl);
+            const ull bad = __ballot(in && m < rl);
+            if (bad) {
+                const int f = __builtin_ctzll(bad);
+                e += 32 * f + __builtin_amdgcn_readlane(m, f);
+                w += f + 1;
+                break;
+            }
+            const int32_t g = min(ur - e, 2048);
+            e += g;
+            w += (uint32_t)(g + 31) >> 5;
+            if (e >= ur) break;
+        }
+        if (lane == l) { ext = e; chunks += w; }
+        return ext;
+    }
     while (need) {
-        const bool one = (need & (need - 1)) == 0;
-        const int width = one ? 64 : 16;            // lanes per run
-        const int sub = one ? lane : lane & 15;
-        int l = __builtin_ctzll(need);               // the run this lane works on
+        int l = __builtin_ctzll(need);               // the run this lane's 16 work on
         bool on = true;
         need &= need - 1;
 #pragma unroll
         for (int j = 1; j < 4; ++j) {
             const bool any = need != 0;
             const int b = any ? __builtin_ctzll(need) : 0;
-            if (!one && (lane >> 4) == j) { l = b; on = any; }
+            if ((lane >> 4) == j) { l = b; on = any; }
             need &= need - 1;
         }
         const int64_t uq = __shfl(qp, l, 64), us = __shfl(sp, l, 64);
@@ -797,23 +839,22 @@ __device__ __forceinline__ int32_t wave_extend(const KArgs& A, const Q& q, bool 
         uint32_t w = 0;
         bool go = on;
         while (__ballot(go)) {
-            const int32_t off = e + 32 * sub;
+            const int32_t off = e + 32 * (lane & 15);
             const bool in = go && off < ur;
             const int32_t o = in ? off : 0;
-            const ull x = win32(q.rd, uq + o) ^ win32(A.seg, us + o);
+            const ull x = win32(q.rd, uq + o) ^ win32(seg, us + o);
             const int32_t rl = min(32, ur - off);
             const int32_t m = min(x ? (int32_t)(__clzll((long long)x) >> 1) : 32, rl);
-            ull bad = __ballot(in && m < rl);
-            if (!one) bad = (bad >> (lane & 48)) & 0xffffull;
+            const ull bad = (__ballot(in && m < rl) >> (lane & 48)) & 0xffffull;
             const int f = bad ? __builtin_ctzll(bad) : 0;
-            const int32_t mf = __shfl(m, one ? f : (lane & 48) + f, 64);
+            const int32_t mf = __shfl(m, (lane & 48) + f, 64);
             if (go) {
                 if (bad) {
                     e += 32 * f + mf;
                     w += f + 1;
                     go = false;
                 } else {
-                    const int32_t g = min(ur - e, 32 * width);
+                    const int32_t g = min(ur - e, 512);
                     e += g;
                     w += (uint32_t)(g + 31) >> 5;
                     go = e < ur;
@@ -826,11 +867,111 @@ __device__ __forceinline__ int32_t wave_extend(const KArgs& A, const Q& q, bool 
             const int lj = __builtin_amdgcn_readlane(l, 16 * j);
             const int32_t ej = __builtin_amdgcn_readlane(e, 16 * j);
             const uint32_t wj = __builtin_amdgcn_readlane(w, 16 * j);
-            const bool onj = __builtin_amdgcn_readlane((int)on, 16 * j) && (j == 0 || !one);
-            if (onj && lane == lj) { ext = ej; chunks += wj; }
+            if (__builtin_amdgcn_readlane((int)on, 16 * j) && lane == lj) { ext = ej; chunks += wj; }
         }
     }
     return ext;
+}
+
+__device__ __forceinline__ ull dir_load(const ull* tab, uint32_t h) {
+    return __hip_atomic_load(&tab[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Length of the common prefix of q[qp ..] and label[sp ..], at most 64 bases
+// (three words of each, loaded together).  `any`: qp and sp are bases of the
+// query and the label; the stores' two words of padding then hold the third
+// word, else (an empty rest at the end of the store) the second is read twice.
+__device__ __forceinline__ int32_t first64(const ull* __restrict__ seg, const Q& q, int64_t qp, int64_t sp, bool any) {
+    const ull *qw = q.rd + (qp >> 5), *sw = seg + (sp >> 5);
+    const int qs = (int)((qp & 31) * 2), ss = (int)((sp & 31) * 2);
+    const ull a0 = qw[0], a1 = qw[1], a2 = qw[any ? 2 : 1], b0 = sw[0], b1 = sw[1], b2 = sw[any ? 2 : 1];
+    const ull x0 = ((a0 << qs) | ((a1 >> 1) >> (63 - qs))) ^ ((b0 << ss) | ((b1 >> 1) >> (63 - ss)));
+    const ull x1 = ((a1 << qs) | ((a2 >> 1) >> (63 - qs))) ^ ((b1 << ss) | ((b2 >> 1) >> (63 - ss)));
+    return x0 ? (int32_t)(__clzll((long long)x0) >> 1) : 32 + (x1 ? (int32_t)(__clzll((long long)x1) >> 1) : 32);
+}
+// A vertex's out-edges: first edge, degree, first two targets, and those
+// targets' labels.
+struct Out {
+    int4 vi, l0, l1;
+};
+__device__ __forceinline__ Out load_out(const int4* __restrict__ vinfo, const int4* __restrict__ vsucc, int32_t v,
+                                        bool want) {
+    Out o;
+    o.vi = make_int4(0, 0, -1, -1);
+    o.l0 = o.l1 = make_int4(0, 0, 0, 0);
+    if (want) {
+        o.vi = vinfo[v];
+        o.l0 = vsucc[2 * (int64_t)v];
+        o.l1 = vsucc[2 * (int64_t)v + 1];
+    }
+    return o;
+}
+// Finds or creates the keys of the lanes with `act` in an open-addressing table
+// that only this wave changes meanwhile: c is what was read from slot h.  No
+// compare-and-swap: lanes that find the same slot empty settle it among
+// themselves, the lowest first.  Returns the slot (-1: the table is full);
+// `made`: this lane's key was not there.
+template <class SH>
+__device__ __forceinline__ int wave_settle(ull* tab, uint32_t mask, ull key, uint32_t h, ull c, bool act, bool& made,
+                                           SH& S, bool trace = false) {
+    const int lane = __lane_id();
+    int slot = act && c == key ? (int)h : -1, n = 0;
+    bool todo = act && c != key;
+    made = false;
+    for (uint32_t p = 0; __ballot(todo); ++p) {
+        ull em = __ballot(todo && c == 0);
+        while (em) {
+            const int f = __builtin_ctzll(em);
+            const uint32_t hf = (uint32_t)__builtin_amdgcn_readlane((int)h, f);
+            const ull kf = (ull)readlane64((int64_t)key, f);
+            const bool here = todo && c == 0 && h == hf;
+            em &= ~__ballot(here);
+            if (lane == f) __hip_atomic_store(&tab[hf], kf, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (here) {
+                if (key == kf) { slot = (int)hf; made = true; todo = false; }
+                else c = kf;   // taken now
+            }
+            ++n;
+        }
+        if (p > mask) break;
+        if (todo) {
+            h = (h + 1) & mask;
+            c = dir_load(tab, h);
+            if (c == key) { slot = (int)h; todo = false; }
+        }
+    }
+    if (n > 0 && lane == 0) {
+        if (trace) S.mn += n; else S.dirn += n;
+    }
+    return slot;
+}
+// Appends the crossing candidates of the lanes with `at_end` (vertex v, target
+// diagonal k2, walk length W, trace index t) to the nc there are: with their
+// labels in LDS, beyond Narrow::C (a list that leaves the narrow path) in the
+// arena.  o: v's out-edges where they have been loaded (`have`).
+template <class SH>
+__device__ __forceinline__ void put_crossings(SH& S, const KArgs& A, Narrow& L, int32_t* cu, int32_t* ck, int32_t* cW,
+                                              int32_t* ct, int32_t& nc, bool at_end, Out o, bool have, int32_t v,
+                                              int32_t k2, int32_t W, int32_t t) {
+    if (__ballot(at_end && !have)) {
+        const Out x = load_out(A.vinfo, A.vsucc, v, at_end && !have);
+        if (at_end && !have) o = x;
+    }
+    const int deg = at_end ? o.vi.y : 0;
+    int tot;
+    const int c = nc + wave_excl_scan(deg, tot);
+    nc += __builtin_amdgcn_readfirstlane(tot);
+    for (int j = 0; j < deg; ++j) {
+        const int32_t u = j == 0 ? o.vi.z : (j == 1 ? o.vi.w : A.out_dst[o.vi.x + j]);
+        if (c + j < Narrow::C) {
+            const int4 lab = j == 0 ? o.l0 : (j == 1 ? o.l1 : A.vlab[u]);
+            L.cu[c + j] = u; L.ck[c + j] = k2; L.ct[c + j] = t; L.cw[c + j] = W;
+            L.cl[c + j] = lab.z; L.cb[c + j] = lab_base(lab);
+        } else if (c + j < A.cand_cap) {
+            cu[c + j] = u; ck[c + j] = k2; cW[c + j] = W; ct[c + j] = t;
+        } else {
+            atomicOr(&S.flags, F_LIST);
+        }
+    }
 }
 
 // Runs scores from S.nr_s on as long as the lists stay narrow; called by the
@@ -861,7 +1002,12 @@ __device__ __attribute__((noinline)) void narrow_scores(int64_t karg) {
     Narrow& L = S.nw;
     const int lane = __lane_id();
     const int li = lane / 3, lj = lane - 3 * li;
-    const int4* __restrict__ vinfo = A.vinfo;
+    // the arguments every score reads, held in scalar registers (from constant
+    // memory the compiler would load them again at each use, and wait)
+    const int4 *vinfo = A.vinfo, *vsucc = A.vsucc;
+    const ull* seg = A.seg;
+    int32_t max_score = A.max_score, a_diff = MODE == 1 && A.prune == GWFA_PRUNE_HEURISTIC ? A.a_diff : 0x7fffffff;
+    asm volatile("" : "+s"(vinfo), "+s"(vsucc), "+s"(seg), "+s"(max_score), "+s"(a_diff));
     const ull t_in = wall_clock64();
     ull t_rounds = 0;
     int64_t work = 0;
@@ -905,13 +1051,16 @@ __device__ __attribute__((noinline)) void narrow_scores(int64_t karg) {
         if (s > 0) {
             if (lane == 0) { S.found = 0; S.iend = -1; S.endkey = ~0ull; }
             // ========== EXPAND + EXTEND ==========
+            // sources: three output slots of 21 entries per step; the candidates
+            // go to a ring in list order, and 64 of them at a time (usually all
+            // of the score's) are extended, one per lane
+            int32_t head = 0, fill = 0;
             for (int32_t c0 = 0; c0 < n; c0 += SRC) {
                 const bool src = lane < 3 * SRC && c0 + li < n;
                 const int32_t si = min(c0 + li, n - 1) + 2;
                 const int4 em2 = L.ie[si - 2], em1 = L.ie[si - 1], e0 = L.ie[si], ep1 = L.ie[si + 1], ep2 = L.ie[si + 2];
                 const int32_t v = e0.x, k = e0.y;
                 const int32_t Lv = L.il[si];
-                const int64_t sb = L.ib[si];
                 const bool pm1 = em1.x == v && em1.y == k - 1;
                 const bool pm2 = pm1 ? (em2.x == v && em2.y == k - 2) : (em1.x == v && em1.y == k - 2);
                 const bool pp1 = ep1.x == v && ep1.y == k + 1;
@@ -924,165 +1073,163 @@ __device__ __attribute__((noinline)) void narrow_scores(int64_t karg) {
                 const bool hasC = lj == 0 || (lj == 1 ? pp1 : pp2);
                 const int bi = lj == 1 ? si : si + 1;
                 const int ci = lj == 0 ? si : (lj == 1 || !pp1 ? si + 1 : si + 2);
-                const int32_t oB = lj == 1 ? e0.z : ep1.z, dB = lj == 1 ? e0.w : ep1.w;
+                const int32_t oB = lj == 1 ? e0.z : ep1.z;
                 const int32_t oC = lj == 0 ? e0.z : (lj == 1 ? ep1.z : ez.z);
                 const int32_t W0 = q.track ? L.iw[si] : 0, WB = q.track ? L.iw[bi] : 0, WC = q.track ? L.iw[ci] : 0;
-                const int32_t t0 = q.tb ? L.it[si] : -1, tB = q.tb ? L.it[bi] : -1, tC = q.tb ? L.it[ci] : -1;
-                int32_t bo = -1, bw = -1, bt = -1;
-                if (lj == 2 && k + e0.z < q.qlen) { bo = e0.z; bw = W0; bt = t0; }
+                int32_t bo = -1, bw = -1, from = si << 1;   // the deciding source's slot, and whether it adds a walk base
+                if (lj == 2 && k + e0.z < q.qlen) { bo = e0.z; bw = W0; }
                 if (hasB && kk + oB < q.qlen && oB < Lv && (oB + 1 > bo || (oB + 1 == bo && WB + 1 > bw))) {
-                    bo = oB + 1; bw = WB + 1; bt = tB;
+                    bo = oB + 1; bw = WB + 1; from = (bi << 1) | 1;
                 }
                 if (hasC && oC < Lv && (oC + 1 > bo || (oC + 1 == bo && WC + 1 > bw))) {
-                    bo = oC + 1; bw = WC + 1; bt = tC;
+                    bo = oC + 1; bw = WC + 1; from = (ci << 1) | 1;
                 }
                 const bool cand = own && bo > (hasB ? oB : -1);
-                const bool chk = cand && !hasB;      // the diagonal's record decides
-                int pg = hasB ? dB : e0.w;
-                if (chk && (kk >> 5) != (k >> 5)) pg = dir_insert(q.dir, q.mask, dkey(v, kk >> 5), &S.dirn);
-                // record, out-edge record and windows in one round of loads
-                const int32_t m = cand ? min(q.qlen - (kk + bo), Lv - bo) : 0;
-                const ull rw = q.pages[chk && pg >= 0 ? pg : 0].R[kk & 31];
-                const int4 vi = vinfo[v];
-                const int64_t qp = q.q0 + (m > 0 ? kk + bo : 0), sp = sb + (m > 0 ? bo : 0);
-                const ull x = win32(q.rd, qp) ^ win32(A.seg, sp);
-                const bool rec = chk && pg >= 0 && rgen(rw) == q.gen;
-                const bool ov = cand && !(rec && bo <= rval(rw));
-                int32_t lx = 0;
-                if (ov && m > 0) {
-                    ++chunks;
-                    lx = min(x ? (int32_t)(__clzll((long long)x) >> 1) : 32, m);
-                }
-                lx += wave_extend(A, q, lx == 32 && m > 32, qp + 32, sp + 32, m - 32, chunks);
-                const ull om = __ballot(ov);
-                const int32_t p = n1 + lanes_below(om);
-                n1 += __popcll(om);
-                int ncr = 0;
-                const int32_t o = bo + lx, W = bw + lx;
-                if (ov) {
-                    if (pg < 0) {
-                        atomicOr(&S.flags, F_GROW);
-                    } else {
-                        ncr = record_entry(q, S, v, kk, o, W, pg, chk && !rec, Lv, o == Lv ? vi.y : 0, lmax);
-                        const int4 e = make_int4(v, kk, o, pg);
-                        if (p < Narrow::N) {
-                            L.oe[p] = e; L.ol[p] = Lv; L.ob[p] = sb;
-                            if (q.track) L.ow[p] = W;
-                            if (q.tb) L.ot[p] = bt;
-                        } else {   // more than a narrow list: it goes on in the wide path
-                            L0.e[p] = make_int4(v, kk, o, page_word(pg, o, Lv));
-                            if (q.track) L0.w[p] = W;
-                            if (q.tb) L0.t[p] = bt;
-                            if ((p & (SAMP - 1)) == 0) S.samp[p / SAMP] = skey(v, kk);
+                const ull cm = __ballot(cand);
+                if (cand)   // source and slot (the diagonal and its page follow), whether its record decides
+                    L.ring[(head + fill + lanes_below(cm)) & (Narrow::R - 1)] =
+                        make_int2(bo, si | (lj << 8) | (from << 10) | (hasB ? 0 : 1 << 20));
+                fill += __popcll(cm);
+                wave_lds_order();
+                while (fill >= 64 || (fill > 0 && c0 + SRC >= n)) {
+                    const int cnt = min(fill, 64);
+                    const bool act = lane < cnt;
+                    const int2 c = L.ring[(head + (act ? lane : 0)) & (Narrow::R - 1)];
+                    head += cnt;
+                    fill -= cnt;
+                    const int32_t sj = c.y & 255, j = (c.y >> 8) & 3;
+                    const int4 se = L.ie[sj];
+                    const int32_t lv = L.il[sj];
+                    const int64_t sb = L.ib[sj];
+                    const int32_t sv = se.x, sk = se.y - 1 + j, b0 = c.x;
+                    const bool chk = act && (c.y >> 20);   // the diagonal's record decides
+                    const int32_t fr = (c.y >> 11) & 127;
+                    const int32_t ct0 = q.tb ? L.it[fr] : -1, cw0 = q.track ? L.iw[fr] + ((c.y >> 10) & 1) : 0;
+                    const bool far = chk && (sk >> 5) != (se.y >> 5);
+                    int pg = chk || j == 1 ? se.w : L.ie[sj + 1].w;
+                    // directory, record, out-edges, successors' labels and windows in one
+                    // round of loads; a diagonal on another page than its source is looked
+                    // for in its key's home slot
+                    const ull key = dkey(sv, sk >> 5);
+                    const uint32_t h = dhash(key) & q.mask;
+                    const ull dprobe = far ? dir_load(q.dir, h) : key;
+                    const int32_t m = act ? min(q.qlen - (sk + b0), lv - b0) : 0;
+                    const ull rw = q.pages[far ? (int)h : pg].R[sk & 31];
+                    const Out o1 = load_out(vinfo, vsucc, sv, act && lv - b0 <= 64);
+                    const int64_t qp = q.q0 + (m > 0 ? sk + b0 : 0), sp = sb + (m > 0 ? b0 : 0);
+                    int32_t lx = first64(seg, q, qp, sp, m > 0);
+                    ull r2 = rw;
+                    if (__ballot(far)) {
+                        bool made;
+                        const int f = wave_settle(q.dir, q.mask, key, h, dprobe, far, made, S);
+                        if (far) {
+                            pg = f;
+                            if (made) r2 = 0;
+                            else if (f >= 0 && f != (int)h) r2 = q.pages[f].R[sk & 31];
                         }
                     }
-                }
-                if (__ballot(ncr != 0)) {
-                    int tot;
-                    const int c = nc + wave_excl_scan(ncr, tot);
-                    nc += __builtin_amdgcn_readfirstlane(tot);
-                    for (int j = 0; j < ncr; ++j) {
-                        const int32_t u = j == 0 ? vi.z : (j == 1 ? vi.w : A.out_dst[vi.x + j]);
-                        if (c + j < Narrow::C) {
-                            L.cu[c + j] = u; L.ck[c + j] = kk + Lv; L.ct[c + j] = bt;
-                            if (q.track) L.cw[c + j] = W;
-                        } else if (c + j < A.cand_cap) {
-                            cu[c + j] = u; ck[c + j] = kk + Lv; cW[c + j] = W; ct[c + j] = bt;
+                    const bool rec = chk && pg >= 0 && rgen(r2) == q.gen;
+                    const bool ov = act && !(rec && b0 <= rval(r2));
+                    lx = ov ? min(lx, m) : 0;
+                    if (ov && m > 0) chunks += lx >= 32 && m > 32 ? 2 : 1;
+                    lx += wave_extend(seg, q, lx == 64 && m > 64, qp + 64, sp + 64, m - 64, chunks);
+                    const ull om = __ballot(ov);
+                    const int32_t p = n1 + lanes_below(om);
+                    n1 += __popcll(om);
+                    int ncr = 0;
+                    const int32_t o = b0 + lx, W = cw0 + lx;
+                    if (ov) {
+                        if (pg < 0) {
+                            atomicOr(&S.flags, F_GROW);
                         } else {
-                            atomicOr(&S.flags, F_LIST);
+                            ncr = record_entry(q, S, sv, sk, o, W, pg, chk && !rec, lv, o == lv ? 1 : 0, lmax);
+                            if (p < Narrow::N) {
+                                L.oe[p] = make_int4(sv, sk, o, pg); L.ol[p] = lv; L.ob[p] = sb;
+                                if (q.track) L.ow[p] = W;
+                                if (q.tb) L.ot[p] = ct0;
+                            } else {   // more than a narrow list: it goes on in the wide path
+                                L0.e[p] = make_int4(sv, sk, o, page_word(pg, o, lv));
+                                if (q.track) L0.w[p] = W;
+                                if (q.tb) L0.t[p] = ct0;
+                                if ((p & (SAMP - 1)) == 0) S.samp[p / SAMP] = skey(sv, sk);
+                            }
                         }
                     }
+                    if (__ballot(ncr != 0)) put_crossings(S, A, L, cu, ck, cW, ct, nc, ncr != 0, o1, lv - b0 <= 64, sv, sk + lv, W, ct0);
+                    wave_lds_order();
                 }
             }
             adm += n1;
         }
         wave_lds_order();
         // ========== crossings, in rounds ==========
-        int32_t xlo = n1, xhi = s == 0 ? n : n1;
-        const int32_t preset = s == 0 ? n : 0;   // the start entries have their trace records
+        int32_t xhi = n1;
+        if (s == 0) {
+            // the start entries: extended where they stand, their trace records are there
+            const bool act = lane < n;
+            const int ix = act ? lane : 0;
+            const int4 e = L.oe[ix];
+            const int32_t lv = L.ol[ix], t = q.tb ? L.ot[ix] : -1;
+            const int64_t sb = L.ob[ix];
+            const int32_t m = act ? min(q.qlen - (e.y + e.z), lv - e.z) : 0;
+            const bool near = lv - e.z <= 64;
+            const Out o1 = load_out(vinfo, vsucc, e.x, act && near);
+            const int64_t qp = q.q0 + (m > 0 ? e.y + e.z : 0), sp = sb + (m > 0 ? e.z : 0);
+            int32_t lx = min(first64(seg, q, qp, sp, m > 0), m);
+            if (m > 0) chunks += lx >= 32 && m > 32 ? 2 : 1;
+            lx += wave_extend(seg, q, lx == 64 && m > 64, qp + 64, sp + 64, m - 64, chunks);
+            const int32_t o = e.z + lx;
+            int ncr = 0;
+            if (act) {
+                ncr = record_entry(q, S, e.x, e.y, o, lx, e.w, true, lv, o == lv ? 1 : 0, lmax);
+                L.oe[lane].z = o;
+                if (q.track) L.ow[lane] = lx;
+            }
+            if (__ballot(ncr != 0)) put_crossings(S, A, L, cu, ck, cW, ct, nc, ncr != 0, o1, near, e.x, e.y + lv, lx, t);
+            xhi = n;
+            wave_lds_order();
+        }
         bool timed = false;
         ull tr = 0;
         for (round = 0;; ++round) {
-            if (xlo < xhi) {
-                // extend the entries created by the previous round (or the starts)
-                const int32_t idx = xlo + lane;
-                const bool act = idx < xhi;
-                const int32_t ix = act ? idx : xlo;
-                const int4 e = L.oe[ix];
-                const int32_t Lv = L.ol[ix];
-                const int64_t sb = L.ob[ix];
-                const int32_t W0 = q.track ? L.ow[ix] : 0;
-                int32_t t = q.tb ? L.ot[ix] : -1;
-                const int32_t v = e.x, k = e.y, o0 = e.z;
-                const bool push = q.tb && act && idx >= preset;
-                const int32_t m = act ? min(q.qlen - (k + o0), Lv - o0) : 0;
-                const int4 vi = vinfo[v];
-                const ull probe = __hip_atomic_load(&q.mkey[push ? (dhash(dkey(v, t)) & q.mask) : 0], __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_AGENT);
-                const int64_t qp = q.q0 + (m > 0 ? k + o0 : 0), sp = sb + (m > 0 ? o0 : 0);
-                const ull x = win32(q.rd, qp) ^ win32(A.seg, sp);
-                int32_t lx = 0;
-                if (m > 0) {
-                    ++chunks;
-                    lx = min(x ? (int32_t)(__clzll((long long)x) >> 1) : 32, m);
-                }
-                lx += wave_extend(A, q, lx == 32 && m > 32, qp + 32, sp + 32, m - 32, chunks);
-                const int32_t o = o0 + lx, W = W0 + lx;
-                int ncr = 0;
-                if (act) {
-                    ncr = record_entry(q, S, v, k, o, W, e.w, true, Lv, o == Lv ? vi.y : 0, lmax);
-                    if (push) t = trace_push_from(q, S, v, t, probe);
-                    L.oe[idx].z = o;
-                    if (q.track) L.ow[idx] = W;
-                    if (q.tb) L.ot[idx] = t;
-                }
-                if (__ballot(ncr != 0)) {
-                    int tot;
-                    const int c = nc + wave_excl_scan(ncr, tot);
-                    nc += __builtin_amdgcn_readfirstlane(tot);
-                    for (int j = 0; j < ncr; ++j) {
-                        const int32_t u = j == 0 ? vi.z : (j == 1 ? vi.w : A.out_dst[vi.x + j]);
-                        if (c + j < Narrow::C) {
-                            L.cu[c + j] = u; L.ck[c + j] = k + Lv; L.ct[c + j] = t;
-                            if (q.track) L.cw[c + j] = W;
-                        } else if (c + j < A.cand_cap) {
-                            cu[c + j] = u; ck[c + j] = k + Lv; cW[c + j] = W; ct[c + j] = t;
-                        } else {
-                            atomicOr(&S.flags, F_LIST);
-                        }
-                    }
-                }
-                wave_lds_order();
-            }
             const int f1 = __builtin_amdgcn_readfirstlane(S.flags | ((S.dirn > half || S.mn > half) ? F_GROW : 0));
             if (f1) { code = NR_FLAGS; val = f1; break; }
-            if (xhi + nc > Narrow::N) { code = NR_ROUNDS; break; }   // may outgrow the narrow lists
+            if (xhi + nc > Narrow::N || nc > Narrow::C) { code = NR_ROUNDS; break; }   // may outgrow the narrow lists
             if (nc == 0) break;
             if (!timed) { timed = true; tr = wall_clock64(); }
-            // claim never-seen diagonals.  One wave holds every candidate, so equal
-            // ones meet here and no atomic is needed: the lowest lane takes the
-            // diagonal, with the largest W among them, and the extension of the
-            // next pass writes its record.
+            // Claim and extend in one step: a candidate carries its vertex's label
+            // (from its predecessor's out-edge record), so that the directory, the
+            // record at the key's home slot, the trace map and the windows are read
+            // together, before it is known whether the diagonal was seen.  One wave
+            // holds every candidate, so equal ones meet here and no atomic is
+            // needed: the lowest lane takes the diagonal, with the largest W.
             const bool act = lane < nc;
             const int ci = act ? lane : 0;
             const int32_t u = L.cu[ci], kc = L.ck[ci], tc = q.tb ? L.ct[ci] : -1;
+            const int32_t lv = L.cl[ci];
+            const int64_t sb = L.cb[ci];
             int32_t wc = q.track ? L.cw[ci] : 0;
-            const ull key = dkey(u, kc >> 5);
-            const uint32_t h = dhash(key) & q.mask;
-            const ull dprobe = __hip_atomic_load(&q.dir[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const int4 lab = A.vlab[u];
+            const ull key = dkey(u, kc >> 5), tkey = dkey(u, tc);
+            const uint32_t h = dhash(key) & q.mask, th = dhash(tkey) & q.mask;
+            const ull dprobe = dir_load(q.dir, h);
             const ull wh = __hip_atomic_load(&q.pages[h].R[kc & 31], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            int ds = -1;
-            bool fresh = false;
-            if (act) {
-                ds = dir_settle(q.dir, q.mask, key, h, dprobe, &S.dirn);
-                if (ds < 0) {
-                    atomicOr(&S.flags, F_GROW);
-                } else {
-                    const ull w = ds == (int)h ? wh : __hip_atomic_load(&q.pages[ds].R[kc & 31], __ATOMIC_RELAXED,
-                                                                        __HIP_MEMORY_SCOPE_AGENT);
-                    fresh = rgen(w) != q.gen;
-                }
+            const ull tprobe = q.tb ? dir_load(q.mkey, th) : 0ull;
+            const int32_t m = act ? min(q.qlen - kc, lv) : 0;
+            const Out o1 = load_out(vinfo, vsucc, u, act && lv <= 64);
+            const int64_t qp = q.q0 + (m > 0 ? kc : 0), sp = sb;
+            int32_t lx = min(first64(seg, q, qp, sp, m > 0), m);
+            // seen, when the page is there and holds a record of this query
+            bool fresh = act && !(dprobe == key && rgen(wh) == q.gen);
+            ull walk = __ballot(fresh && dprobe != key && dprobe != 0);   // another key's slot: look further
+            uint32_t hs = h;
+            ull dp = dprobe;
+            while (walk) {
+                const bool mine = (walk >> lane) & 1;
+                if (mine) { hs = (hs + 1) & q.mask; dp = dir_load(q.dir, hs); }
+                const bool hit = mine && dp == key;
+                if (hit && rgen(__hip_atomic_load(&q.pages[hs].R[kc & 31], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == q.gen)
+                    fresh = false;
+                walk = __ballot(mine && dp != key && dp != 0 && hs != h);
             }
             ull todo = __ballot(fresh), lead = 0;
             while (todo) {
@@ -1097,20 +1244,39 @@ __device__ __attribute__((noinline)) void narrow_scores(int64_t karg) {
                     if (lane == f) wc = wm;
                 }
             }
-            if ((lead >> lane) & 1) {
-                const int32_t p = xhi + lanes_below(lead);
-                L.oe[p] = make_int4(u, kc, 0, ds);
-                L.ol[p] = lab.z; L.ob[p] = lab_base(lab);
-                if (q.track) L.ow[p] = wc;
-                if (q.tb) L.ot[p] = tc;
-            }
-            wave_lds_order();
-            const int f2 = __builtin_amdgcn_readfirstlane(S.flags | (S.dirn > half ? F_GROW : 0));
-            if (f2) { code = NR_FLAGS; val = f2; break; }
-            xlo = xhi;
-            xhi += __popcll(lead);
-            cross += xhi - xlo;
             nc = 0;
+            if (lead) {
+                const bool ld = (lead >> lane) & 1;
+                bool made;
+                const int ds = wave_settle(q.dir, q.mask, key, hs, dp, ld, made, S);
+                if (ld && m > 0) chunks += lx >= 32 && m > 32 ? 2 : 1;
+                lx += wave_extend(seg, q, ld && lx == 64 && m > 64, qp + 64, sp + 64, m - 64, chunks);
+                int32_t t = -1;
+                if (q.tb) {   // Algorithm 5: T gets (u, tc) unless the pair is there
+                    t = wave_settle(q.mkey, q.mask, tkey, th, tprobe, ld, made, S, true);
+                    if (ld && t >= 0) { q.Tv[t] = u; q.Tt[t] = tc; }
+                }
+                const int32_t W = wc + lx;
+                int ncr = 0;
+                if (ld) {
+                    if (ds < 0 || (q.tb && t < 0)) {
+                        atomicOr(&S.flags, F_GROW);
+                    } else {
+                        ncr = record_entry(q, S, u, kc, lx, W, ds, true, lv, lx == lv ? 1 : 0, lmax);
+                        const int32_t p = xhi + lanes_below(lead);
+                        L.oe[p] = make_int4(u, kc, lx, ds);
+                        L.ol[p] = lv; L.ob[p] = sb;
+                        if (q.track) L.ow[p] = W;
+                        if (q.tb) L.ot[p] = t;
+                    }
+                }
+                const int add = __popcll(lead);
+                xhi += add;
+                cross += add;
+                wave_lds_order();   // the candidates are read before the next ones are written
+                if (__ballot(ncr != 0)) put_crossings(S, A, L, cu, ck, cW, ct, nc, ncr != 0, o1, lv <= 64, u, kc + lv, W, t);
+                wave_lds_order();
+            }
         }
         if (timed) t_rounds += wall_clock64() - tr;
         ntot = xhi;
@@ -1118,12 +1284,8 @@ __device__ __attribute__((noinline)) void narrow_scores(int64_t karg) {
         work += ntot;
         int32_t amax = 0, imax = 0;
         if (q.track) {
-            for (int m = 32; m >= 1; m >>= 1) {
-                lmax.x = max(lmax.x, __shfl_xor(lmax.x, m, 64));
-                lmax.y = max(lmax.y, __shfl_xor(lmax.y, m, 64));
-            }
-            amax = __builtin_amdgcn_readfirstlane(lmax.x);
-            imax = __builtin_amdgcn_readfirstlane(lmax.y);
+            amax = wave_max(lmax.x);
+            if (LEARN) imax = wave_max(lmax.y);
         }
         // this lane's entry of the score's list: outputs first, then crossing entries
         const bool ent = lane < ntot;
@@ -1149,14 +1311,14 @@ __device__ __attribute__((noinline)) void narrow_scores(int64_t karg) {
             code = NR_END; val = GWFA_ST_OK;
             break;
         }
-        if (A.max_score >= 0 && s >= A.max_score) { code = NR_END; val = GWFA_ST_MAX_SCORE; break; }
+        if (max_score >= 0 && s >= max_score) { code = NR_END; val = GWFA_ST_MAX_SCORE; break; }
         if (ntot == 0) { code = NR_END; val = q.ve >= 0 ? GWFA_ST_UNREACHABLE : GWFA_ST_MAX_SCORE; break; }
         if (q.ve < 0 && s > q.qlen + 1) { code = NR_END; val = GWFA_ST_MAX_SCORE; break; }
         // ========== merge of the crossing entries, and Algorithm 4 ==========
         {
             bool keep = ent;
-            if (MODE == 1 && A.prune == GWFA_PRUNE_HEURISTIC && amax > A.a_diff) {
-                keep = ent && amax - (e.y + e.z + eW) < A.a_diff;
+            if (MODE == 1 && amax > a_diff) {
+                keep = ent && amax - (e.y + e.z + eW) < a_diff;
                 const ull dm = __ballot(ent && !keep);
                 if (ent && !keep) q.pages[e.w].R[e.y & 31] = mkR(q.gen, e.z);   // the record stays
                 dropped += __popcll(dm);
@@ -1220,12 +1382,7 @@ __device__ __attribute__((noinline)) void narrow_scores(int64_t karg) {
     }
     // ========== what is left for the wide path ==========
     if (code == NR_ROUNDS) {
-        if (q.track) {
-            for (int m = 32; m >= 1; m >>= 1) {
-                lmax.x = max(lmax.x, __shfl_xor(lmax.x, m, 64));
-                lmax.y = max(lmax.y, __shfl_xor(lmax.y, m, 64));
-            }
-        }
+        if (q.track) lmax = make_int2(wave_max(lmax.x), wave_max(lmax.y));
         if (lane < min(ntot, Narrow::N)) {
             const int4 e = L.oe[lane];
             const int32_t p = lane < n1 ? lane : xb + lane - n1;
@@ -1235,18 +1392,10 @@ __device__ __attribute__((noinline)) void narrow_scores(int64_t karg) {
             if (lane < n1 && (lane & (SAMP - 1)) == 0) S.samp[lane / SAMP] = skey(e.x, e.y);
         }
         // the candidates to where the wide path looks for them
-        int32_t u2[2], k2[2], w2[2], t2[2];
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int c = lane + 64 * j;
-            u2[j] = L.cu[c]; k2[j] = L.ck[c]; w2[j] = q.track ? L.cw[c] : 0; t2[j] = L.ct[c];
-        }
+        const int cj = min(lane, Narrow::C - 1);
+        const int32_t u2 = L.cu[cj], k2 = L.ck[cj], w2 = q.track ? L.cw[cj] : 0, t2 = L.ct[cj];
         wave_lds_order();
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int c = lane + 64 * j;
-            if (c < nc) put_cand(S, A, cu, ck, cW, ct, c, u2[j], k2[j], w2[j], t2[j]);
-        }
+        if (lane < min(nc, Narrow::C)) put_cand(S, A, cu, ck, cW, ct, lane, u2, k2, w2, t2);
         for (int c = Narrow::C + lane; c < min(nc, (int)SH::CS); c += 64) {
             S.csu[c] = cu[c]; S.csk[c] = ck[c]; S.cst[c] = ct[c];
         }
@@ -1373,7 +1522,7 @@ __device__ __forceinline__ void expand_part(const KArgs& A, const Q& q, Shared<B
             ++chunks;
             lx = min(x ? (int32_t)(__clzll((long long)x) >> 1) : 32, m);
         }
-        lx += wave_extend(A, q, lx == 32 && m > 32, q.q0 + i + 32, sb + bo + 32, m - 32, chunks);
+        lx += wave_extend(seg, q, lx == 32 && m > 32, q.q0 + i + 32, sb + bo + 32, m - 32, chunks);
         const ull om = __ballot(ov);
         const int32_t o = bo + lx, W = W0 + lx;
         int ncr = 0;
