@@ -113,9 +113,6 @@ __device__ __forceinline__ ull win32(const ull* __restrict__ w, int64_t p) {
 // one holding the range's last base (both stores end with two words of
 // padding, so that word exists): a window that starts inside the range never
 // reaches past it, and the words clamped are never used.
-// ALL = false loads only the words the step needs (fewer registers in
-// flight, for call sites where registers are scarce).
-template <bool ALL = true>
 __device__ __forceinline__ int32_t lcp(const ull* __restrict__ qw, int64_t qp, int64_t qmax, const ull* __restrict__ sw,
                                        int64_t sp, int64_t smax, int32_t lim, uint32_t& chunks) {
     int32_t l = 0;
@@ -126,14 +123,8 @@ __device__ __forceinline__ int32_t lcp(const ull* __restrict__ qw, int64_t qp, i
         ull a[5], b[5];
 #pragma unroll
         for (int j = 0; j < 5; ++j) {
-            if (ALL) {
-                a[j] = qw[min(qi + j, qmax)];
-                b[j] = sw[min(si + j, smax)];
-            } else {
-                const bool need = 32 * (j - 1) < rem;   // word j is needed by windows j-1 and j
-                a[j] = need ? qw[qi + j] : 0ull;
-                b[j] = need ? sw[si + j] : 0ull;
-            }
+            a[j] = qw[min(qi + j, qmax)];
+            b[j] = sw[min(si + j, smax)];
         }
         int32_t m = 0;
         bool stop = false;
@@ -1429,20 +1420,23 @@ __device__ __attribute__((noinline)) void narrow_scores(int64_t karg) {
 // shifts (the group before and the group after fill in at the ends); each
 // source makes up to three candidates, which go to the wave's ring in LDS in
 // list order.  The next group's entries and labels are loaded meanwhile.
-//   Outputs: whenever the ring holds 64 candidates, one per lane: records,
-// out-edge records, labels and windows are loaded, the run is extended, and
-// the outputs are written behind the wave's previous ones (at most three per
-// source, so the part's place in the new list is known from the start).
+//   Outputs: whenever the ring holds 64 candidates, one per lane: labels are
+// loaded, then the windows they lead to, out-edge records and records, the run
+// is extended, and the outputs are written behind the wave's previous ones (at
+// most three per source, so the part's place in the new list is known from the
+// start).
 // Before, a block staged 256 entries in LDS, each lane computed three output
 // slots of which one is taken on average, and three barriers and a scan
 // ordered the outputs of every batch (800 vector instructions a wave and
 // batch; here about 160 per 64 sources and 220 per 64 outputs).  What bounds
-// it now: issue when four workgroups share a CU, the two round trips of
-// extend() when they do not.  Per call: 20,000 reads on the 1 Mb DAG 135.5 ->
-// 122 ms, 3,001 noisy reads on the 10 Mb graph 459 -> 435 ms (its hardest
-// read alone takes 400), 500 reads of 100 kb through loops 518 -> 383 ms (its
-// lists of 25,000 to 50,000 entries are merged by the bitmap now, which holds
-// 65,536 positions instead of 32,768).
+// it now: latency.  The waves wait 72 to 77% of their cycles, for the two round
+// trips of a batch and for its stores, with the vector units 33 to 42% busy;
+// the registers (128, four waves a SIMD) leave room for no deeper queue.  Per
+// call: 20,000 reads on the 1 Mb DAG 135.5 -> 119 ms, 3,001 noisy reads on the
+// 10 Mb graph 459 -> 408 ms (its hardest read takes most of that alone), 500
+// reads of 100 kb through loops 518 -> 237 ms (its lists of 25,000 to 50,000
+// entries are merged by the bitmap now, which holds 65,536 positions instead
+// of 32,768).
 // ---------------------------------------------------------------------------
 // x of the lane below (above), `edge` in lane 0 (63)
 __device__ __forceinline__ int32_t lane_below(int32_t x, int32_t edge) {
@@ -1494,60 +1488,125 @@ __device__ __forceinline__ void expand_part(const KArgs& A, const Q& q, Shared<B
             if (q.tb) x.t = Ls.t[p];
         }
     };
-    // up to 64 candidates from the head of the ring
-    auto extend = [&](int cnt) {
-        const bool act = lane < cnt;
-        const int ri = (head + (act ? lane : 0)) & (SH::Ring::N - 1);
-        const int4 c = R.e[ri];
-        const int32_t t = q.tb ? R.t[ri] : -1;
-        const int32_t W0 = q.track ? R.w[ri] : 0;
-        const int32_t v = c.x, kk = c.y, bo = c.z & 0x7fffffff;
-        const bool chk = c.z < 0;
-        int d = c.w;
-        const int4 lab = vlab[v];
-        const int4 vi = vinfo[v];
-        // a missing page means no record: the output is admitted and needs the
-        // page, so it is created now
-        if (act && d < 0) d = dir_insert(q.dir, q.mask, dkey(v, kk >> 5), &S.dirn);
-        const ull rw = q.pages[max(d, 0)].R[kk & 31];
-        const int32_t Lv = lab.z;
-        const int64_t sb = lab_base(lab);
-        const int32_t i = kk + bo;
-        const int32_t m = act ? min(q.qlen - i, Lv - bo) : 0;
-        const ull x = win32(q.rd, q.q0 + (m > 0 ? i : 0)) ^ win32(seg, sb + (m > 0 ? bo : 0));
-        const bool rec = chk && d >= 0 && rgen(rw) == q.gen;
-        const bool ov = act && !(rec && bo <= rval(rw));
-        int32_t lx = 0;
-        if (ov && m > 0) {
-            ++chunks;
-            lx = min(x ? (int32_t)(__clzll((long long)x) >> 1) : 32, m);
-        }
-        lx += wave_extend(seg, q, lx == 32 && m > 32, q.q0 + i + 32, sb + bo + 32, m - 32, chunks);
-        const ull om = __ballot(ov);
-        const int32_t o = bo + lx, W = W0 + lx;
-        int ncr = 0;
-        if (ov) {
-            if (d < 0) {
-                atomicOr(&S.flags, F_GROW);
-            } else {
-                ncr = record_entry(q, S, v, kk, o, W, d, chk && !rec, Lv, o == Lv ? vi.y : 0, lmax);
-                const int32_t j = nout + lanes_below(om);
-                Ld.e[place0 + j] = make_int4(v, kk, o, page_word(d, o, Lv));
-                if (q.track) Ld.w[place0 + j] = W;
-                if (q.tb) Ld.t[place0 + j] = t;
-                if ((j & (SAMP - 1)) == 0 && j < SAMP * SH::SEGS) samp[j / SAMP] = skey(v, kk);
-                if (j == 0) S.partK[wv] = skey(v, kk);
+    // Batches of up to 64 candidates, one per lane.  PIPE: in two stages behind
+    // the sources, `one` with its labels on the way, `two` its first windows,
+    // out-edges and records; a batch is finished two groups after it was taken, so
+    // both round trips pass under the work on the groups between.  Where a wave's
+    // part is long: 1 Mb DAG 122.3 -> 118.8 ms, 10 Mb graph 429 -> 406 ms against
+    // one batch after the other (both at 256 lanes).  Not with eight waves, where
+    // parts are of one or two groups and the empty stages cost more than they
+    // hide: 50 reads of 1 kb 297 -> 305 us, 500 reads through loops 236 -> 238 ms
+    // with it.
+    constexpr bool PIPE = NW < 8;
+    struct Taken {
+        int n;                   // candidates (0: none)
+        int4 c;                  // the ring's entry
+        int32_t t, w;
+        int4 lab;
+    };
+    Taken one, two;
+    int4 vi;
+    ull rw, dp;                  // record (at the key's home slot when the page is not known), that slot's key
+    ull a0, a1, b0, b1;          // first window's words
+    one.n = 0;
+    two.n = 0;
+    // the batch whose windows are here
+    auto finish = [&]() {
+        if (!PIPE || two.n > 0) {
+            const bool act = lane < two.n;
+            const int32_t v = two.c.x, kk = two.c.y, bo = two.c.z & 0x7fffffff;
+            const bool chk = two.c.z < 0;
+            int d = two.c.w;
+            if (PIPE && __ballot(act && d < 0)) {
+                // a missing page means no record: the output is admitted and needs
+                // the page, so it is created now
+                const ull key = dkey(v, kk >> 5);
+                const uint32_t h = dhash(key) & q.mask;
+                if (act && d < 0) {
+                    d = dp == key ? (int)h : dir_settle(q.dir, q.mask, key, h, dp, &S.dirn);
+                    if (d >= 0 && d != (int)h) rw = q.pages[d].R[kk & 31];
+                    else if (dp != key) rw = 0;      // not there when the record was read: never seen
+                }
+            }
+            const int32_t Lv = two.lab.z;
+            const int64_t sb = lab_base(two.lab);
+            const int32_t i = kk + bo;
+            const int32_t m = act ? min(q.qlen - i, Lv - bo) : 0;
+            const int qs = (int)((q.q0 + i) & 31) * 2, ss = (int)((sb + bo) & 31) * 2;
+            const ull x = ((a0 << qs) | ((a1 >> 1) >> (63 - qs))) ^ ((b0 << ss) | ((b1 >> 1) >> (63 - ss)));
+            const bool rec = chk && d >= 0 && rgen(rw) == q.gen;
+            const bool ov = act && !(rec && bo <= rval(rw));
+            int32_t lx = 0;
+            if (ov && m > 0) {
+                ++chunks;
+                lx = min(x ? (int32_t)(__clzll((long long)x) >> 1) : 32, m);
+            }
+            lx += wave_extend(seg, q, lx == 32 && m > 32, q.q0 + i + 32, sb + bo + 32, m - 32, chunks);
+            const ull om = __ballot(ov);
+            const int32_t o = bo + lx, W = two.w + lx;
+            int ncr = 0;
+            if (ov) {
+                if (d < 0) {
+                    atomicOr(&S.flags, F_GROW);
+                } else {
+                    ncr = record_entry(q, S, v, kk, o, W, d, chk && !rec, Lv, o == Lv ? vi.y : 0, lmax);
+                    const int32_t j = nout + lanes_below(om);
+                    Ld.e[place0 + j] = make_int4(v, kk, o, page_word(d, o, Lv));
+                    if (q.track) Ld.w[place0 + j] = W;
+                    if (q.tb) Ld.t[place0 + j] = two.t;
+                    if ((j & (SAMP - 1)) == 0 && j < SAMP * SH::SEGS) samp[j / SAMP] = skey(v, kk);
+                    if (j == 0) S.partK[wv] = skey(v, kk);
+                }
+            }
+            nout += __popcll(om);
+            // crossing candidates of the whole wave in one allocation, skipped when
+            // no lane reached a vertex end
+            if (__ballot(ncr != 0)) {
+                const int cp = wave_alloc(ncr, &S.ncand);
+                if (ncr) put_out_edges(S, A, cu, ck, cW, ct, cp, vi, kk + Lv, W, two.t);
             }
         }
-        nout += __popcll(om);
-        // crossing candidates of the whole wave in one allocation, skipped when
-        // no lane reached a vertex end
-        if (__ballot(ncr != 0)) {
-            const int cp = wave_alloc(ncr, &S.ncand);
-            if (ncr) put_out_edges(S, A, cu, ck, cW, ct, cp, vi, kk + Lv, W, t);
+    };
+    // the windows of the batch whose labels are here (a lane without bases to
+    // compare reads the first words)
+    auto windows = [&]() {
+        if (!PIPE || two.n > 0) {
+            const int32_t bo = two.c.z & 0x7fffffff, i = two.c.y + bo;
+            const bool any = lane < two.n && i < q.qlen && bo < two.lab.z;
+            const ull* const qp = q.rd + ((q.q0 + (any ? i : 0)) >> 5);
+            const ull* const sp = seg + ((lab_base(two.lab) + (any ? bo : 0)) >> 5);
+            a0 = qp[0]; a1 = qp[1];
+            b0 = sp[0]; b1 = sp[1];
         }
-        head = (head + cnt) & (SH::Ring::N - 1);
-        fill -= cnt;
+    };
+    // its out-edges and records
+    auto records = [&]() {
+        if (!PIPE || two.n > 0) {
+            vi = vinfo[two.c.x];
+            if (PIPE) {
+                const uint32_t h = dhash(dkey(two.c.x, two.c.y >> 5)) & q.mask;
+                dp = 0;
+                if (lane < two.n && two.c.w < 0) dp = __hip_atomic_load(&q.dir[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                rw = q.pages[two.c.w < 0 ? (int)h : two.c.w].R[two.c.y & 31];
+            } else {
+                if (lane < two.n && two.c.w < 0) two.c.w = dir_insert(q.dir, q.mask, dkey(two.c.x, two.c.y >> 5), &S.dirn);
+                rw = q.pages[max(two.c.w, 0)].R[two.c.y & 31];
+            }
+        }
+    };
+    // the next candidates of the ring
+    auto take = [&]() {
+        one.n = min(fill, 64);
+        if (!PIPE || one.n > 0) {
+            const bool act = lane < one.n;
+            const int ri = (head + (act ? lane : 0)) & (SH::Ring::N - 1);
+            one.c = R.e[ri];
+            one.t = q.tb ? R.t[ri] : -1;
+            one.w = q.track ? R.w[ri] : 0;
+            one.lab = vlab[one.c.x];
+            head = (head + one.n) & (SH::Ring::N - 1);
+            fill -= one.n;
+        }
     };
 
     Ent cur, nxt, nn;
@@ -1565,7 +1624,7 @@ __device__ __forceinline__ void expand_part(const KArgs& A, const Q& q, Shared<B
     for (int32_t g = lo; g < hi; g += 64) {
         fetch(g + 128, nn);
         // all 64 sources at once, or 16 at a time when the ring has no room for
-        // so many candidates (made again then: they are not kept over extend)
+        // so many candidates (made again then: they are not kept over the batches)
         for (int sub = 0, width = 64; sub < 64;) {
         asm volatile("" : "+v"(cur.e.y));
         const int32_t v = cur.e.x, k = cur.e.y, o0 = cur.e.z, ds0 = page_of(cur.e.w);
@@ -1636,7 +1695,10 @@ __device__ __forceinline__ void expand_part(const KArgs& A, const Q& q, Shared<B
         }
         const bool flush = sub >= 64 && g + 64 >= hi;
         wave_lds_order();
-        while (fill >= 64 || (flush && fill > 0)) extend(min(fill, 64));
+        while (fill >= 64 || (flush && (fill > 0 || (PIPE && (one.n > 0 || two.n > 0))))) {
+            if (PIPE) { finish(); two = one; windows(); records(); take(); }
+            else      { take(); two = one; records(); windows(); finish(); }
+        }
         wave_lds_order();
         }
         cur = nxt;

@@ -133,6 +133,31 @@ def test_hubs_around_the_merge_limits(G, lanes):
     _compare(gw, ctx, [hub_case(rng, deg, False) for deg in (255, 256, 257, 511, 1023, 1024, 1025)], 0)
 
 
+@pytest.mark.parametrize("lanes", [64, 128, 256, 512])
+def test_start_windows_around_whole_batches(G, lanes):
+    """Wide lists whose parts hold one, two and three groups of 64 entries, one
+    or two fewer and one more: first, middle and last batches of a wave, full
+    and of a few candidates.  With the number of workgroups given the exact
+    batch keeps the width asked for."""
+    gw, ctx = G
+    rng = np.random.default_rng(8500)
+    cases, windows = [], []
+    for b in (1, 2, 3):
+        for n in (lanes * b + d for d in (-2, -1, 0, 1)):
+            labels, edges, q, v_s = hub_case(rng, 5, False)
+            labels[0] = _dna(rng, 1700)
+            cases.append((labels, edges, labels[0][n:].encode() + q[70:], v_s))
+            j0 = int(rng.integers(0, 1700 - n + 1))
+            windows.append((j0, j0 + n - 1))
+    ctx.config(lanes=lanes, groups=len(cases))
+    try:
+        for a_diff in (0, 100000):
+            print(f"[gpu-narrow] lanes {lanes}: {len(cases)} whole batches, a_diff={a_diff}", flush=True)
+            _compare(gw, ctx, cases, a_diff, windows)
+    finally:
+        ctx.config()
+
+
 def test_batches_around_the_widening_limits(G):
     """Exact batches small enough to be resident at more lanes per query are
     launched with more: the same results at every size."""
