@@ -2380,7 +2380,7 @@ __global__ __launch_bounds__(BLOCK, waves_per_simd(BLOCK, MODE)) void k_align(KA
     }
     // counters: once per workgroup, on one of STAT_SLOTS lines.  Twelve atomics
     // per query on one line bounded short queries (87 ns a query, whatever the
-    // number of workgroups: 20,011 seeded reads of 200 bases 1.9 ms, now 0.4).
+    // number of workgroups: 20,011 seeded reads of 200 bases 1.9 ms, 0.4 without them).
     if (threadIdx.x < 16 && A.stats && S.acc[threadIdx.x])
         atomicAdd(&A.stats[16 * (blockIdx.x % STAT_SLOTS) + threadIdx.x], S.acc[threadIdx.x]);
 }
