@@ -537,7 +537,7 @@ static int first_tier(const KArgs& A) {
 // query still has a workgroup resident at once.  An exact wavefront has work
 // for all of them: 500 reads of 100 kb take 384 ms at 256 lanes (half the
 // slots empty) and 237 ms at 512; with more queries than slots the wider
-// workgroups cost throughput (20,000 reads of 10 kb: 119 and 185 ms).
+// workgroups cost throughput (20,000 reads of 10 kb: 115 and 185 ms).
 static int launch_lanes(const gwfa_ctx* ctx, const KArgs& A, int64_t n) {
     int lanes = ctx->lanes;
     if (A.prune != GWFA_PRUNE_NONE || A.dump || ctx->groups > 0) return lanes;

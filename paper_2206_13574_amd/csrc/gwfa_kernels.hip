@@ -1432,8 +1432,8 @@ __device__ __attribute__((noinline)) void narrow_scores(int64_t karg) {
 // it now: latency.  The waves wait 72 to 77% of their cycles, for the two round
 // trips of a batch and for its stores, with the vector units 33 to 42% busy;
 // the registers (128, four waves a SIMD) leave room for no deeper queue.  Per
-// call: 20,000 reads on the 1 Mb DAG 135.5 -> 119 ms, 3,001 noisy reads on the
-// 10 Mb graph 459 -> 408 ms (its hardest read takes most of that alone), 500
+// call: 20,000 reads on the 1 Mb DAG 135.5 -> 115 ms, 3,001 noisy reads on the
+// 10 Mb graph 459 -> 397 ms (its hardest read takes most of that alone), 500
 // reads of 100 kb through loops 518 -> 237 ms (its lists of 25,000 to 50,000
 // entries are merged by the bitmap now, which holds 65,536 positions instead
 // of 32,768).
