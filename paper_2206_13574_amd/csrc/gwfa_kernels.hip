@@ -825,7 +825,8 @@ __device__ __forceinline__ int32_t wave_extend(const ull* __restrict__ seg, cons
             need &= need - 1;
         }
         const int64_t uq = __shfl(qp, l, 64), us = __shfl(sp, l, 64);
-        const int32_t ur = on ? __shfl(rem, l, 64) : 0;
+        const int32_t lr = __shfl(rem, l, 64);       // by every lane: a lane that sits an exchange out is read as 0
+        const int32_t ur = on ? lr : 0;
         int32_t e = 0;
         uint32_t w = 0;
         bool go = on;
