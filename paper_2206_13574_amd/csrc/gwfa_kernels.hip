@@ -814,14 +814,16 @@ __device__ __forceinline__ int32_t wave_extend(const ull* __restrict__ seg, cons
         return ext;
     }
     while (need) {
-        int l = __builtin_ctzll(need);               // the run this lane's 16 work on
+        // the run this lane's 16 work on (without one: they stand at the first
+        // run, whose bases are in the stores; a lane without a run may be past them)
+        int l = __builtin_ctzll(need);
         bool on = true;
         need &= need - 1;
 #pragma unroll
         for (int j = 1; j < 4; ++j) {
             const bool any = need != 0;
             const int b = any ? __builtin_ctzll(need) : 0;
-            if ((lane >> 4) == j) { l = b; on = any; }
+            if ((lane >> 4) == j) { l = any ? b : l; on = any; }
             need &= need - 1;
         }
         const int64_t uq = __shfl(qp, l, 64), us = __shfl(sp, l, 64);

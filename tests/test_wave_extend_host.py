@@ -1,10 +1,14 @@
 """The wave's run extension (wave_extend in gwfa_kernels.hip) on the host: all
 64 lanes take part in every exchange between lanes (an exchange under a branch
-of some lanes reads nothing from the others), and every run gets its length.
+of some lanes reads nothing from the others), no lane reads a word outside the
+packed stores, and every run gets its length.
 
 The function's text is compiled for the host with the wave's lanes as
 coroutines; each exchange is a switch point and checks that every lane stands
-at the same one.  Lengths and counted words are compared with a plain loop."""
+at the same one, and the window load checks its words against the store,
+(N + 31) / 32 + 2 words for N bases.  Callers hand every lane's position
+already advanced by one or two words, so a lane without a run may stand past
+the store's end.  Lengths and counted words are compared with a plain loop."""
 import re
 import subprocess
 
@@ -60,8 +64,15 @@ template <class T> static T lane_value(int line, T x, int l) { return (T)exchang
 #define __builtin_amdgcn_readlane(x, l) lane_value(__LINE__, (x), (l))
 #define readlane64(x, l) lane_value(__LINE__, (int64_t)(x), (l))
 static const ull* store[2];
+static int64_t words[2];
 static ull win32(const ull* w, int64_t p) {
+    const int k = w == store[0] ? 0 : 1;
     const int64_t wi = p >> 5;
+    if (p < 0 || wi + 1 >= words[k]) {
+        printf("lane %d reads words %lld, %lld of %s store of %lld words\n", cur, (long long)wi, (long long)wi + 1,
+               k ? "the label" : "the query", (long long)words[k]);
+        exit(1);
+    }
     const int sh = (int)(p & 31) * 2;
     return (w[wi] << sh) | ((w[wi + 1] >> 1) >> (63 - sh));
 }
@@ -70,7 +81,7 @@ static ull win32(const ull* w, int64_t p) {
 _MAIN = r"""
 static struct Lane { bool more; int64_t qp, sp; int32_t rem, ext; uint32_t chunks; } L[64];
 static std::vector<ull> pack(const std::vector<int>& b) {
-    std::vector<ull> w((b.size() + 31) / 32 + 2 + 4, 0);
+    std::vector<ull> w((b.size() + 31) / 32 + 2, 0);
     for (size_t i = 0; i < b.size(); ++i) w[i / 32] |= (ull)b[i] << (62 - 2 * (i % 32));
     return w;
 }
@@ -94,6 +105,7 @@ int main() {
         for (int i = 0; i < errs; ++i) s[rng() % n] ^= 1;
         const std::vector<ull> qw = pack(q), sw = pack(s);
         store[0] = qw.data(); store[1] = sw.data();
+        words[0] = qw.size(); words[1] = sw.size();
             const int step = round & 1 ? 32 : 64, runs = (round / 2) % 8;
         for (int l = 0; l < 64; ++l) {   // no run: anywhere a batch's lane may stand, the store's end among them
             const int at = rng() % 3 == 0 ? n - (int)(rng() % 3) : (int)(rng() % n);
@@ -154,5 +166,5 @@ def run(tmp_path_factory):
     return subprocess.run([str(d / "t")], capture_output=True, text=True, timeout=120)
 
 
-def test_runs_have_their_lengths(run):
+def test_runs_stay_in_the_stores_and_have_their_lengths(run):
     assert run.returncode == 0 and run.stdout == "ok\n", run.stdout + run.stderr
