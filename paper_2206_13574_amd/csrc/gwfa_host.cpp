@@ -173,13 +173,15 @@ int ensure_tier(gwfa_ctx* ctx, int ti) {
     size_t bytes = (size_t)t.stride * (size_t)t.groups;
     hipError_t e = hipMalloc((void**)&t.arena, bytes);
     if (e != hipSuccess && ti > 0 && ctx->tier[0].arena) {
-        // make room: the pruned runs' arenas come back when they are needed
-        // (hipFree waits for the kernels using them)
+        // make room: pruned runs have the configured tier as well (see
+        // set_first_tier; hipFree waits for the kernels using the arenas)
         free_tier(ctx->tier[0]);
         ctx->epoch++;
         e = hipMalloc((void**)&t.arena, bytes);
+        (void)hipGetLastError();
     }
     if (e != hipSuccess) {
+        (void)hipGetLastError();   // the caller gets the code; an error left here would be its next launch's
         t.arena = nullptr;
         ctx->err = "arena allocation of " + std::to_string(bytes) + " bytes failed";
         return GWFA_ERR_NOMEM;
@@ -562,6 +564,20 @@ static int set_tier(gwfa_ctx* ctx, KArgs& A, int ti, const int32_t* order, int32
     return GWFA_OK;
 }
 
+// The same for the tier a call starts on, *ti: first_tier's, or the configured
+// one where the small arenas have no room (they were given back for a larger
+// tier, or the caller holds the memory).
+static int set_first_tier(gwfa_ctx* ctx, KArgs& A, const int32_t* order, int32_t n, int* groups, int* ti) {
+    *ti = first_tier(A);
+    int rc = set_tier(ctx, A, *ti, order, n, groups);
+    if (rc == GWFA_ERR_NOMEM && *ti == 0) {
+        ctx->err.clear();
+        *ti = 1;
+        rc = set_tier(ctx, A, *ti, order, n, groups);
+    }
+    return rc;
+}
+
 // Tiers ti0, ti0+1, ...: after each launch the queries that overflowed
 // their working memory (if any) are re-run on the next, larger tier.  When
 // `launched` the launch of tier ti0 has already been issued.  The first
@@ -590,13 +606,13 @@ static int run_tiers(gwfa_ctx* ctx, KArgs& A, int ti0, int32_t n, bool launched,
     return GWFA_OK;
 }
 
-// Checks the arguments and launches the screen pass and the first tier; A is
-// left as run_tiers(.., launched) takes it.
+// Checks the arguments and launches the screen pass and the first tier, *ti; A
+// is left as run_tiers(.., launched) takes it.
 static int align_begin(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const uint64_t* d_packed,
                        const int64_t* d_read_off, const int32_t* d_v_start, const int32_t* d_v_end,
                        const int32_t* d_order, const gwfa_opts* opts, gwfa_result* d_res, int32_t* d_path_buf,
                        int64_t path_cap, int64_t* d_path_used, float* d_dump, int64_t dump_cap, int64_t* d_dump_count,
-                       hipStream_t st, const int32_t* d_start_off, const int32_t* d_start_hi, KArgs& A) {
+                       hipStream_t st, const int32_t* d_start_off, const int32_t* d_start_hi, KArgs& A, int* ti) {
     int rc = fill_args(ctx, g, n_reads, d_packed, d_read_off, d_v_start, d_v_end, opts, d_res, d_path_buf,
                        path_cap, d_path_used, d_dump, dump_cap, d_dump_count, A);
     if (!rc) rc = ensure_lists(ctx, n_reads);
@@ -607,7 +623,7 @@ static int align_begin(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, cons
     A.n_reads = n_reads;
     HIPCHK(ctx, gwfa_launch_screen(A, ctx->d_valid, st));
     int groups = 0;
-    rc = set_tier(ctx, A, first_tier(A), ctx->d_valid, n_reads, &groups);
+    rc = set_first_tier(ctx, A, ctx->d_valid, n_reads, &groups, ti);
     if (rc) return rc;
     HIPCHK(ctx, gwfa_launch_align(A, launch_lanes(ctx, A, n_reads), groups, st));
     return GWFA_OK;
@@ -623,11 +639,12 @@ static int align_dev(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const 
     HIPCHK(ctx, hipSetDevice(ctx->device));
     hipStream_t st = hip_stream ? (hipStream_t)hip_stream : ctx->stream;
     KArgs A;
+    int ti = 0;
     const int rc = align_begin(ctx, g, n_reads, d_packed, d_read_off, d_v_start, d_v_end, d_order, opts, d_res,
                                d_path_buf, path_cap, d_path_used, d_dump, dump_cap, d_dump_count, st, d_start_off,
-                               d_start_hi, A);
+                               d_start_hi, A, &ti);
     if (rc || n_reads == 0) return rc;
-    return run_tiers(ctx, A, first_tier(A), n_reads, true, st);
+    return run_tiers(ctx, A, ti, n_reads, true, st);
 }
 
 int gwfa_align_batch_dev(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const uint64_t* d_packed,
@@ -724,6 +741,7 @@ struct gwfa_plan {
     int device = 0;
     int64_t epoch = 0;
     KArgs A;
+    int tier = 0;                      // that the captured launch runs on
     const int32_t* order = nullptr;
     int32_t n_reads = 0;
     hipStream_t cap = nullptr;
@@ -760,7 +778,7 @@ int gwfa_plan_create(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const 
     KArgs S0 = p->A;   // the screen pass reads the caller's order
     S0.order = d_order;
     S0.n_reads = n_reads;
-    if (!rc) rc = set_tier(ctx, p->A, first_tier(p->A), ctx->d_valid, n_reads, &groups);   // allocates before the capture
+    if (!rc) rc = set_first_tier(ctx, p->A, ctx->d_valid, n_reads, &groups, &p->tier);   // allocates before the capture
     if (rc) { gwfa_plan_destroy(p); return rc; }
     p->epoch = ctx->epoch;   // after any reallocation of the context's lists
     hipError_t e = hipStreamCreateWithFlags(&p->cap, hipStreamNonBlocking);
@@ -800,7 +818,7 @@ int gwfa_plan_finish(gwfa_plan* p, void* hip_stream) {
     hipStream_t st = hip_stream ? (hipStream_t)hip_stream : ctx->stream;
     HIPCHK(ctx, hipSetDevice(ctx->device));
     KArgs A = p->A;
-    return run_tiers(ctx, A, first_tier(A), p->n_reads, true, st);
+    return run_tiers(ctx, A, p->tier, p->n_reads, true, st);
 }
 
 // The workspace of the host-buffer entry points, at least `bytes`.
@@ -885,11 +903,12 @@ int gwfa_align_batch(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const 
         e = gwfa_launch_pack((const uint8_t*)d + o_ascii, bases, (unsigned long long*)(d + o_packed), words, nullptr, st);
     int out_rc = e == hipSuccess ? GWFA_OK : dev_fail(ctx, e, "query upload");
     KArgs A;
+    int ti = 0;
     if (out_rc == GWFA_OK)
         out_rc = align_begin(ctx, g, n_reads, (const uint64_t*)(d + o_packed), (const int64_t*)(d + o_off),
                              (const int32_t*)(d + o_vs), nullptr, (const int32_t*)(d + o_order), opts,
                              (gwfa_result*)(d + o_res), want_path ? (int32_t*)(d + o_path) : nullptr,
-                             want_path ? path_cap : 0, (int64_t*)(d + o_used), nullptr, 0, nullptr, st, nullptr, nullptr, A);
+                             want_path ? path_cap : 0, (int64_t*)(d + o_used), nullptr, 0, nullptr, st, nullptr, nullptr, A, &ti);
     if (out_rc == GWFA_OK) {
         // results and the overflow count in one wait; after a re-run (rare) again
         char* const h = ctx->stage + STAGE_IN;
@@ -904,7 +923,7 @@ int gwfa_align_batch(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const 
         };
         e = fetch();
         if (e == hipSuccess && *ctx->h_retry > 0) {
-            out_rc = run_tiers(ctx, A, first_tier(A), n_reads, true, st);
+            out_rc = run_tiers(ctx, A, ti, n_reads, true, st);
             if (out_rc == GWFA_OK) e = fetch();
         }
         if (out_rc == GWFA_OK && e == hipSuccess) {

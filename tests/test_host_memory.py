@@ -1,0 +1,83 @@
+"""Working memory on a device without room: which tier a call runs on, what is
+given back for what, and what captured plans and the caller see of it.  Host
+code on a stand-in for the HIP runtime (tests/fake_hip)."""
+import ctypes
+
+import pytest
+
+from paper_2206_13574_amd import gwfa
+from tests import fake_hip
+
+PRUNED = dict(prune=gwfa.PRUNE_HEURISTIC, a_diff=50)
+MIB = 1 << 20
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    return fake_hip.Host(fake_hip.compile_host(str(tmp_path_factory.mktemp("host"))))
+
+
+@pytest.fixture
+def H(host):
+    """(host, context, graph) on an empty device of 288 GiB; tiers of 2^14,
+    2^18, 2^20 and 2^22 pages."""
+    host.reset()
+    ctx = host.context(lanes=64, dir_log2_max=18, list_cap=1 << 17, dir_factor=256)
+    g = host.graph(ctx)
+    yield host, ctx, g
+    host.lib.gwfa_graph_destroy(g)
+    host.lib.gwfa_ctx_destroy(ctx)
+    assert host.lib.fake_used() == 0
+
+
+def test_tiers_in_order(H):
+    """With room: exact calls on the configured tier, pruned ones on the small
+    arenas, overflows on the next."""
+    h, ctx, g = H
+    assert h.align(ctx, g) == 0 and h.dirs() == [18]
+    assert h.align(ctx, g, **PRUNED) == 0 and h.dirs() == [14]
+    h.lib.fake_overflow(14, 7)
+    h.lib.fake_overflow(18, 3)
+    assert h.align(ctx, g, **PRUNED) == 0 and h.dirs() == [14, 18, 20]
+
+
+@pytest.mark.parametrize("prune", [PRUNED, dict(prune=gwfa.PRUNE_LEARNED)])
+def test_pruned_calls_run_where_the_small_arenas_do_not_fit(H, prune):
+    """The rest of the device is the caller's: a pruned call, and a plan of
+    one, take the configured tier, as exact calls do."""
+    h, ctx, g = H
+    assert h.align(ctx, g) == 0
+    h.lib.fake_memory(h.lib.fake_used() + 64 * MIB)
+    h.launches()
+    assert h.align(ctx, g, **prune) == 0 and h.dirs() == [18]
+    rc, p = h.plan(ctx, g, **prune)
+    assert rc == 0
+    assert h.lib.gwfa_plan_launch(p, None) == 0 and h.dirs() == [18]
+    h.lib.fake_overflow(18, 2)
+    h.lib.fake_memory(288 * fake_hip.GIB)
+    assert h.lib.gwfa_plan_launch(p, None) == 0 and h.lib.gwfa_plan_finish(p, None) == 0
+    assert h.dirs() == [18, 20]
+    h.lib.gwfa_plan_destroy(p)
+    assert h.lib.gwfa_last_error(ctx) == b"" and h.lib.fake_last_error() == 0
+
+
+def test_pruned_calls_after_the_small_arenas_made_room(H):
+    """An overflow whose tier fits only in the small arenas' place: the calls
+    after it run on that tier."""
+    h, ctx, g = H
+    assert h.align(ctx, g, **PRUNED) == 0 and h.dirs() == [14]
+    small = h.lib.fake_used()
+    h.lib.fake_overflow(14, 5)
+    assert h.align(ctx, g, **PRUNED) == 0
+    both = h.lib.fake_used()
+    assert h.dirs() == [14, 18]
+    # the same on a device that holds one of the two
+    h.lib.gwfa_ctx_config(ctx, 64, 0, 18, 1 << 17, 256)
+    h.lib.fake_memory(both - small // 2)
+    h.lib.fake_overflow(14, 0)
+    assert h.align(ctx, g, **PRUNED) == 0 and h.dirs() == [14]
+    h.lib.fake_overflow(14, 5)
+    assert h.align(ctx, g, **PRUNED) == 0 and h.lib.fake_last_error() == 0
+    assert [x[0] for x in h.launches()] == [14, 18]     # the first one's arenas are given back by now
+    for _ in range(3):
+        assert h.align(ctx, g, **PRUNED) == 0 and h.dirs() == [18]
