@@ -195,8 +195,12 @@ int ensure_tier(gwfa_ctx* ctx, int ti) {
 }
 
 // Share of the device memory free at configuration time that each tier's
-// arenas may take (all of them can be allocated at once).
+// arenas may take, and all of them together: the rest is the caller's, whose
+// graph, queries and results may come later.  Where the shares add up to more,
+// tier 2 gives way (it re-runs the few queries that outgrow the configured
+// tier).
 constexpr double TIER_SHARE[N_TIERS] = {0.14, 0.60, 0.20, 0.05};
+constexpr double TIERS_SHARE = 0.85;
 
 void set_tiers(gwfa_ctx* ctx, int32_t dir_log2_max, int32_t list_cap) {
     // default: as many persistent workgroups as can be resident at once
@@ -213,7 +217,8 @@ void set_tiers(gwfa_ctx* ctx, int32_t dir_log2_max, int32_t list_cap) {
     for (int i = 0; i < N_TIERS; ++i) free_tier(ctx->tier[i]);
     size_t free_b = 0, total_b = 0;
     if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || free_b == 0) free_b = (size_t)64 << 30;
-    for (int i = 0; i < N_TIERS; ++i) {
+    int64_t held = 0;
+    for (const int i : {0, 1, 3, 2}) {
         Tier& t = ctx->tier[i];
         if (i == 0) {
             t.dir_log2_max = std::min(dir_log2_max, PRUNED_DIR_LOG2);
@@ -226,8 +231,10 @@ void set_tiers(gwfa_ctx* ctx, int32_t dir_log2_max, int32_t list_cap) {
         layout(t);
         // larger tiers keep as many workgroups as their share of memory holds:
         // queries that overflow the first tier still run at full width
-        const int64_t fit = (int64_t)(TIER_SHARE[i] * (double)free_b) / t.stride;
-        t.groups = (int)std::max<int64_t>(4, std::min<int64_t>(i == 0 ? pruned_groups : groups, fit));
+        const int64_t share = std::min((int64_t)(TIER_SHARE[i] * (double)free_b),
+                                       (int64_t)(TIERS_SHARE * (double)free_b) - held);
+        t.groups = (int)std::max<int64_t>(4, std::min<int64_t>(i == 0 ? pruned_groups : groups, share / t.stride));
+        held += t.groups * t.stride;
     }
 }
 

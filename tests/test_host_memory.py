@@ -81,3 +81,22 @@ def test_pruned_calls_after_the_small_arenas_made_room(H):
     assert [x[0] for x in h.launches()] == [14, 18]     # the first one's arenas are given back by now
     for _ in range(3):
         assert h.align(ctx, g, **PRUNED) == 0 and h.dirs() == [18]
+
+
+@pytest.mark.parametrize("cfg", [dict(), dict(lanes=64), dict(lanes=256, dir_log2_max=18, list_cap=1 << 17),
+                                 dict(lanes=64, dir_log2_max=18, list_cap=1 << 17), dict(lanes=64, dir_log2_max=19)])
+def test_tiers_leave_the_caller_memory(host, cfg):
+    """All tiers together take at most 85% of the memory free when the context
+    is configured; the configured tier keeps its 60%."""
+    host.reset()
+    ctx = host.context(**cfg)
+    g = host.graph(ctx)
+    for d in range(14, 24):
+        host.lib.fake_overflow(d, 1)
+    before = host.lib.fake_used()
+    assert host.align(ctx, g, n=100_000, **PRUNED) == 0
+    ls = host.launches()
+    assert len(ls) == 4 and all(x[5] for x in ls)
+    assert host.lib.fake_used() - before <= 0.85 * 288 * fake_hip.GIB
+    host.lib.gwfa_graph_destroy(g)
+    host.lib.gwfa_ctx_destroy(ctx)
