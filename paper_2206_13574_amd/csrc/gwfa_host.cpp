@@ -166,29 +166,38 @@ void free_tier(Tier& t) {
     t.arena = nullptr;
 }
 
+// Allocates device memory; where there is none left, the small arenas make
+// room: pruned runs have the configured tier as well (set_first_tier), and
+// hipFree waits for the kernels using them.  *p is null on failure.  A failed
+// attempt leaves no error behind, which the caller's next launch would report.
+template <class T>
+bool dev_alloc(gwfa_ctx* ctx, T** p, int64_t bytes) {
+    hipError_t e = hipMalloc((void**)p, (size_t)bytes);
+    if (e == hipSuccess) return true;
+    (void)hipGetLastError();
+    if (ctx->tier[0].arena) {
+        free_tier(ctx->tier[0]);
+        ctx->epoch++;
+        e = hipMalloc((void**)p, (size_t)bytes);
+        if (e == hipSuccess) return true;
+        (void)hipGetLastError();
+    }
+    *p = nullptr;
+    return false;
+}
+
 int ensure_tier(gwfa_ctx* ctx, int ti) {
     Tier& t = ctx->tier[ti];
     if (t.arena) return GWFA_OK;
     layout(t);
     size_t bytes = (size_t)t.stride * (size_t)t.groups;
-    hipError_t e = hipMalloc((void**)&t.arena, bytes);
-    if (e != hipSuccess && ti > 0 && ctx->tier[0].arena) {
-        // make room: pruned runs have the configured tier as well (see
-        // set_first_tier; hipFree waits for the kernels using the arenas)
-        free_tier(ctx->tier[0]);
-        ctx->epoch++;
-        e = hipMalloc((void**)&t.arena, bytes);
-        (void)hipGetLastError();
-    }
-    if (e != hipSuccess) {
-        (void)hipGetLastError();   // the caller gets the code; an error left here would be its next launch's
-        t.arena = nullptr;
+    if (!dev_alloc(ctx, &t.arena, (int64_t)bytes)) {
         ctx->err = "arena allocation of " + std::to_string(bytes) + " bytes failed";
         return GWFA_ERR_NOMEM;
     }
     // generation 0 everywhere: record words of generation 0 read as "never
     // seen" for every query (queries use generations 1, 2, ...)
-    e = hipMemset(t.arena, 0, bytes);
+    hipError_t e = hipMemset(t.arena, 0, bytes);
     if (e == hipSuccess) e = hipDeviceSynchronize();   // finished before any kernel on any stream uses it
     if (e != hipSuccess) return dev_fail(ctx, e, "arena clear");
     return GWFA_OK;
@@ -406,15 +415,13 @@ int gwfa_graph_create(gwfa_ctx* ctx, int32_t n_vtx, const uint8_t* seq, const in
     const int64_t words = gwfa_packed_words(bases);
     uint8_t* d_ascii = nullptr;
     int32_t* d_err = nullptr;
-    bool ok = hipMalloc((void**)&g->d_seg, words * 8) == hipSuccess &&
-              hipMalloc((void**)&g->d_seg_off, (size_t)(n_vtx + 1) * 8) == hipSuccess &&
-              hipMalloc((void**)&g->d_out_off, (size_t)(n_vtx + 1) * 4) == hipSuccess &&
-              hipMalloc((void**)&g->d_out_dst, dst.size() * 4) == hipSuccess &&
-              hipMalloc((void**)&g->d_vinfo, (size_t)n_vtx * sizeof(int4)) == hipSuccess &&
-              hipMalloc((void**)&g->d_vlab, (size_t)n_vtx * sizeof(int4)) == hipSuccess &&
-              hipMalloc((void**)&g->d_vsucc, vsucc.size() * sizeof(int4)) == hipSuccess &&
-              hipMalloc((void**)&d_ascii, (size_t)std::max<int64_t>(bases, 1)) == hipSuccess &&
-              hipMalloc((void**)&d_err, 4) == hipSuccess;
+    bool ok = dev_alloc(ctx, &g->d_seg, words * 8) && dev_alloc(ctx, &g->d_seg_off, ((int64_t)n_vtx + 1) * 8) &&
+              dev_alloc(ctx, &g->d_out_off, ((int64_t)n_vtx + 1) * 4) &&
+              dev_alloc(ctx, &g->d_out_dst, (int64_t)dst.size() * 4) &&
+              dev_alloc(ctx, &g->d_vinfo, n_vtx * (int64_t)sizeof(int4)) &&
+              dev_alloc(ctx, &g->d_vlab, n_vtx * (int64_t)sizeof(int4)) &&
+              dev_alloc(ctx, &g->d_vsucc, (int64_t)(vsucc.size() * sizeof(int4))) &&
+              dev_alloc(ctx, &d_ascii, std::max<int64_t>(bases, 1)) && dev_alloc(ctx, &d_err, 4);
     if (!ok) {
         if (d_ascii) (void)hipFree(d_ascii);
         if (d_err) (void)hipFree(d_err);
@@ -525,11 +532,8 @@ static int ensure_lists(gwfa_ctx* ctx, int32_t n_reads) {
     ctx->retry_cap = 0;
     ctx->epoch++;   // captured plans hold the old lists
     for (auto& p : ctx->d_retry)
-        if (hipMalloc((void**)&p, (size_t)n_reads * 4) != hipSuccess) { p = nullptr; return GWFA_ERR_NOMEM; }
-    if (hipMalloc((void**)&ctx->d_valid, (size_t)n_reads * 4) != hipSuccess) {
-        ctx->d_valid = nullptr;
-        return GWFA_ERR_NOMEM;
-    }
+        if (!dev_alloc(ctx, &p, (int64_t)n_reads * 4)) return GWFA_ERR_NOMEM;
+    if (!dev_alloc(ctx, &ctx->d_valid, (int64_t)n_reads * 4)) return GWFA_ERR_NOMEM;
     ctx->retry_cap = n_reads;
     return GWFA_OK;
 }
@@ -839,10 +843,7 @@ static int ensure_ws(gwfa_ctx* ctx, int64_t bytes) {
     ctx->ws = nullptr;
     ctx->ws_bytes = 0;
     const int64_t want = std::max<int64_t>(bytes, STAGE_IN);
-    if (hipMalloc((void**)&ctx->ws, (size_t)want) != hipSuccess) {
-        ctx->ws = nullptr;
-        return GWFA_ERR_NOMEM;
-    }
+    if (!dev_alloc(ctx, &ctx->ws, want)) return GWFA_ERR_NOMEM;
     ctx->ws_bytes = want;
     return GWFA_OK;
 }
@@ -1032,25 +1033,16 @@ int gwfa_cigar_dev(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const ui
         if (ctx->d_cig_arena) (void)hipFree(ctx->d_cig_arena);
         ctx->d_cig_arena = nullptr;
         ctx->cig_bytes = 0;
-        if (hipMalloc((void**)&ctx->d_cig_arena, need) != hipSuccess) {
-            ctx->d_cig_arena = nullptr;
-            return GWFA_ERR_NOMEM;
-        }
+        if (!dev_alloc(ctx, &ctx->d_cig_arena, (int64_t)need)) return GWFA_ERR_NOMEM;
         ctx->cig_bytes = need;
     }
-    if (!ctx->d_cig_queue && hipMalloc((void**)&ctx->d_cig_queue, 4) != hipSuccess) {
-        ctx->d_cig_queue = nullptr;
-        return GWFA_ERR_NOMEM;
-    }
+    if (!ctx->d_cig_queue && !dev_alloc(ctx, &ctx->d_cig_queue, 4)) return GWFA_ERR_NOMEM;
     // the largest distances first (a counting sort: distances are small)
     if (ctx->cig_order_cap < n_reads) {
         if (ctx->d_cig_order) (void)hipFree(ctx->d_cig_order);
         ctx->d_cig_order = nullptr;
         ctx->cig_order_cap = 0;
-        if (hipMalloc((void**)&ctx->d_cig_order, (size_t)n_reads * 4) != hipSuccess) {
-            ctx->d_cig_order = nullptr;
-            return GWFA_ERR_NOMEM;
-        }
+        if (!dev_alloc(ctx, &ctx->d_cig_order, (int64_t)n_reads * 4)) return GWFA_ERR_NOMEM;
         ctx->cig_order_cap = n_reads;
     }
     {
@@ -1098,11 +1090,7 @@ int gwfa_mlp_grad_dev(gwfa_ctx* ctx, const float* d_feat, int64_t n, int64_t fea
     if (n > 0 && (!d_feat || !d_label)) return GWFA_ERR_ARG;
     hipStream_t st = hip_stream ? (hipStream_t)hip_stream : ctx->stream;
     HIPCHK(ctx, hipSetDevice(ctx->device));
-    if (!ctx->d_mlp_scr)
-        if (hipMalloc((void**)&ctx->d_mlp_scr, (size_t)gwfa_mlp_scratch_floats() * 4) != hipSuccess) {
-            ctx->d_mlp_scr = nullptr;
-            return GWFA_ERR_NOMEM;
-        }
+    if (!ctx->d_mlp_scr && !dev_alloc(ctx, &ctx->d_mlp_scr, gwfa_mlp_scratch_floats() * 4)) return GWFA_ERR_NOMEM;
     HIPCHK(ctx, gwfa_launch_mlp_grad(d_feat, feat_stride, sc, d_label, n, pos_weight, d_w, ctx->d_mlp_scr,
                                      d_grad, d_loss, st));
     return GWFA_OK;

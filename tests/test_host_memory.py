@@ -3,6 +3,7 @@ given back for what, and what captured plans and the caller see of it.  Host
 code on a stand-in for the HIP runtime (tests/fake_hip)."""
 import ctypes
 
+import numpy as np
 import pytest
 
 from paper_2206_13574_amd import gwfa
@@ -100,3 +101,47 @@ def test_tiers_leave_the_caller_memory(host, cfg):
     assert host.lib.fake_used() - before <= 0.85 * 288 * fake_hip.GIB
     host.lib.gwfa_graph_destroy(g)
     host.lib.gwfa_ctx_destroy(ctx)
+
+
+def _lists(h, ctx, g):
+    return h.align(ctx, g, n=20_000_000)
+
+
+def _host_batch(h, ctx, g):
+    n = 1 << 20
+    off, res = np.arange(n + 1, dtype=np.int64) * 100, np.zeros(n, gwfa.RESULT_DTYPE)
+    return h.lib.gwfa_align_batch(ctx, g, n, np.full(n * 100, 65, np.uint8).ctypes.data_as(fake_hip._P),
+                                  off.ctypes.data_as(fake_hip._P), np.zeros(n, np.int32).ctypes.data_as(fake_hip._P),
+                                  ctypes.byref(gwfa.opts(traceback=False)), res.ctypes.data_as(fake_hip._P), None, 0,
+                                  None)
+
+
+def _cigar(h, ctx, g, n=1000, dist=3000):
+    res = np.zeros(n, gwfa.RESULT_DTYPE)
+    res["dist"], res["path_len"] = dist, 10
+    off = np.arange(n + 1, dtype=np.int64) * 10_000
+    b = h._buf.ctypes.data_as(fake_hip._P)
+    return h.lib.gwfa_cigar_dev(ctx, g, n, b, off.ctypes.data_as(fake_hip._P), res.ctypes.data_as(fake_hip._P), b, b,
+                                0, b, b, b, None)
+
+
+def _grad(h, ctx, g):
+    b = h._buf.ctypes.data_as(fake_hip._P)
+    return h.lib.gwfa_mlp_grad_dev(ctx, b, 1, 8, b, b, 1.0, b, b, b, None)
+
+
+def _graph(h, ctx, g):
+    h.lib.gwfa_graph_destroy(h.graph(ctx, n_vtx=1_000_000))
+    return 0
+
+
+@pytest.mark.parametrize("call", [_lists, _host_batch, _cigar, _grad, _graph])
+def test_small_arenas_give_way_to_other_calls(H, call):
+    """With the device full, a call's own memory takes the place of the pruned
+    runs' arenas; pruned calls then run on the configured tier."""
+    h, ctx, g = H
+    assert h.align(ctx, g) == 0 and h.align(ctx, g, **PRUNED) == 0 and h.dirs() == [18, 14]
+    h.lib.fake_memory(h.lib.fake_used())
+    assert call(h, ctx, g) == 0 and h.lib.fake_last_error() == 0
+    h.lib.fake_memory(h.lib.fake_used())
+    assert h.align(ctx, g, **PRUNED) == 0 and h.dirs()[-1] == 18
