@@ -353,10 +353,13 @@ void gwfa_gfa_free(gwfa_gfa *g);
 
 /* ---- captured launches ---------------------------------------------------
  * A plan records the alignment of one device-resident batch (the arguments
- * of gwfa_align_batch_dev, fixed at creation) as a HIP graph: the reset of
- * the work queue and counters, the screen pass of the query parameters and
- * the first-tier launch of the persistent alignment kernel, kernels only.  gwfa_plan_launch replays it on
- * `hip_stream` (NULL = context stream), asynchronously, with no host work.
+ * of gwfa_align_batch_dev, fixed at creation) as a HIP graph: the screen pass
+ * of the query parameters, which also resets the work queue and counters, and
+ * the first-tier launch of the persistent alignment kernel, kernels only.
+ * gwfa_plan_launch replays it on `hip_stream` (NULL = context stream),
+ * asynchronously, with no host work; only where another call on the context
+ * has taken over its working memory (a full device) is it recorded again
+ * first.
  * gwfa_plan_finish then synchronises that stream and re-runs, eagerly, the
  * queries that overflowed the first tier's working memory (usually none);
  * after it returns, results are complete exactly as after

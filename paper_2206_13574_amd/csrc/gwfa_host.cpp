@@ -37,6 +37,7 @@ struct Tier {
     int32_t sort_cap = 1 << 15;
     int32_t groups = 0;
     char* arena = nullptr;
+    int64_t freed = 0;                 // times the arenas were given back (plans captured on them are captured again)
     int64_t stride = 0;
     int64_t o_hdr = 0, o_dir = 0, o_pages = 0, o_mkey = 0, o_tv = 0, o_tt = 0, o_lists = 0, o_cand = 0, o_sort = 0;
 };
@@ -98,7 +99,7 @@ struct gwfa_ctx {
     float* d_mlp_scale = nullptr;
     bool mlp_loaded = false;
     float* d_mlp_scr = nullptr;        // training: the workgroups' partial gradients
-    int64_t epoch = 0;                 // bumped when working memory is freed (invalidates plans)
+    int64_t epoch = 0;                 // bumped when the lists move or the context is configured (invalidates plans)
     char* d_cig_arena = nullptr;       // base-level alignment: per-workgroup regions
     size_t cig_bytes = 0;
     int32_t* d_cig_queue = nullptr;
@@ -162,8 +163,10 @@ bool all_acgt(const uint8_t* s, int64_t n) {
 }
 
 void free_tier(Tier& t) {
-    if (t.arena) (void)hipFree(t.arena);
+    if (!t.arena) return;
+    (void)hipFree(t.arena);
     t.arena = nullptr;
+    t.freed++;
 }
 
 // Allocates device memory; where there is none left, the small arenas make
@@ -177,7 +180,6 @@ bool dev_alloc(gwfa_ctx* ctx, T** p, int64_t bytes) {
     (void)hipGetLastError();
     if (ctx->tier[0].arena) {
         free_tier(ctx->tier[0]);
-        ctx->epoch++;
         e = hipMalloc((void**)p, (size_t)bytes);
         if (e == hipSuccess) return true;
         (void)hipGetLastError();
@@ -751,8 +753,9 @@ struct gwfa_plan {
     gwfa_ctx* ctx = nullptr;
     int device = 0;
     int64_t epoch = 0;
-    KArgs A;
-    int tier = 0;                      // that the captured launch runs on
+    KArgs A;                           // the captured launch's arguments
+    int tier = 0;                      // the tier it runs on, and how often that had been given back
+    int64_t freed = 0;
     const int32_t* order = nullptr;
     int32_t n_reads = 0;
     hipStream_t cap = nullptr;
@@ -767,6 +770,35 @@ void gwfa_plan_destroy(gwfa_plan* p) {
     if (p->graph) (void)hipGraphDestroy(p->graph);
     if (p->cap) (void)hipStreamDestroy(p->cap);
     delete p;
+}
+
+// Captures the plan's launches on the tier its batch starts on now.
+static int plan_capture(gwfa_plan* p) {
+    gwfa_ctx* ctx = p->ctx;
+    if (p->exec) (void)hipGraphExecDestroy(p->exec);
+    if (p->graph) (void)hipGraphDestroy(p->graph);
+    p->exec = nullptr;
+    p->graph = nullptr;
+    int groups = 0;
+    KArgs S0 = p->A;   // the screen pass reads the caller's order
+    S0.order = p->order;
+    S0.n_reads = p->n_reads;
+    const int rc = set_first_tier(ctx, p->A, ctx->d_valid, p->n_reads, &groups, &p->tier);   // allocates before the capture
+    if (rc) return rc;
+    p->freed = ctx->tier[p->tier].freed;
+    hipError_t e = hipSuccess;
+    if (!p->cap) e = hipStreamCreateWithFlags(&p->cap, hipStreamNonBlocking);
+    if (e == hipSuccess) e = hipStreamBeginCapture(p->cap, hipStreamCaptureModeThreadLocal);
+    if (e == hipSuccess) {
+        // kernels only (no memset nodes): the screen pass (which resets the
+        // queue and the counters), then the first tier
+        hipError_t e1 = gwfa_launch_screen(S0, ctx->d_valid, p->cap);
+        if (e1 == hipSuccess) e1 = gwfa_launch_align(p->A, launch_lanes(ctx, p->A, p->n_reads), groups, p->cap);
+        e = hipStreamEndCapture(p->cap, &p->graph);
+        if (e1 != hipSuccess) e = e1;
+    }
+    if (e == hipSuccess) e = hipGraphInstantiate(&p->exec, p->graph, nullptr, nullptr, 0);
+    return e == hipSuccess ? GWFA_OK : dev_fail(ctx, e, "plan capture");
 }
 
 int gwfa_plan_create(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const uint64_t* d_packed,
@@ -785,29 +817,9 @@ int gwfa_plan_create(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const 
     int rc = fill_args(ctx, g, n_reads, d_packed, d_read_off, d_v_start, nullptr, opts, d_res, d_path_buf,
                        path_cap, d_path_used, nullptr, 0, nullptr, p->A);
     if (!rc) rc = ensure_lists(ctx, n_reads);
-    int groups = 0;
-    KArgs S0 = p->A;   // the screen pass reads the caller's order
-    S0.order = d_order;
-    S0.n_reads = n_reads;
-    if (!rc) rc = set_first_tier(ctx, p->A, ctx->d_valid, n_reads, &groups, &p->tier);   // allocates before the capture
+    if (!rc) rc = plan_capture(p);
     if (rc) { gwfa_plan_destroy(p); return rc; }
     p->epoch = ctx->epoch;   // after any reallocation of the context's lists
-    hipError_t e = hipStreamCreateWithFlags(&p->cap, hipStreamNonBlocking);
-    if (e == hipSuccess) e = hipStreamBeginCapture(p->cap, hipStreamCaptureModeThreadLocal);
-    if (e == hipSuccess) {
-        // kernels only (no memset nodes): the screen pass (which resets the
-        // queue and the counters), then the first tier
-        hipError_t e1 = gwfa_launch_screen(S0, ctx->d_valid, p->cap);
-        if (e1 == hipSuccess) e1 = gwfa_launch_align(p->A, launch_lanes(ctx, p->A, n_reads), groups, p->cap);
-        e = hipStreamEndCapture(p->cap, &p->graph);
-        if (e1 != hipSuccess) e = e1;
-    }
-    if (e == hipSuccess) e = hipGraphInstantiate(&p->exec, p->graph, nullptr, nullptr, 0);
-    if (e != hipSuccess) {
-        rc = dev_fail(ctx, e, "plan capture");
-        gwfa_plan_destroy(p);
-        return rc;
-    }
     *out = p;
     return GWFA_OK;
 }
@@ -818,6 +830,10 @@ int gwfa_plan_launch(gwfa_plan* p, void* hip_stream) {
     if (p->epoch != ctx->epoch) return GWFA_ERR_ARG;
     hipStream_t st = hip_stream ? (hipStream_t)hip_stream : ctx->stream;
     HIPCHK(ctx, hipSetDevice(ctx->device));
+    if (!p->exec || p->freed != ctx->tier[p->tier].freed) {   // its arenas were given back since (rare)
+        const int rc = plan_capture(p);
+        if (rc) return rc;
+    }
     HIPCHK(ctx, hipGraphLaunch(p->exec, st));
     return GWFA_OK;
 }

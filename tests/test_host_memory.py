@@ -145,3 +145,26 @@ def test_small_arenas_give_way_to_other_calls(H, call):
     assert call(h, ctx, g) == 0 and h.lib.fake_last_error() == 0
     h.lib.fake_memory(h.lib.fake_used())
     assert h.align(ctx, g, **PRUNED) == 0 and h.dirs()[-1] == 18
+
+
+@pytest.mark.parametrize("by", ["finish", "call"])
+def test_plans_outlive_their_arenas(H, by):
+    """A pruned batch's plan whose arenas were given back, by its own finish or
+    by another call, is launched again like any other."""
+    h, ctx, g = H
+    rc, p = h.plan(ctx, g, **PRUNED)
+    assert rc == 0 and h.lib.gwfa_plan_launch(p, None) == 0 and h.lib.gwfa_plan_finish(p, None) == 0
+    assert h.dirs() == [14]
+    h.lib.fake_memory(180 * fake_hip.GIB)      # no room for the configured tier beside them
+    if by == "finish":
+        h.lib.fake_overflow(14, 3)
+        assert h.lib.gwfa_plan_launch(p, None) == 0 and h.lib.gwfa_plan_finish(p, None) == 0
+    else:
+        assert h.align(ctx, g) == 0
+    h.launches()
+    for _ in range(2):
+        assert h.lib.gwfa_plan_launch(p, None) == 0 and h.lib.gwfa_plan_finish(p, None) == 0
+        assert h.dirs() == [18]
+    # what ends a plan is what ended it before
+    assert h.align(ctx, g, n=200_000) == 0 and h.lib.gwfa_plan_launch(p, None) == gwfa.ERR_ARG
+    h.lib.gwfa_plan_destroy(p)
