@@ -1044,13 +1044,16 @@ int gwfa_cigar_dev(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const ui
     const int64_t per_cu = lds > 0 ? std::max<int64_t>(1, std::min<int64_t>(2048 / lanes, ((int64_t)160 << 10) / (lds + 512))) : 8;
     int64_t groups = std::min<int64_t>(std::max<int64_t>(n_ok, 1), (int64_t)ctx->n_cu * per_cu);
     groups = std::max<int64_t>(1, std::min<int64_t>(groups, ((int64_t)16 << 30) / A.arena_stride));
-    const size_t need = (size_t)(A.arena_stride * groups);
-    if (need > ctx->cig_bytes) {
+    if (A.arena_stride * groups > (int64_t)ctx->cig_bytes) {
         if (ctx->d_cig_arena) (void)hipFree(ctx->d_cig_arena);
         ctx->d_cig_arena = nullptr;
         ctx->cig_bytes = 0;
-        if (!dev_alloc(ctx, &ctx->d_cig_arena, (int64_t)need)) return GWFA_ERR_NOMEM;
-        ctx->cig_bytes = need;
+        // on a full device, as many workgroups as have room
+        while (!dev_alloc(ctx, &ctx->d_cig_arena, A.arena_stride * groups)) {
+            if (groups == 1) return GWFA_ERR_NOMEM;
+            groups = (groups + 1) / 2;
+        }
+        ctx->cig_bytes = (size_t)(A.arena_stride * groups);
     }
     if (!ctx->d_cig_queue && !dev_alloc(ctx, &ctx->d_cig_queue, 4)) return GWFA_ERR_NOMEM;
     // the largest distances first (a counting sort: distances are small)

@@ -168,3 +168,18 @@ def test_plans_outlive_their_arenas(H, by):
     # what ends a plan is what ended it before
     assert h.align(ctx, g, n=200_000) == 0 and h.lib.gwfa_plan_launch(p, None) == gwfa.ERR_ARG
     h.lib.gwfa_plan_destroy(p)
+
+
+def test_cigars_run_in_the_room_there_is(H):
+    """Distances of 3,000 ask for 18 MB a workgroup: the call takes as many
+    workgroups as the device has room for, down to one."""
+    h, ctx, g = H
+    for room, lo, hi in ((64 * fake_hip.GIB, 500, 1000), (8 * fake_hip.GIB, 100, 500), (100 * MIB, 1, 6), (30 * MIB, 1, 1)):
+        h.lib.gwfa_ctx_destroy(ctx)
+        ctx.value = h.context().value
+        h.lib.fake_memory(h.lib.fake_used() + room)
+        assert _cigar(h, ctx, g) == 0 and lo <= h.lib.fake_cigar_groups() <= hi, (room, h.lib.fake_cigar_groups())
+    h.lib.gwfa_ctx_destroy(ctx)
+    ctx.value = h.context().value
+    h.lib.fake_memory(h.lib.fake_used() + 10 * MIB)
+    assert _cigar(h, ctx, g) == gwfa.ERR_NOMEM
