@@ -566,7 +566,8 @@ static int set_tier(gwfa_ctx* ctx, KArgs& A, int ti, const int32_t* order, int32
     int rc = ensure_tier(ctx, ti);
     if (rc) return rc;
     const Tier& t = ctx->tier[ti];
-    A.order = order; A.n_reads = n; A.tier = ti;
+    A.order = order; A.n_reads = n;
+    A.tier = ti - 1;   // in trace records: dumps start on the configured tier, 0
     A.retry = (ti + 1 < N_TIERS) ? ctx->d_retry[ti & 1] : nullptr;
     A.arena = t.arena; A.arena_stride = t.stride;
     A.dir_log2_max = t.dir_log2_max; A.list_cap = t.list_cap; A.cand_cap = t.cand_cap; A.sort_cap = t.sort_cap;

@@ -183,3 +183,15 @@ def test_cigars_run_in_the_room_there_is(H):
     ctx.value = h.context().value
     h.lib.fake_memory(h.lib.fake_used() + 10 * MIB)
     assert _cigar(h, ctx, g) == gwfa.ERR_NOMEM
+
+
+def test_trace_records_count_tiers_from_the_configured_one(H):
+    """The tier in a record's `attempt`: 0 on the configured tier, where dumps
+    start, pruned or not, then 1 and 2."""
+    h, ctx, g = H
+    b = h._buf.ctypes.data_as(fake_hip._P)
+    h.lib.fake_overflow(18, 5)
+    h.lib.fake_overflow(20, 2)
+    for o in (gwfa.opts(), gwfa.opts(**PRUNED)):
+        assert h.lib.gwfa_align_dump_dev(ctx, g, 100, b, b, b, None, ctypes.byref(o), b, b, 0, b, b, 0, b, None) == 0
+        assert [(x[0], x[4]) for x in h.launches()] == [(18, 0), (20, 1), (22, 2)]
