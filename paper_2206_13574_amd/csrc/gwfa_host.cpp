@@ -362,7 +362,7 @@ int gwfa_ctx_config(gwfa_ctx* c, int32_t lanes, int32_t n_groups, int32_t dir_lo
 int64_t gwfa_packed_words(int64_t n_bases) { return n_bases < 0 ? 0 : (n_bases + 31) / 32 + 2; }
 
 int gwfa_graph_create(gwfa_ctx* ctx, int32_t n_vtx, const uint8_t* seq, const int64_t* seq_off, int64_t n_edge,
-                      const int32_t* edge_src, const int32_t* edge_dst, gwfa_graph** out) {
+                      const int32_t* edge_src, const int32_t* edge_dst, gwfa_graph** out) try {
     if (!ctx || !out || n_vtx <= 0 || !seq_off || n_edge < 0) return GWFA_ERR_ARG;
     if (n_edge > 0 && (!edge_src || !edge_dst)) return GWFA_ERR_ARG;
     *out = nullptr;
@@ -453,6 +453,8 @@ int gwfa_graph_create(gwfa_ctx* ctx, int32_t n_vtx, const uint8_t* seq, const in
     }
     *out = g;
     return GWFA_OK;
+} catch (const std::bad_alloc&) {   // host memory for the edge and label records, before any device memory
+    return GWFA_ERR_NOMEM;
 }
 
 void gwfa_graph_destroy(gwfa_graph* g) {

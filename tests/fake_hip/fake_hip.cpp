@@ -17,6 +17,15 @@
 #include "gwfa.h"
 #include "gwfa_internal.h"
 
+// Host allocations of the library of at least this size fail.
+static size_t new_limit = SIZE_MAX;
+void* operator new(size_t n) {
+    if (n >= new_limit) throw std::bad_alloc();
+    return malloc(n ? n : 1);
+}
+void operator delete(void* p) noexcept { free(p); }
+void operator delete(void* p, size_t) noexcept { free(p); }
+
 namespace {
 struct Block { size_t bytes; bool real; };
 std::map<uintptr_t, Block> blocks;
@@ -46,6 +55,7 @@ void run(const Launch& l) {
 extern "C" {
 void fake_memory(int64_t bytes) { total = (size_t)bytes; }
 void fake_largest(int64_t bytes) { largest = bytes < 0 ? SIZE_MAX : (size_t)bytes; }   // largest block to be had
+void fake_new_limit(int64_t bytes) { new_limit = bytes < 0 ? SIZE_MAX : (size_t)bytes; }
 int64_t fake_used() { return (int64_t)used; }
 void fake_overflow(int dir_log2, int queries) { overflow[dir_log2] = queries; }
 void fake_clear() { launches.clear(); last = hipSuccess; }

@@ -195,3 +195,15 @@ def test_trace_records_count_tiers_from_the_configured_one(H):
     for o in (gwfa.opts(), gwfa.opts(**PRUNED)):
         assert h.lib.gwfa_align_dump_dev(ctx, g, 100, b, b, b, None, ctypes.byref(o), b, b, 0, b, b, 0, b, None) == 0
         assert [(x[0], x[4]) for x in h.launches()] == [(18, 0), (20, 1), (22, 2)]
+
+
+@pytest.mark.parametrize("bytes_", [40_000, 160_000, 320_000])
+def test_graphs_report_host_memory_that_is_not_there(H, bytes_):
+    """10,000 vertices: edge offsets of 40 kB, records of 160 kB, label records
+    of their targets of 320 kB."""
+    h, ctx, g = H
+    before = h.lib.fake_used()
+    h.lib.fake_new_limit(bytes_)
+    rc = h.graph(ctx, n_vtx=10_000)
+    h.lib.fake_new_limit(-1)
+    assert rc == gwfa.ERR_NOMEM and h.lib.fake_used() == before
