@@ -9,6 +9,14 @@
 constexpr int STAT_SLOTS = 64;
 // Counters of the work queue, on lines of their own.
 constexpr int Q_SLOTS = 8, Q_STRIDE = 32;
+// Place in the work queue of take `taken` of counter `slot`; an empty take's
+// may lie past 2^31.
+__host__ __device__ constexpr int64_t queue_place(int32_t taken, int slots, int slot) {
+    return (int64_t)taken * slots + slot;
+}
+// Workgroups of the screen pass, SCREEN places each.
+constexpr int SCREEN = 256;
+constexpr int64_t screen_blocks(int32_t n_reads) { return ((int64_t)n_reads + SCREEN - 1) / SCREEN; }
 
 struct KArgs {
     // graph (device)

@@ -2386,10 +2386,10 @@ __global__ __launch_bounds__(BLOCK, waves_per_simd(BLOCK, MODE)) void k_align(KA
     while (left > 0) {
         if (threadIdx.x == 0) S.read = atomicAdd(&A.queue[Q_STRIDE * slot], 1);
         __syncthreads();
-        const int ridx = __builtin_amdgcn_readfirstlane(S.read) * slots + slot;
+        const int64_t ridx = queue_place(__builtin_amdgcn_readfirstlane(S.read), slots, slot);
         __syncthreads();
         if (ridx < n_q) {
-            const int r = __builtin_amdgcn_readfirstlane(A.order ? A.order[ridx] : ridx);
+            const int r = __builtin_amdgcn_readfirstlane(A.order ? A.order[ridx] : (int)ridx);
             if (r >= 0) align_read<BLOCK, MODE>(arena, r, S);
         } else {
             --left;
@@ -2411,7 +2411,6 @@ __global__ __launch_bounds__(BLOCK, waves_per_simd(BLOCK, MODE)) void k_align(KA
 // parameters index the graph in bounds.  It also resets the queue and the
 // call's counters (20,011 queries: 6 us; 60 us when one workgroup compacted
 // the list, and a launch of its own for the reset).
-constexpr int SCREEN = 256;
 __device__ __forceinline__ void reset_counters(int32_t* queue, ull* path_cursor, int32_t* retry_count, ull* dump_count) {
     if (threadIdx.x < Q_SLOTS) queue[Q_STRIDE * threadIdx.x] = 0;
     if (threadIdx.x == 0) {
@@ -2581,8 +2580,7 @@ void* gwfa_static_scratch(int device) {
 
 hipError_t gwfa_launch_screen(const KArgs& A, int32_t* valid, hipStream_t st) {
     (void)hipGetLastError();
-    const int blocks = (A.n_reads + gwfa_dev::SCREEN - 1) / gwfa_dev::SCREEN;
-    hipLaunchKernelGGL(gwfa_dev::k_screen, dim3(blocks), dim3(gwfa_dev::SCREEN), 0, st, A, valid);
+    hipLaunchKernelGGL(gwfa_dev::k_screen, dim3((unsigned)screen_blocks(A.n_reads)), dim3(SCREEN), 0, st, A, valid);
     return hipGetLastError();
 }
 

@@ -33,7 +33,7 @@ class Host:
             f = getattr(self.lib, name, None)
             if f is not None:
                 f.restype, f.argtypes = res, args
-        for name in ("fake_used", "fake_cigar_groups"):
+        for name in ("fake_used", "fake_cigar_groups", "fake_screen_blocks", "fake_queue_place"):
             getattr(self.lib, name).restype = ctypes.c_int64
         self.lib.fake_memory.argtypes = [ctypes.c_int64]
         self.lib.fake_largest.argtypes = self.lib.fake_new_limit.argtypes = [ctypes.c_int64]

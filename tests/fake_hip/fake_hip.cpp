@@ -68,6 +68,8 @@ void fake_launch(int i, int64_t* out) {
     const int64_t v[7] = {l.A.dir_log2_max, l.lanes, l.groups, l.A.n_reads, l.A.tier, live, l.A.arena_stride};
     memcpy(out, v, sizeof v);
 }
+int64_t fake_screen_blocks(int32_t n) { return screen_blocks(n); }
+int64_t fake_queue_place(int32_t taken, int32_t slots, int32_t slot) { return queue_place(taken, slots, slot); }
 int64_t fake_cigar_groups() { return cig_groups; }
 int fake_last_error() { return (int)last; }
 

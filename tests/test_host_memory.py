@@ -207,3 +207,16 @@ def test_graphs_report_host_memory_that_is_not_there(H, bytes_):
     rc = h.graph(ctx, n_vtx=10_000)
     h.lib.fake_new_limit(-1)
     assert rc == gwfa.ERR_NOMEM and h.lib.fake_used() == before
+
+
+def test_launch_arithmetic_at_the_largest_batch(host):
+    """2^31 - 1 queries: the screen pass has a thread for each, and an empty
+    take of any counter lies behind the last query."""
+    n = 2**31 - 1
+    assert host.lib.fake_screen_blocks(n) == 2**23 and host.lib.fake_screen_blocks(1) == 1
+    assert host.lib.fake_screen_blocks(256) == 1 and host.lib.fake_screen_blocks(257) == 2
+    for slot in range(8):
+        last = (n - 1 - slot) // 8                  # the counter's last query
+        assert host.lib.fake_queue_place(last, 8, slot) < n
+        for empty in (1, 4096):
+            assert host.lib.fake_queue_place(last + empty, 8, slot) >= n
