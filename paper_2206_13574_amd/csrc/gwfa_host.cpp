@@ -26,9 +26,24 @@ namespace {
 // Queries that outgrow a tier are re-run on the next.
 constexpr int N_TIERS = 4;
 constexpr int32_t PRUNED_DIR_LOG2 = 14, PRUNED_LIST_CAP = 4096, PRUNED_DIR_FACTOR = 16;
-// Algorithm 4 keeps diagonals that lag by less than a_diff: with more lag than
-// this the record sets of long reads outgrow tier 0 and would be run twice.
-constexpr int32_t PRUNED_A_DIFF = 1024;
+// Pruned runs start on tier 0 where they prune enough for it: Algorithm 4 up to
+// this lag, the network up to this gate and period and from this log-odds of a
+// diagonal being needed (1 : 160,000) on.  4,096 reads of 10-30 kb, 1-10% errors,
+// on the 10 Mb graph, tier 0 against the configured tier on the kernel without
+// it: lag 50 11.7 and 41.9 ms, 1,000 74 and 117; gate 32 19 and 50, 512 77 and
+// 142, 1,024 (181 reads run twice) 280 and 230; period 32 37 and 73, 128 (3 run
+// twice) 124 and 173; threshold -12 41 and 73, -20 (2,015 run twice) 470 and 318.
+constexpr int32_t PRUNED_A_DIFF = 1024, PRUNED_GATE = 512, PRUNED_PERIOD = 32;
+constexpr float PRUNED_THRESHOLD = -12.0f;
+// How many record pages such a run takes for each vertex of its walk: measured
+// there at 10% errors (lag 50 1.2, 1,000 4.4; network 1.5, gate 512 4.0, period
+// 32 2.1, threshold -12 2.5).  The screen pass leaves longer reads than tier 0
+// holds by this to the configured tier: 1,000 reads of 120 kb at lag 1,000 took
+// 213 ms, 320 of them run twice, and 119 ms on the configured tier alone.
+float pruned_pages_per_vtx(const KArgs& A) {
+    if (A.prune == GWFA_PRUNE_HEURISTIC) return 1.2f + (float)A.a_diff / 310.0f;
+    return 1.4f + (float)A.mlp_gate / 200.0f + (float)A.mlp_period / 30.0f + (A.keep_threshold < -8.0f ? 1.2f : 0.0f);
+}
 
 struct Tier {
     int32_t dir_log2_max = 16;
@@ -510,6 +525,7 @@ static int fill_args(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, const 
     memset(&A, 0, sizeof(A));
     A.seg = g->d_seg; A.seg_off = g->d_seg_off; A.out_off = g->d_out_off; A.out_dst = g->d_out_dst;
     A.vinfo = g->d_vinfo; A.vlab = g->d_vlab; A.vsucc = g->d_vsucc; A.n_vtx = g->n_vtx;
+    A.vtx_per_base = (float)g->n_vtx / (float)std::max<int64_t>(g->bases, 1);
     A.rd = (const unsigned long long*)d_packed; A.rd_off = d_read_off; A.v_start = d_v_start;
     A.v_end = d_v_end; A.end_vertex = opts->end_vertex;
     A.res = d_res; A.path_buf = d_path_buf; A.path_cap = d_path_buf ? path_cap : 0;
@@ -546,7 +562,9 @@ static int ensure_lists(gwfa_ctx* ctx, int32_t n_reads) {
 // tier: it prunes nothing unless asked to).
 static int first_tier(const KArgs& A) {
     if (A.dump) return 1;
-    return A.prune == GWFA_PRUNE_LEARNED || (A.prune == GWFA_PRUNE_HEURISTIC && A.a_diff <= PRUNED_A_DIFF) ? 0 : 1;
+    if (A.prune == GWFA_PRUNE_LEARNED)
+        return A.mlp_gate <= PRUNED_GATE && A.mlp_period <= PRUNED_PERIOD && A.keep_threshold >= PRUNED_THRESHOLD ? 0 : 1;
+    return A.prune == GWFA_PRUNE_HEURISTIC && A.a_diff <= PRUNED_A_DIFF ? 0 : 1;
 }
 
 // Lanes per query of a launch: the configured ones, or, for an exact batch that
@@ -574,6 +592,7 @@ static int set_tier(gwfa_ctx* ctx, KArgs& A, int ti, const int32_t* order, int32
     A.arena = t.arena; A.arena_stride = t.stride;
     A.dir_log2_max = t.dir_log2_max; A.list_cap = t.list_cap; A.cand_cap = t.cand_cap; A.sort_cap = t.sort_cap;
     A.dir_factor = ti == 0 ? std::min(ctx->dir_factor, PRUNED_DIR_FACTOR) : ctx->dir_factor;
+    A.pages_per_vtx = ti == 0 ? pruned_pages_per_vtx(A) : 0.0f;
     A.o_hdr = t.o_hdr; A.o_dir = t.o_dir; A.o_pages = t.o_pages; A.o_mkey = t.o_mkey;
     A.o_tv = t.o_tv; A.o_tt = t.o_tt; A.o_lists = t.o_lists; A.o_cand = t.o_cand; A.o_sort = t.o_sort;
     *groups = (int)std::min<int64_t>(t.groups, n);
@@ -635,12 +654,12 @@ static int align_begin(gwfa_ctx* ctx, const gwfa_graph* g, int32_t n_reads, cons
     if (rc || n_reads == 0) return rc;
     A.v_off = d_start_off;
     A.v_off_hi = d_start_hi;
-    A.order = d_order;
-    A.n_reads = n_reads;
-    HIPCHK(ctx, gwfa_launch_screen(A, ctx->d_valid, st));
     int groups = 0;
     rc = set_first_tier(ctx, A, ctx->d_valid, n_reads, &groups, ti);
     if (rc) return rc;
+    KArgs S0 = A;   // the screen pass reads the caller's order
+    S0.order = d_order;
+    HIPCHK(ctx, gwfa_launch_screen(S0, ctx->d_valid, st));
     HIPCHK(ctx, gwfa_launch_align(A, launch_lanes(ctx, A, n_reads), groups, st));
     return GWFA_OK;
 }
@@ -783,12 +802,11 @@ static int plan_capture(gwfa_plan* p) {
     p->exec = nullptr;
     p->graph = nullptr;
     int groups = 0;
-    KArgs S0 = p->A;   // the screen pass reads the caller's order
-    S0.order = p->order;
-    S0.n_reads = p->n_reads;
     const int rc = set_first_tier(ctx, p->A, ctx->d_valid, p->n_reads, &groups, &p->tier);   // allocates before the capture
     if (rc) return rc;
     p->freed = ctx->tier[p->tier].freed;
+    KArgs S0 = p->A;   // the screen pass reads the caller's order
+    S0.order = p->order;
     hipError_t e = hipSuccess;
     if (!p->cap) e = hipStreamCreateWithFlags(&p->cap, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipStreamBeginCapture(p->cap, hipStreamCaptureModeThreadLocal);

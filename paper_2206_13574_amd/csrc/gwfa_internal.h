@@ -34,7 +34,7 @@ struct KArgs {
     const int32_t* v_start;
     const int32_t* v_off;            // per-query start offsets in the start vertex, or null (all 0)
     const int32_t* v_off_hi;         // per-query end of a free start window, or null (= v_off)
-    const int32_t* order;            // work-queue order (-1: no query) or null
+    const int32_t* order;            // work-queue order (-1: no query, -2 - r: r is left to the next tier) or null
     const int32_t* v_end;            // per-query end vertices (global form) or null
     int32_t end_vertex;              // end vertex of every query (global form) or -1
     int32_t n_reads;
@@ -64,6 +64,9 @@ struct KArgs {
     int64_t arena_stride;
     int32_t dir_log2_max, dir_factor, list_cap, cand_cap, sort_cap;
     int64_t o_hdr, o_dir, o_pages, o_mkey, o_tv, o_tt, o_lists, o_cand, o_sort;
+    // queries expected to need more pages than this tier has are left to the
+    // next: vertices per base of the graph, pages per vertex of the walk (0: all are tried)
+    float vtx_per_base, pages_per_vtx;
 };
 
 // 4-byte words of one wavefront list per entry of its capacity (gwfa_kernels.hip,

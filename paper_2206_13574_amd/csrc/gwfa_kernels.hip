@@ -2361,6 +2361,17 @@ __device__ void align_read(char* __restrict__ arena, int r, Shared<BLOCK, MODE>&
 constexpr int waves_per_simd(int block, int mode) {
     return mode == 2 ? 2 : (block >= 512 ? (mode == 0 ? 4 : 1) : (mode == 3 ? (block == 64 ? 2 : 3) : 4));
 }
+// Query r as if it had outgrown this tier.
+__device__ void leave_to_next(const KArgs& A, int r) {
+    gwfa_result* const out = A.res + r;
+    const int64_t t = (int64_t)wall_clock64();
+    out->t_begin = t; out->t_end = t;
+    out->dist = -1; out->end_v = -1; out->end_off = -1; out->status = GWFA_ST_ARENA;
+    out->path_off = -1; out->path_len = 0; out->n_scores = 0; out->work = 0;
+    out->start_off = A.v_off ? A.v_off[r] : 0; out->clip = 0;
+    if (A.retry) A.retry[atomicAdd(A.retry_count, 1)] = r;
+}
+
 template <int BLOCK, int MODE>
 __global__ __launch_bounds__(BLOCK, waves_per_simd(BLOCK, MODE)) void k_align(KArgs A) {
     constexpr bool LEARN = MODE >= 2;
@@ -2374,7 +2385,8 @@ __global__ __launch_bounds__(BLOCK, waves_per_simd(BLOCK, MODE)) void k_align(KA
         }
     }
     if (threadIdx.x < 16) S.acc[threadIdx.x] = 0;
-    // The work queue: query ridx of `order` (-1: turned away by the screen pass).
+    // The work queue: query ridx of `order` (-1: turned away by the screen pass,
+    // -2 - r: query r is left to the next tier).
     // Device atomics on one address take their turns (7 ns each), so a batch
     // with many queries per workgroup is dealt out by Q_SLOTS counters, every
     // Q_SLOTS-th query each; a workgroup goes on to the next counter when one
@@ -2391,6 +2403,7 @@ __global__ __launch_bounds__(BLOCK, waves_per_simd(BLOCK, MODE)) void k_align(KA
         if (ridx < n_q) {
             const int r = __builtin_amdgcn_readfirstlane(A.order ? A.order[ridx] : (int)ridx);
             if (r >= 0) align_read<BLOCK, MODE>(arena, r, S);
+            else if (r < -1 && threadIdx.x == 0) leave_to_next(A, -2 - r);
         } else {
             --left;
             slot = slot + 1 == slots ? 0 : slot + 1;
@@ -2408,9 +2421,14 @@ __global__ __launch_bounds__(BLOCK, waves_per_simd(BLOCK, MODE)) void k_align(KA
 // end vertex is out of range gets its result here, with status
 // GWFA_ST_BAD_INPUT, and leaves -1 in its place of `valid`; the others are
 // listed there, so that the alignment kernel only ever takes queries whose
-// parameters index the graph in bounds.  It also resets the queue and the
-// call's counters (20,011 queries: 6 us; 60 us when one workgroup compacted
-// the list, and a launch of its own for the reset).
+// parameters index the graph in bounds.  A query r expected to need more pages
+// than half the tier's directory (a run ends there) is listed as -2 - r; where
+// more than 1 in 64 are, so are all: the next tier runs after this one, and a
+// batch on both takes the sum of two long reads' times (900 reads of 10-120 kb,
+// 17% of them too long: 220 ms split by length, 164 on the kernel without
+// tiers), while the few of a large batch pass under it.  It also resets the queue
+// and the call's counters (20,011 queries: 6 us; 60 us when one workgroup
+// compacted the list, and a launch of its own for the reset).
 __device__ __forceinline__ void reset_counters(int32_t* queue, ull* path_cursor, int32_t* retry_count, ull* dump_count) {
     if (threadIdx.x < Q_SLOTS) queue[Q_STRIDE * threadIdx.x] = 0;
     if (threadIdx.x == 0) {
@@ -2422,8 +2440,23 @@ __device__ __forceinline__ void reset_counters(int32_t* queue, ull* path_cursor,
 __global__ __launch_bounds__(SCREEN) void k_screen(KArgs A, int32_t* valid) {
     if (blockIdx.x == 0) reset_counters(A.queue, A.path_cursor, A.retry_count, A.dump_count);
     const int32_t idx = (int32_t)blockIdx.x * SCREEN + (int32_t)threadIdx.x;
-    if (idx >= A.n_reads) return;
-    const int32_t r = A.order ? A.order[idx] : idx;
+    const bool any = idx < A.n_reads;
+    const int32_t r = any ? (A.order ? A.order[idx] : idx) : 0;
+    bool leave = false;
+    if (A.pages_per_vtx > 0.0f) {
+        const float most = (float)(1 << (A.dir_log2_max - 1)) / (A.vtx_per_base * A.pages_per_vtx);   // bases
+        auto big = [&](int32_t x) { return (float)(A.rd_off[x + 1] - A.rd_off[x]) > most; };
+        // the batch, by up to SCREEN places spread over it (the same in every workgroup)
+        const int32_t m = min(SCREEN, A.n_reads);
+        bool seen = false;
+        if ((int32_t)threadIdx.x < m) {
+            const int32_t j = (int32_t)((int64_t)threadIdx.x * A.n_reads / m);
+            seen = big(A.order ? A.order[j] : j);
+        }
+        const int n_big = __syncthreads_count(seen);
+        leave = 64 * n_big > m || big(r);
+    }
+    if (!any) return;
     const int32_t vs = A.v_start[r];
     const int32_t ve = A.v_end ? A.v_end[r] : A.end_vertex;
     const int32_t j0 = A.v_off ? A.v_off[r] : 0;
@@ -2438,7 +2471,7 @@ __global__ __launch_bounds__(SCREEN) void k_screen(KArgs A, int32_t* valid) {
         out->path_off = -1; out->path_len = 0; out->n_scores = 0; out->work = 0;
         out->start_off = j0; out->clip = 0;
     }
-    valid[idx] = good ? r : -1;
+    valid[idx] = good ? (leave ? -2 - r : r) : -1;
 }
 
 // Four ASCII bases (the first in the low byte) -> 8 bits, the first base in

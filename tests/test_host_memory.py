@@ -220,3 +220,15 @@ def test_launch_arithmetic_at_the_largest_batch(host):
         assert host.lib.fake_queue_place(last, 8, slot) < n
         for empty in (1, 4096):
             assert host.lib.fake_queue_place(last + empty, 8, slot) >= n
+
+
+@pytest.mark.parametrize("o,first", [
+    (dict(prune=gwfa.PRUNE_HEURISTIC, a_diff=1024), 14), (dict(prune=gwfa.PRUNE_HEURISTIC, a_diff=1025), 18),
+    (dict(prune=gwfa.PRUNE_LEARNED, keep_threshold=-12.0, mlp_gate=512, mlp_period=32), 14),
+    (dict(prune=gwfa.PRUNE_LEARNED, keep_threshold=-12.5, mlp_gate=512, mlp_period=32), 18),
+    (dict(prune=gwfa.PRUNE_LEARNED, keep_threshold=float("-inf")), 18),
+    (dict(prune=gwfa.PRUNE_LEARNED, keep_threshold=-12.0, mlp_gate=513, mlp_period=32), 18),
+    (dict(prune=gwfa.PRUNE_LEARNED, keep_threshold=-12.0, mlp_gate=512, mlp_period=33), 18)])
+def test_first_tier_of_what_prunes_enough(H, o, first):
+    h, ctx, g = H
+    assert h.align(ctx, g, **o) == 0 and h.dirs() == [first]
