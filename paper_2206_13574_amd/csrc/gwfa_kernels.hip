@@ -2424,10 +2424,10 @@ __global__ __launch_bounds__(BLOCK, waves_per_simd(BLOCK, MODE)) void k_align(KA
 // parameters index the graph in bounds.  A query r expected to need more pages
 // than half the tier's directory (a run ends there) is listed as -2 - r; where
 // more than 1 in 64 are, so are all: the next tier runs after this one, and a
-// batch on both takes the sum of two long reads' times (900 reads of 10-120 kb,
-// 17% of them too long: 220 ms split by length, 164 on the kernel without
-// tiers), while the few of a large batch pass under it.  It also resets the queue
-// and the call's counters (20,011 queries: 6 us; 60 us when one workgroup
+// batch on both takes the sum of two long reads' times (900 reads of 10-120 kb
+// at lag 400, 17% of them too long: 220 ms split by length, 129 on the next tier
+// alone), while the few of a large batch matter less than its rest.  It also
+// resets the queue and the call's counters (20,011 queries: 6 us; 60 us when one workgroup
 // compacted the list, and a launch of its own for the reset).
 __device__ __forceinline__ void reset_counters(int32_t* queue, ull* path_cursor, int32_t* retry_count, ull* dump_count) {
     if (threadIdx.x < Q_SLOTS) queue[Q_STRIDE * threadIdx.x] = 0;
