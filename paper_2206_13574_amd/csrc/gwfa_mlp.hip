@@ -276,14 +276,26 @@ __global__ void k_cast(const float* __restrict__ src, uint16_t* __restrict__ dst
     if (i < n) dst[i] = f2bf(src[i]);
 }
 
-// Logits of n samples: the network of the alignment kernel's inference routine
-// (same products and roundings, the last sums in another order), persistent
-// waves with the weights in registers.  A wave takes 64 samples, one per lane,
+// Lanes 0..31: a of lanes l and l+32 added; lanes 32..63: b of them.
+__device__ __forceinline__ float sum_rows32(float a, float b) {
+    const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(x[0]) + __uint_as_float(x[1]);
+}
+// Rows of 16 lanes: a of rows 0 and 1 added, b of rows 0 and 1, a of rows 2
+// and 3, b of rows 2 and 3.
+__device__ __forceinline__ float sum_rows16(float a, float b) {
+    const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(x[0]) + __uint_as_float(x[1]);
+}
+
+// Logits of n samples, bit for bit those of the alignment kernel's inference
+// routine (same products, roundings and order of the sums), persistent waves
+// with the weights in registers.  A wave takes 64 samples, one per lane,
 // and scores them 16 at a time.  The weights of layer 1 stand in all four
 // quarters of the product's 32 positions and the samples of tile t in quarter
 // t, so each lane's inputs are its operand as they lie; layer 2 is taken
 // transposed (units by samples), so its inputs are layer 1's outputs and the
-// last sum is 16 products in a lane and two exchanges.
+// last sum is 16 products in a lane and five exchanges of rows (no LDS).
 // 1,000,003 samples: 29 us (36 MB: 1.2 TB/s); with the weights gathered from
 // LDS for every tile and 20 exchanges 81 us.  Bound by the roundings and
 // packing between the layers (about 120 vector instructions per 16 samples).
@@ -345,17 +357,22 @@ __global__ __launch_bounds__(256, 3) void k_logits(const float* __restrict__ fea
 #pragma unroll
                 for (int i = 0; i < 4; ++i) h[c >> 1][4 * (c & 1) + i] = (__bf16)fmaxf(d[i], 0.0f);
             }
-            float z = 0.0f;
+            // the last layer in the order of the alignment kernel's routine: over
+            // units 16c + u, then pairs of u that differ in bit 3 (group g xor 2), bit
+            // 2 (group g xor 1), bit 1 and bit 0 (i)
+            float q[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 f32x4 a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w2a[0][c], h[0], b2[c], 0, 0, 0);
                 a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w2a[1][c], h[1], a, 0, 0, 0);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) z = fmaf(w3[c][i], round_bf16(fmaxf(a[i], 0.0f)), z);
+                for (int i = 0; i < 4; ++i) q[i] = fmaf(w3[c][i], round_bf16(fmaxf(a[i], 0.0f)), q[i]);
             }
-            z += __shfl_xor(z, 16, 64);
-            z += __shfl_xor(z, 32, 64);
-            z_out = grp == t ? z + b3 : z_out;
+            // rows 0, 1: q0, rows 2, 3: q1 (q2, q3); then rows q0, q2, q1, q3
+            const float z = sum_rows16(sum_rows32(q[0], q[1]), sum_rows32(q[2], q[3]));
+            const float y = sum_rows16(z, z);                     // rows 0, 1: q0 + q2; rows 2, 3: q1 + q3
+            const float logit = b3 + sum_rows32(y, y);            // (by every lane, not under a branch of some)
+            z_out = grp == t ? logit : z_out;
         }
         if (ok) out[b] = z_out;
     }
