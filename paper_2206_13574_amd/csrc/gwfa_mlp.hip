@@ -326,6 +326,21 @@ __global__ __launch_bounds__(256, 3) void k_logits(const float* __restrict__ fea
         }
     }
     const float b3 = bf2f(w[MW_B3]);
+    // Weights that are not finite must not meet the zeros that stand for the other
+    // quarters' samples (0 times infinity is not a number): then only the first
+    // quarter holds weights, and every tile's samples are brought there.
+    uint32_t top = 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) top = max(top, (uint32_t)(w[(16 * c + col) * 8 + i] & 0x7f80u));
+    const bool first_only = __ballot(top == 0x7f80u) != 0;
+    if (first_only && grp != 0) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) w1a[c][i] = bf_bits(0);
+    }
     const bool wide = (stride & 3) == 0 && (reinterpret_cast<uintptr_t>(feat) & 15) == 0;   // rows of 16-byte words
     const int64_t waves = (int64_t)gridDim.x * 4;
     for (int64_t g = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); g * 64 < n; g += waves) {
@@ -350,6 +365,12 @@ __global__ __launch_bounds__(256, 3) void k_logits(const float* __restrict__ fea
             bf16x8 xb;
 #pragma unroll
             for (int i = 0; i < 8; ++i) xb[i] = grp == t ? xp[i] : bf_bits(0);
+            if (first_only) {
+                const int4 p = __builtin_bit_cast(int4, xp);
+                const int4 q = make_int4(__shfl(p.x, 16 * t + col, 64), __shfl(p.y, 16 * t + col, 64),
+                                         __shfl(p.z, 16 * t + col, 64), __shfl(p.w, 16 * t + col, 64));
+                xb = __builtin_bit_cast(bf16x8, grp == 0 ? q : make_int4(0, 0, 0, 0));
+            }
             bf16x8 h[2];   // units 32ks + 4g + i and 32ks + 16 + 4g + i of sample 16t + m
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
