@@ -98,6 +98,9 @@ __global__ __launch_bounds__(64 * GRAD_WAVES, 1) void k_grad(const float* __rest
     __syncthreads();
     const int64_t tiles = (n + 15) / 16;
     for (int64_t t = (int64_t)blockIdx.x * GRAD_WAVES + wv; t < tiles; t += (int64_t)gridDim.x * GRAD_WAVES) {
+        // the rows that fill up the last tile: every activation and gradient 0, so
+        // that no weight, infinite ones among them, is multiplied into the sums
+        const bool row = 16 * t + col < n;
         // inputs: two features per lane, column 8 is 1 (the bias)
         {
             const int64_t b = 16 * t + col;
@@ -129,7 +132,7 @@ __global__ __launch_bounds__(64 * GRAD_WAVES, 1) void k_grad(const float* __rest
             d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1a[c], xb, d, 0, 0, 0);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                h[4 * c + i] = round_bf16(fmaxf(d[i], 0.0f));
+                h[4 * c + i] = row ? round_bf16(fmaxf(d[i], 0.0f)) : 0.0f;
                 T.h[col * LD + 16 * c + 4 * grp + i] = h[4 * c + i];
             }
         }
@@ -169,7 +172,7 @@ __global__ __launch_bounds__(64 * GRAD_WAVES, 1) void k_grad(const float* __rest
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 dw3[c] = fmaf(dz, h2[c], dw3[c]);
-                g2[c][i] = a2[c][i] > 0.0f ? dz * w3[c] : 0.0f;
+                g2[c][i] = ok[i] && a2[c][i] > 0.0f ? dz * w3[c] : 0.0f;
                 db2[c] += g2[c][i];
                 T.g[(4 * grp + i) * LD + 16 * c + col] = g2[c][i];
             }

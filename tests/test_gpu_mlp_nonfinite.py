@@ -1,6 +1,6 @@
 """GPU: weights that are not finite reach the samples whose inputs they
-multiply, and no others: batch logits against numpy with the same
-rules (a product of zero and infinity is not a number, a ReLU of that is 0)."""
+multiply, and no others: batch logits and the gradient against numpy with the
+same rules (a product of zero and infinity is not a number, a ReLU of that is 0)."""
 import numpy as np
 import pytest
 
@@ -44,3 +44,29 @@ def test_logits_of_infinite_weights(G, at):  # noqa: F811
             gw.mlp_logits_dev(ctx, torch.from_numpy(f).to(ctx.tdev), SCALE, _bits(ctx, w), out)
             z = out.cpu().numpy()
             assert np.array_equal(z, _layers(w, M.inputs(f, SCALE)).astype(np.float32), equal_nan=True), (value, n)
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 63, 64, 65])
+def test_gradient_of_an_infinite_weight_no_sample_meets(G, n):  # noqa: F811
+    """Unit 5 of layer 1 is off for every sample (a positive bias, a negative
+    input), so its infinite weight into unit 7 of layer 2 turns that unit off as
+    well and meets no gradient: the gradient is finite, as without the two
+    units, whatever the rows that fill up the last tile hold."""
+    gw, ctx = G
+    torch = ctx.torch
+    w, _, f, y = _case(n, 8, 0, 7200 + n)
+    f[:, 0] = -2.0 - np.abs(f[:, 0])
+    W1, b1, W2, b2, W3, b3 = [a.copy() for a in M.unpack(w)]
+    W1[5], b1[5] = 0.0, 1.0
+    W1[5, 0] = 4.0
+    W2[7], b2[7], W2[:, 5] = 0.0, -1.0, 0.0
+    grads = []
+    for value in (0.0, INF):
+        W2[7, 5] = value
+        grad = torch.full((M.N_PARAM,), 7.0, dtype=torch.float32, device=ctx.tdev)
+        loss = torch.full((1,), 7.0, dtype=torch.float32, device=ctx.tdev)
+        gw.mlp_grad_dev(ctx, torch.from_numpy(f).to(ctx.tdev), torch.from_numpy(y).to(ctx.tdev), SCALE,
+                        _bits(ctx, np.concatenate([W1.ravel(), b1, W2.ravel(), b2, W3, [b3]])), grad, loss,
+                        pos_weight=3.0)
+        grads.append(np.append(grad.cpu().numpy(), loss.cpu().numpy()))
+    assert np.isfinite(grads[0]).all() and np.array_equal(grads[0], grads[1])
