@@ -76,13 +76,30 @@ def _mode_opts(mode: str):
                      mlp_period=W["period"]), W
 
 
+def _launch_config(cfg: dict, n: int, mode: str) -> dict:
+    """The configuration to time: the library launches exact batches small
+    enough to be resident at more lanes per query with more than were
+    configured, unless the number of workgroups is given.  Here it is given
+    for them (one a query), so that the lanes timed are the lanes launched:
+    candidates of one launch would differ by noise alone."""
+    if mode == "exact" and cfg["groups"] == 0 and n <= WIDENED:
+        return dict(cfg, groups=n)
+    return cfg
+
+
+# no batch of more queries is launched with more lanes than configured: 128
+# lanes, the narrowest it can be widened to, are resident at most 8 times on each
+# of 256 compute units
+WIDENED = 2048
+
+
 def _time_config(g, sub, cfg, repeats, stream, mode: str = "exact"):
     from . import gwfa
     import torch
     o, W = _mode_opts(mode)
     ctx = gwfa.Context(0, stream=stream)
     try:
-        ctx.config(**cfg)
+        ctx.config(**_launch_config(cfg, sub.n, mode))
         if W is not None:
             ctx.mlp_load(W["w_bf16"], W["scale"])
         graph = gwfa.Graph.of(ctx, g)
