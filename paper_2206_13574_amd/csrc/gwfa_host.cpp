@@ -635,8 +635,7 @@ static int run_tiers(gwfa_ctx* ctx, KArgs& A, int ti0, int32_t n, bool launched,
         ctx->rerun_total += h_retry;
         order = ctx->d_retry[ti & 1];
         n = h_retry;
-        // reset the queue and the retry counter, keep the path cursor and the dump counter
-        HIPCHK(ctx, gwfa_launch_reset(ctx->d_queue, nullptr, ctx->d_retry_count, nullptr, st));
+        HIPCHK(ctx, gwfa_launch_reset(ctx->d_queue, ctx->d_retry_count, st));
     }
     return GWFA_OK;
 }

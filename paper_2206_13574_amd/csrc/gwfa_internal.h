@@ -79,8 +79,8 @@ hipError_t gwfa_launch_align(const KArgs& A, int lanes, int groups, hipStream_t 
 int gwfa_align_blocks_per_cu(int lanes, int prune);
 hipError_t gwfa_launch_pack(const uint8_t* ascii, int64_t n, unsigned long long* out, int64_t n_words,
                             int32_t* err, hipStream_t st);
-hipError_t gwfa_launch_reset(int32_t* queue, unsigned long long* cursor, int32_t* retry_count,
-                             unsigned long long* dump_count, hipStream_t st);
+// resets the queue and the retry counter before a re-run
+hipError_t gwfa_launch_reset(int32_t* queue, int32_t* retry_count, hipStream_t st);
 // Working memory of the entry point that allocates nothing
 // (gwfa_align_batch_static_dev): a file-scope device array of STATIC_BYTES
 // per device holding a header (queue, counters), the screened query list

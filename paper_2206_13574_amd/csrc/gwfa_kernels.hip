@@ -146,21 +146,10 @@ __device__ __forceinline__ int32_t lcp(const ull* __restrict__ qw, int64_t qp, i
     return l;
 }
 
-__device__ int dir_find(const ull* __restrict__ dir, uint32_t mask, ull key) {
-    uint32_t h = dhash(key) & mask;
-    for (uint32_t p = 0; p <= mask; ++p) {
-        const ull c = __hip_atomic_load(&dir[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (c == key) return (int)h;
-        if (c == 0) return -1;
-        h = (h + 1) & mask;
-    }
-    return -1;
-}
-
-// Find-or-insert; counts insertions in *n_ins.  -1 when the table is full.
-// The same, continuing from `c`, a value read from slot h earlier (it may be
-// stale: a slot only ever goes from empty to a key, and an empty slot is
-// claimed by compare-and-swap, which sees the current value).
+// Finds or inserts a key, going on from `c`, a value read from slot h earlier (it
+// may be stale: a slot only ever goes from empty to a key, and an empty slot
+// is claimed by compare-and-swap, which sees the current value); counts
+// insertions in *n_ins.  -1 when the table is full.
 __device__ int dir_settle(ull* dir, uint32_t mask, ull key, uint32_t h, ull c, int* n_ins) {
     for (uint32_t p = 0; p <= mask; ++p) {
         if (p > 0) c = __hip_atomic_load(&dir[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -174,6 +163,7 @@ __device__ int dir_settle(ull* dir, uint32_t mask, ull key, uint32_t h, ull c, i
     }
     return -1;
 }
+// The same from the key's home slot.
 __device__ __forceinline__ int dir_insert(ull* dir, uint32_t mask, ull key, int* n_ins) {
     const uint32_t h = dhash(key) & mask;
     return dir_settle(dir, mask, key, h, __hip_atomic_load(&dir[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), n_ins);
@@ -245,16 +235,6 @@ __device__ __forceinline__ int block_excl_scan(int x, int& total, int* scan) {
     lds_barrier();
     total = __builtin_amdgcn_readfirstlane(tot);   // block-uniform: kept in a scalar register
     return off + ex;
-}
-
-// Reads a shared word that other threads may update in the phase that just
-// ended, so that every thread takes the same decision: barrier, read,
-// barrier (nobody can write it again before everybody has read it).
-__device__ __forceinline__ int read_uniform(const int& x) {
-    __syncthreads();
-    const int v = *(const volatile int*)&x;
-    __syncthreads();
-    return __builtin_amdgcn_readfirstlane(v);
 }
 
 // A wavefront list: per entry the diagonal (v, k), its offset o and record
@@ -2531,9 +2511,8 @@ __global__ void k_zero(ull* p, int64_t n_words) {
         p[i] = 0ull;
 }
 
-__global__ void k_reset(int32_t* queue, ull* path_cursor, int32_t* retry_count, ull* dump_count) {
-    reset_counters(queue, path_cursor, retry_count, dump_count);
-}
+// Before a re-run: the walks' and the records' cursors go on.
+__global__ void k_reset(int32_t* queue, int32_t* retry_count) { reset_counters(queue, nullptr, retry_count, nullptr); }
 
 }  // namespace gwfa_dev
 
@@ -2617,9 +2596,8 @@ hipError_t gwfa_launch_screen(const KArgs& A, int32_t* valid, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t gwfa_launch_reset(int32_t* queue, unsigned long long* cursor, int32_t* retry_count,
-                             unsigned long long* dump_count, hipStream_t st) {
+hipError_t gwfa_launch_reset(int32_t* queue, int32_t* retry_count, hipStream_t st) {
     (void)hipGetLastError();
-    hipLaunchKernelGGL(gwfa_dev::k_reset, dim3(1), dim3(64), 0, st, queue, cursor, retry_count, dump_count);
+    hipLaunchKernelGGL(gwfa_dev::k_reset, dim3(1), dim3(64), 0, st, queue, retry_count);
     return hipGetLastError();
 }

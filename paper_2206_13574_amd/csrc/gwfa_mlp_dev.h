@@ -25,44 +25,9 @@ __device__ __forceinline__ uint16_t f2bf(float x) {
     return (uint16_t)(__float_as_uint(round_bf16(x)) >> 16);
 }
 
-// logit of one entry: x = bf16(f * scale); the order of every sum is the
-// order of the loops below
-__device__ __forceinline__ float mlp_logit(const float* f, const float* scale, const uint16_t* w) {
-    float x[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) x[i] = round_bf16(f[i] * scale[i]);
-    // first-layer activations as packed bfloat16 pairs (32 registers)
-    uint32_t h1[32];
-#pragma unroll
-    for (int j2 = 0; j2 < 32; ++j2) {
-        float a0 = bf2f(w[MW_B1 + 2 * j2]), a1 = bf2f(w[MW_B1 + 2 * j2 + 1]);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            a0 = fmaf(bf2f(w[(2 * j2) * 8 + i]), x[i], a0);
-            a1 = fmaf(bf2f(w[(2 * j2 + 1) * 8 + i]), x[i], a1);
-        }
-        h1[j2] = (__float_as_uint(round_bf16(fmaxf(a0, 0.0f))) >> 16) |
-                 (__float_as_uint(round_bf16(fmaxf(a1, 0.0f))) & 0xffff0000u);
-    }
-    float z = bf2f(w[MW_B3]);
-#pragma unroll 1
-    for (int j = 0; j < 64; ++j) {
-        float acc = bf2f(w[MW_B2 + j]);
-        const uint32_t* row = reinterpret_cast<const uint32_t*>(w + MW_W2 + j * 64);
-#pragma unroll
-        for (int m = 0; m < 32; ++m) {
-            const uint32_t wp = row[m];
-            acc = fmaf(__uint_as_float(wp << 16), __uint_as_float(h1[m] << 16), acc);
-            acc = fmaf(__uint_as_float(wp & 0xffff0000u), __uint_as_float(h1[m] & 0xffff0000u), acc);
-        }
-        z = fmaf(bf2f(w[MW_W3 + j]), round_bf16(fmaxf(acc, 0.0f)), z);
-    }
-    return z;
-}
-
 // ---------------------------------------------------------------------------
-// The same network for the 64 entries of a wave at once, on the matrix
-// cores.  Every lane of the wave calls it together (uniform control flow,
+// The network for the 64 entries of a wave at once, on the matrix cores:
+// x = bf16(f * scale), each ReLU's output rounded to bfloat16.  Every lane of the wave calls it together (uniform control flow,
 // all 64 lanes active) with its own entry's features and gets its entry's
 // logit.  Entries are taken 16 at a time (four tiles t); all products are
 // v_mfma_f32_16x16x32_bf16 (bfloat16 operands, float32 sums):
@@ -76,8 +41,7 @@ __device__ __forceinline__ float mlp_logit(const float* f, const float* scale, c
 //     weights are gathered in the same order, so no data moves between
 //     lanes;
 //   layer 3: per entry, a sum over the 16 lanes of a row group.
-// Weights, biases and roundings are those of mlp_logit; only the order of
-// the float32 sums differs.  w: the 4801 weights, 16-byte aligned.
+// w: the 4801 weights, 16-byte aligned.
 // ---------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
@@ -166,13 +130,6 @@ __device__ __forceinline__ float mlp_logit_wave(const float* f, const float* sca
         if (grp == t) z_out = b3 + mine;
     }
     return z_out;
-}
-
-// The same as a call of its own: its registers then do not add to those of
-// the alignment loop around it (inlined there, the compiler spills the
-// loop's registers around the matrix products).
-__device__ __attribute__((noinline)) float mlp_logit_wave_call(const float* f, const float* scale, const uint16_t* w) {
-    return mlp_logit_wave(f, scale, w);
 }
 
 }  // namespace gwfa_nn

@@ -143,7 +143,7 @@ hipError_t gwfa_launch_align(const KArgs& A, int lanes, int groups, hipStream_t)
 }
 int gwfa_align_blocks_per_cu(int lanes, int prune) { return std::min(16, (prune == 2 ? 512 : 1024) / lanes); }
 hipError_t gwfa_launch_pack(const uint8_t*, int64_t, unsigned long long*, int64_t, int32_t*, hipStream_t) { return hipSuccess; }
-hipError_t gwfa_launch_reset(int32_t*, unsigned long long*, int32_t* retry_count, unsigned long long*, hipStream_t) {
+hipError_t gwfa_launch_reset(int32_t*, int32_t* retry_count, hipStream_t) {
     *retry_count = 0;
     return hipSuccess;
 }
