@@ -281,7 +281,7 @@ int gwfa_align_dump_dev(gwfa_ctx *ctx, const gwfa_graph *g, int32_t n_reads, con
  * outgrows it gets GWFA_ST_ARENA and is not re-run (gwfa_align_batch_dev
  * re-runs such queries with more memory).  At most 2^20 queries per call
  * (GWFA_ERR_ARG beyond, with the reason in gwfa_last_error).  Launches
- * kernels only (queue reset, screen pass, alignment) on `hip_stream`.  Every
+ * kernels only (screen pass, alignment) on `hip_stream`.  Every
  * call on one device shares that device's array: calls that overlap in time
  * on one device (from any context or thread) race and must not be issued.
  * GWFA_ERR_DEVICE if the array could not be set up on this device. */

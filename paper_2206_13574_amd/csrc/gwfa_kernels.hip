@@ -1412,10 +1412,12 @@ __device__ __attribute__((noinline)) void narrow_scores(int64_t karg) {
 // slots of which one is taken on average, and three barriers and a scan
 // ordered the outputs of every batch (800 vector instructions a wave and
 // batch; here about 160 per 64 sources and 220 per 64 outputs).  What bounds
-// it now: latency.  The waves wait 72 to 77% of their cycles, for the two round
-// trips of a batch and for its stores, with the vector units 33 to 42% busy;
-// the registers (128, four waves a SIMD) leave room for no deeper queue.  Per
-// call: 20,000 reads on the 1 Mb DAG 135.5 -> 115 ms, 3,001 noisy reads on the
+// it now: the two round trips of a batch and its stores.  On the 1 Mb and the
+// 10 Mb workload the waves wait 66 and 72% of their cycles, with the vector
+// units 50% busy and 381 and 927 cycles to a read of the L2, of which 52 and
+// 38% hit; the latter moves 5.2 TB/s, as much as a copy (a record word is read
+// for every candidate, also where it decides nothing).  The registers (128,
+// four waves a SIMD) leave room for no deeper queue.  Per call: 20,000 reads on the 1 Mb DAG 135.5 -> 115 ms, 3,001 noisy reads on the
 // 10 Mb graph 459 -> 397 ms (its hardest read takes most of that alone), 500
 // reads of 100 kb through loops 518 -> 237 ms (its lists of 25,000 to 50,000
 // entries are merged by the bitmap now, which holds 65,536 positions instead
