@@ -438,7 +438,8 @@ int gwfa_label_entries(int32_t n_vtx, const uint8_t *seq, const int64_t *seq_off
 /* Kernel-level counters accumulated since the last reset (device totals over
  * every query): [0] wavefront entries (sum |F_s|), [1] crossings admitted,
  * [2] pages created, [3] 32-base compare chunks in the extension,
- * [4] expansion candidates admitted, [5] queries re-run for memory,
+ * [4] expansion candidates admitted, [5] queries re-run for memory, or left
+ * to more of it without a run,
  * [6] MLP evaluations, [7] entries dropped by pruning, [8] scores run,
  * [9]..[12] device wall-clock ticks (100 MHz) summed over queries spent in
  * the expansion+extension pass, the crossing rounds, the crossing merge and

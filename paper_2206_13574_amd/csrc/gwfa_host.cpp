@@ -208,6 +208,9 @@ int ensure_tier(gwfa_ctx* ctx, int ti) {
     if (t.arena) return GWFA_OK;
     layout(t);
     size_t bytes = (size_t)t.stride * (size_t)t.groups;
+    size_t free_b = 0, total_b = 0;
+    // (every pruned call on a full device comes here: no attempt that is bound to fail)
+    if (ti == 0 && hipMemGetInfo(&free_b, &total_b) == hipSuccess && free_b < bytes) return GWFA_ERR_NOMEM;
     if (!dev_alloc(ctx, &t.arena, (int64_t)bytes)) {
         ctx->err = "arena allocation of " + std::to_string(bytes) + " bytes failed";
         return GWFA_ERR_NOMEM;

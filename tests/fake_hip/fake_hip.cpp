@@ -32,6 +32,7 @@ std::map<uintptr_t, Block> blocks;
 size_t total = (size_t)288 << 30, used = 0, largest = SIZE_MAX;
 uintptr_t next_addr = (uintptr_t)1 << 46;
 hipError_t last = hipSuccess;
+int failed = 0;
 bool capturing = false;
 int overflow[32];
 struct Launch { KArgs A; int lanes, groups; };
@@ -71,10 +72,11 @@ void fake_launch(int i, int64_t* out) {
 int64_t fake_screen_blocks(int32_t n) { return screen_blocks(n); }
 int64_t fake_queue_place(int32_t taken, int32_t slots, int32_t slot) { return queue_place(taken, slots, slot); }
 int64_t fake_cigar_groups() { return cig_groups; }
+int fake_failed() { return failed; }      // allocations refused so far
 int fake_last_error() { return (int)last; }
 
 hipError_t hipMalloc(void** p, size_t n) {
-    if (capturing || used + n > total || n > largest) return last = hipErrorOutOfMemory;
+    if (capturing || used + n > total || n > largest) { ++failed; return last = hipErrorOutOfMemory; }
     const bool real = n <= (size_t)64 << 20;
     *p = real ? calloc(1, n + 1) : (void*)next_addr;
     if (!real) next_addr += (n + 8191) / 4096 * 4096;

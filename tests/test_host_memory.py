@@ -232,3 +232,13 @@ def test_launch_arithmetic_at_the_largest_batch(host):
 def test_first_tier_of_what_prunes_enough(H, o, first):
     h, ctx, g = H
     assert h.align(ctx, g, **o) == 0 and h.dirs() == [first]
+
+
+def test_full_devices_are_not_asked_again_and_again(H):
+    h, ctx, g = H
+    assert h.align(ctx, g) == 0
+    h.lib.fake_memory(h.lib.fake_used() + 64 * MIB)
+    before = h.lib.fake_failed()
+    for _ in range(5):
+        assert h.align(ctx, g, **PRUNED) == 0
+    assert h.lib.fake_failed() == before
